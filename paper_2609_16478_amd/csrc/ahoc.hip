@@ -46,6 +46,7 @@ template <typename T> struct Prec {
   T* af = nullptr;    // alpha on face nodes (N_q)
   T* bufA = nullptr;  // interior work (V)
   T* bufB = nullptr;  // interior work (U)
+  T* scr = nullptr;   // interior work of the passes of lengths without an FFT plan (else null)
   T* qT = nullptr;    // N_q, Q in this precision
   T* zq = nullptr;    // N_q zeros
   T* wf[3] = {nullptr, nullptr, nullptr};  // per axis: one-sided face weights w_lo(k), w_hi(k)
@@ -124,6 +125,7 @@ struct ahoc_handle {
   double *h1 = nullptr, *h2 = nullptr, *nrm = nullptr, *part = nullptr, *y = nullptr;
   double *resid = nullptr, *beta = nullptr, *bvec = nullptr, *dq = nullptr, *rvec = nullptr, *R = nullptr;
   double* zvec = nullptr;    // preconditioned Krylov vector
+  double* zt = nullptr;      // scratch of the preconditioner's face transforms (an axis without an FFT plan)
   // GMRES operator (preconditioner and Schur matvec) captured as a HIP graph per operator
   // precision ([0] FP32, [1] FP64), replayed once per Krylov step from the fixed input gin
   // to the fixed output gout; captured on its second use, eager when capture fails
@@ -321,6 +323,13 @@ bool faces_available(const Geom& g) {
   return true;
 }
 
+// Whether every axis has an FFT plan.
+bool has_plans(const Geom& g) {
+  for (int a = 0; a < g.dim; ++a)
+    if (!dst_ppt(g.n[a])) return false;
+  return true;
+}
+
 template <typename T> int prec_init(ahoc_handle* h, Prec<T>& P, int tile_opt, hipStream_t st) {
   const Geom& g = h->g;
   for (int a = 0; a < g.dim; ++a) {
@@ -407,6 +416,7 @@ template <typename T> int prec_init(ahoc_handle* h, Prec<T>& P, int tile_opt, hi
   }
   TRY(alloc_int(h, &P.bufA, st));
   TRY(alloc_int(h, &P.bufB, st));
+  if (!has_plans(g)) TRY(alloc_int(h, &P.scr, st));
   // setup-time choice between the FFT and the matrix-core pass for the plain passes of the
   // operator, timed on their own shapes: the x (row) passes; in 3-D also the strided y passes
   if (g.dim == 2) {
@@ -467,22 +477,27 @@ template <typename T> void prec_free(Prec<T>& P) {
 }
 
 // Dirichlet solve on an interior array: buf <- scale * S (S in / lambda), in place unless
-// `in` is given (then the first pass reads it and `in` is left unchanged).
+// `in` is given (then the first pass reads it and `in` is left unchanged).  The plain passes of
+// an axis without an FFT plan go from buf to P.scr or back (each such axis has two of them, so
+// the result ends in buf), its fused pass through the other of the two.
 template <typename T>
 int poisson(ahoc_handle* h, Prec<T>& P, T* buf, const DstScale<T>& sc, hipStream_t st, const T* in = nullptr,
             const RowLift<T>* lf = nullptr) {
   const Geom& g = h->g;
   const double pass_bytes = 2.0 * (double)g.nint * g.nb * sizeof(T);  // one read + one write of the array
   const T* src = in ? in : buf;
+  T* cur = buf;
   bool first = true;
   auto run = [&](int kind, const DstTables<T>& tb, long long outer, long long inner,
                  const DstScale<T>* f, int tile) -> int {
     hipEvent_t e = tbegin(h, st);
+    T* other = P.scr ? (cur == buf ? P.scr : buf) : nullptr;
+    if (!tb.ppt && !f && other) std::swap(cur, other);
     // with lf, the first (row) pass adds the lift's face layers to its input while loading
-    const int rc = (first && lf) ? dst_rows_lift_pass<T>(tb.N, tb.tw, tb.sn, src, buf, outer, g.px, *lf, st)
-                                 : dst_pass<T>(tb, src, buf, outer, inner, g.px, f, tile, st);
+    const int rc = (first && lf) ? dst_rows_lift_pass<T>(tb.N, tb.tw, tb.sn, src, cur, outer, g.px, *lf, st)
+                                 : dst_pass<T>(tb, src, cur, outer, inner, g.px, f, tile, st, nullptr, other);
     first = false;
-    src = buf;
+    src = cur;
     tend(h, kind, e, pass_bytes, st);
     return rc;
   };
@@ -949,21 +964,21 @@ int precond_init(ahoc_handle* h, hipStream_t st) {
 }
 
 // 2-D DST-I of every face block of a Q-layout vector, from x into y (y may equal x; the
-// first pass of each face reads x, later ones work in place on y).  Faces x-, x+ hold
+// first pass of each face reads x, in 3-D it writes `mid`, which may be y).  Faces x-, x+ hold
 // [k][j], y-, y+ [k][i], z-, z+ [j][i] (lower axis fastest, no padding).  A square 2-D
 // batch (N_x = N_y) is one row pass: its Q vector is 4 nb rows of N-1 entries.
-int face_dst_q(ahoc_handle* h, const double* x, double* y, hipStream_t st) {
+int face_dst_q(ahoc_handle* h, const double* x, double* y, double* mid, hipStream_t st) {
   const Geom& g = h->g;
   const DstTables<double>* tb = h->ptb;
   const long long ox = g.face_off[0], oy = g.face_off[2];
   if (g.dim == 3) {
     const long long oz = g.face_off[4];
-    TRY(dst_pass<double>(tb[1], x + ox, y + ox, 2LL * g.ni[2], 1, g.ni[1], nullptr, 0, st));
-    TRY(dst_pass<double>(tb[2], y + ox, y + ox, 2, g.ni[1], g.ni[1], nullptr, 0, st));
-    TRY(dst_pass<double>(tb[0], x + oy, y + oy, 2LL * g.ni[2], 1, g.ni[0], nullptr, 0, st));
-    TRY(dst_pass<double>(tb[2], y + oy, y + oy, 2, g.ni[0], g.ni[0], nullptr, 0, st));
-    TRY(dst_pass<double>(tb[0], x + oz, y + oz, 2LL * g.ni[1], 1, g.ni[0], nullptr, 0, st));
-    TRY(dst_pass<double>(tb[1], y + oz, y + oz, 2, g.ni[0], g.ni[0], nullptr, 0, st));
+    TRY(dst_pass<double>(tb[1], x + ox, mid + ox, 2LL * g.ni[2], 1, g.ni[1], nullptr, 0, st));
+    TRY(dst_pass<double>(tb[2], mid + ox, y + ox, 2, g.ni[1], g.ni[1], nullptr, 0, st));
+    TRY(dst_pass<double>(tb[0], x + oy, mid + oy, 2LL * g.ni[2], 1, g.ni[0], nullptr, 0, st));
+    TRY(dst_pass<double>(tb[2], mid + oy, y + oy, 2, g.ni[0], g.ni[0], nullptr, 0, st));
+    TRY(dst_pass<double>(tb[0], x + oz, mid + oz, 2LL * g.ni[1], 1, g.ni[0], nullptr, 0, st));
+    TRY(dst_pass<double>(tb[1], mid + oz, y + oz, 2, g.ni[0], g.ni[0], nullptr, 0, st));
   } else if (g.n[0] == g.n[1] && g.nq == 4LL * g.ni[0]) {
     TRY(dst_pass<double>(tb[0], x, y, 4LL * g.nb, 1, g.ni[0], nullptr, 0, st));
   } else {  // each face line of every instance of a batch (instances nq apart)
@@ -979,9 +994,12 @@ int face_dst_q(ahoc_handle* h, const double* x, double* y, hipStream_t st) {
 int precond_apply(ahoc_handle* h, const double* v, double* y, hipStream_t st) {
   const Geom& g = h->g;
   hipEvent_t e = tbegin(h, st);
-  TRY(face_dst_q(h, v, y, st));
-  TRY(precond_modes<double>(g, h->pc, h->qc, y, st));
-  TRY(face_dst_q(h, y, y, st));
+  // with a scratch vector (an axis without an FFT plan) no pass works in place
+  double* mid = h->zt ? h->zt : y;
+  double* f = g.dim == 3 ? y : mid;
+  TRY(face_dst_q(h, v, f, mid, st));
+  TRY(precond_modes<double>(g, h->pc, h->qc, f, st));
+  TRY(face_dst_q(h, f, y, mid, st));
   tend(h, AHOC_K_PRECOND, e, (double)TQ(g) * 16.0, st);
   return ST_OK;
 }
@@ -1589,6 +1607,7 @@ int setup_impl(const ahoc_problem* pbs, int count, hipStream_t st, ahoc_handle* 
   TRY(alloc_t(h, &h->dq, TQ(g)));
   TRY(alloc_t(h, &h->rvec, TQ(g)));
   TRY(alloc_t(h, &h->zvec, TQ(g)));
+  if (!has_plans(g)) TRY(alloc_t(h, &h->zt, TQ(g)));
   if (h->opt.use_graph) {
     TRY(alloc_t(h, &h->gin, TQ(g)));
     TRY(alloc_t(h, &h->gout, TQ(g)));

@@ -190,11 +190,14 @@ int face_reduce(const T* W, long long planes, int ny, int nx, int px, const T* w
 
 // One pass of the batched DST-I along an axis of an interior array viewed as
 // [outer][L][inner] (L = N-1).  inner == 1 means contiguous pencils: `outer` rows
-// of L elements starting `pitch` elements apart.
+// of L elements starting `pitch` elements apart.  tmp: optional array of out's size, apart
+// from in and out, that a fused pass of a length without an FFT plan keeps its scaled
+// spectrum in (a pass that writes elsewhere than it reads can split a pencil's outputs over
+// work-groups).
 template <typename T>
 int dst_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long long inner,
              long long pitch, const DstScale<T>* fused, int tile_seqs, hipStream_t st,
-             const DstFaces<T>* faces = nullptr);
+             const DstFaces<T>* faces = nullptr, T* tmp = nullptr);
 
 // Length-specialised kernels (dst_fast.hip) for N in {32, 64, 96, ..., 4096}.
 bool dst_fast_supported(int N);
@@ -302,11 +305,11 @@ template <typename T> int dst_plan_only(DstTables<T>& tb, int N);
 constexpr int DST_MAX_N = 8192;
 bool dst_supported(int N);
 int dst_ppt(int N);
-// Direct O(N) per output pass for any length (same layouts and fused scaling as dst_pass;
+// O(N) per output pass for any length (same layouts, fused scaling and tmp as dst_pass;
 // `sn2` holds sin(pi j / N), j = 0..2N-1).
 template <typename T>
 int dst_direct_pass(int N, const T* sn2, const T* in, T* out, long long outer, long long inner, long long pitch,
-                    const DstScale<T>* fused, hipStream_t st);
+                    const DstScale<T>* fused, hipStream_t st, T* tmp = nullptr);
 int dst_default_tile(int N, int elem_bytes);
 
 }  // namespace ahoc

@@ -563,7 +563,7 @@ int dst_get_variant() { return g_variant_.load(std::memory_order_relaxed); }
 template <typename T>
 int dst_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long long inner,
              long long pitch, const DstScale<T>* fused, int tile_seqs, hipStream_t st,
-             const DstFaces<T>* faces) {
+             const DstFaces<T>* faces, T* tmp) {
   const int N = tb.N;
   const int g_variant = dst_get_variant();
   if (inner == 1 && pitch < N - 1) return ST_INVALID;
@@ -582,9 +582,9 @@ int dst_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long 
   }
   if (faces && faces->mode) return ST_UNSUPPORTED;  // face sums only in the specialised kernels
   const int ppt = tb.ppt;
-  if (!ppt) {  // no FFT plan for this length: the direct sine sums
+  if (!ppt) {  // no FFT plan for this length: the sine sums
     if (!tb.sn) return ST_INVALID;
-    return dst_direct_pass<T>(N, tb.sn, in, out, outer, inner, pitch, fused, st);
+    return dst_direct_pass<T>(N, tb.sn, in, out, outer, inner, pitch, fused, st, tmp);
   }
   if (!tb.tw) return ST_INVALID;
   const int tps = N / ppt;
@@ -636,9 +636,9 @@ template int dst_plan_only<double>(DstTables<double>&, int);
 template void dst_tables_free<float>(DstTables<float>&);
 template void dst_tables_free<double>(DstTables<double>&);
 template int dst_pass<float>(const DstTables<float>&, const float*, float*, long long, long long,
-                             long long, const DstScale<float>*, int, hipStream_t, const DstFaces<float>*);
+                             long long, const DstScale<float>*, int, hipStream_t, const DstFaces<float>*, float*);
 template int dst_pass<double>(const DstTables<double>&, const double*, double*, long long,
                               long long, long long, const DstScale<double>*, int, hipStream_t,
-                              const DstFaces<double>*);
+                              const DstFaces<double>*, double*);
 
 }  // namespace ahoc

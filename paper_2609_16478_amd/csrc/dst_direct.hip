@@ -1,16 +1,29 @@
-// Direct DST-I pass for transform lengths without a radix-2/3 FFT plan (gfx950).
+// DST-I pass for transform lengths without a radix-2/3 FFT plan (gfx950).
 //
-// X_k = sum_{m=1}^{N-1} x_m sin(pi k m / N), k = 1..N-1, evaluated as written: O(N) work
-// per output, with sin(pi j / N) read from a one-period table (index k m mod 2N, advanced
-// incrementally).  It gives every grid length from the one-sided formula's minimum
-// (N_a >= 4, Sec. 2.2) upward a pass with the same layouts as the FFT kernels: rows
-// (contiguous pencils, `pitch` apart) or strided pencils [outer][L][inner].  The fused
-// form (slowest axis of a Poisson solve) transforms, multiplies mode k of column c by
-// scale / (A_c + B_c s_this[k-1]) -- the compact Laplacian's eigenvalue, Sec. 2.3 -- and
-// transforms back before one store.
+// X_k = sum_{m=1}^{N-1} x_m sin(pi k m / N), k = 1..N-1, O(N) work per output, with
+// sin(pi j / N) read from a one-period table (index k m mod 2N, advanced incrementally).
+// It gives every grid length from the one-sided formula's minimum (N_a >= 4, Sec. 2.2)
+// upward a pass with the same layouts as the FFT kernels: rows (contiguous pencils, `pitch`
+// apart) or strided pencils [outer][L][inner].  The fused form (slowest axis of a Poisson
+// solve) transforms, multiplies mode k of column c by scale / (A_c + B_c s_this[k-1]) -- the
+// compact Laplacian's eigenvalue, Sec. 2.3 -- and transforms back.
 //
-// A work-group stages a tile of P pencils in LDS (reads complete before any write, so the
-// pass may run in place), then each thread forms outputs of one pencil at a time.
+// k_dst_sine runs the sums on the matrix cores as two half-size products: with
+// sin(pi k (N-m) / N) = (-1)^(k+1) sin(pi k m / N), odd outputs are sums over m <= N/2 of
+// e_m = x_m + x_{N-m}, even ones of o_m = x_m - x_{N-m} (e = x_m at m = N/2), N^2 flops per
+// pencil, accumulated in the working precision.  What bounds it: the matrix cores from N of
+// about 200 (FP64, 128 flop per cycle and CU) upward, memory below.  A wavefront owns TO pairs
+// of 16 odd and 16 even outputs next to each other for TP x 16 pencils; e and o of a chunk of m
+// are staged in LDS once for all of them.  The sine operand is gathered from the period table
+// in LDS instead of read as a stored matrix: no N^2 / 2 table per length (16 MB at N = 2000)
+// that each handle would build and each work-group stream through L2, and the gather's bank
+// conflicts hide behind the MFMAs (64 cycles each in FP64) once two pencil tiles share it.
+// Against one thread per output (the form this replaces): FP32 along y of 199 x 149 x 119
+// points 549 -> 19 us a call, an FP64 Poisson solve of 99 x 89 x 74 points 227 -> 61 us, a 2-D
+// 500 x 300 FP64 solve (25 GMRES iterations) 118.8 -> 7.4 ms; errors against 64-bit sums no
+// larger (FP32 2.2e-7 -> 1.6e-7).
+// k_dst_direct, one thread per output and the whole pencil in LDS, remains for in-place
+// passes of N > 2048, whose outputs k_dst_sine could not hold in registers.
 #include "common.h"
 
 #include <mutex>
@@ -129,6 +142,184 @@ template <typename T> __global__ void __launch_bounds__(256) k_dst_direct(Direct
   }
 }
 
+template <typename T> struct SineOps;
+template <> struct SineOps<float> {
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ v4 mfma(float a, float b, v4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  // row of the 16x16 result held in element r of lane group lk = lane / 16
+  static __device__ __forceinline__ int row(int lk, int r) { return 4 * lk + r; }
+  static constexpr int PAD = 4;  // LDS row padding of the row-pass tile -> conflict-free reads
+};
+template <> struct SineOps<double> {
+  typedef double v4 __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ v4 mfma(double a, double b, v4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int lk, int r) { return lk + 4 * r; }
+  static constexpr int PAD = 2;
+};
+
+template <typename T> struct SineArgs {
+  const T* in;
+  T* out;
+  const T* sn2;       // sin(pi j / N), j = 0..2N-1
+  int N;
+  long long outer, inner, pitch;
+  long long ntile_inner;
+  bool scaled;        // multiply by the eigen scaling before the store (strided pencils)
+  DstScale<T> fs;
+};
+
+// m values of one LDS chunk, and the words of one half's (e or o) tile
+template <int TP> constexpr int sine_chunk() { return 2048 / (16 * TP); }
+template <typename T, bool ROWS, int TP> constexpr int sine_half() {
+  return ROWS ? 16 * TP * (sine_chunk<TP>() + SineOps<T>::PAD) : sine_chunk<TP>() * (TP == 1 ? 16 : 16 * TP + 16);
+}
+
+// grid.x: tiles of 16 TP pencils; grid.y: groups of blockDim.x / 64 * TO output pairs (one
+// group when the pass runs in place: the tile's reads end, at a barrier, before its writes).
+template <typename T, bool ROWS, int TO, int TP>
+__global__ void __launch_bounds__(1024) k_dst_sine(SineArgs<T> a) {
+  using S = SineOps<T>;
+  using v4 = typename S::v4;
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int P = 16 * TP, MC = sine_chunk<TP>(), HALF = sine_half<T, ROWS, TP>();
+  constexpr int LDX = MC + S::PAD;             // rows: [pencil][m]
+  constexpr int LDC = TP == 1 ? 16 : P + 16;   // strided: [m][pencil]
+  T* xe = reinterpret_cast<T*>(smem);
+  T* xo = xe + HALF;
+  T* tab = xo + HALF;
+  const int N = a.N, L = N - 1, two_n = 2 * N, Hm = N / 2;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nt = blockDim.x;
+  const int li = lane & 15, lk = lane >> 4;
+  long long base, c0 = 0;
+  int ncols;
+  if (ROWS) {
+    base = (long long)blockIdx.x * P;
+    const long long left = a.outer - base;
+    ncols = left < P ? (int)left : P;
+  } else {
+    const long long o = blockIdx.x / a.ntile_inner;
+    c0 = (blockIdx.x - o * a.ntile_inner) * (long long)P;
+    base = o * (long long)L * a.inner + c0;
+    const long long left = a.inner - c0;
+    ncols = left < P ? (int)left : P;
+  }
+  for (int i = threadIdx.x; i < two_n; i += nt) tab[i] = a.sn2[i];
+  // this lane's outputs of pair t: k = 2 j + 1 (odd) and 2 j + 2 (even), j = j0[t] + li; its
+  // sine index starts at m = 1 + lk and advances by 4 k per step, modulo the period
+  const int p0 = (blockIdx.y * (nt >> 6) + w) * TO;
+  unsigned ie[TO], io[TO], de[TO], dd[TO];
+#pragma unroll
+  for (int t = 0; t < TO; ++t) {
+    const unsigned k = 2u * (16u * (p0 + t) + li) + 1u;
+    ie[t] = (k % two_n) * (1u + lk) % two_n;
+    io[t] = ((k + 1u) % two_n) * (1u + lk) % two_n;
+    de[t] = 4u * (k % two_n) % two_n;
+    dd[t] = 4u * ((k + 1u) % two_n) % two_n;
+  }
+  v4 ae[TO][TP], ao[TO][TP];
+#pragma unroll
+  for (int t = 0; t < TO; ++t)
+#pragma unroll
+    for (int b = 0; b < TP; ++b) ae[t][b] = ao[t][b] = v4{T(0), T(0), T(0), T(0)};
+  for (int m0 = 0; m0 < Hm; m0 += MC) {
+    const int kc = Hm - m0 < MC ? (Hm - m0 + 3) & ~3 : MC;
+    if (m0) __syncthreads();  // the last chunk's reads are done
+    for (int e = threadIdx.x; e < kc * P; e += nt) {
+      int p, q;
+      if (ROWS) {
+        p = e / kc;
+        q = e - p * kc;
+      } else {
+        q = e / P;
+        p = e - q * P;
+      }
+      const int m = m0 + q + 1;
+      T x = 0, y = 0;
+      if (m <= Hm && p < ncols) {
+        if (ROWS) {
+          const T* rp = a.in + (base + p) * a.pitch;
+          x = rp[m - 1];
+          if (2 * m != N) y = rp[N - m - 1];
+        } else {
+          const T* cp = a.in + base + p;
+          x = cp[(long long)(m - 1) * a.inner];
+          if (2 * m != N) y = cp[(long long)(N - m - 1) * a.inner];
+        }
+      }
+      const int at = ROWS ? p * LDX + q : q * LDC + p;
+      xe[at] = x + y;
+      xo[at] = x - y;
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int s = 0; s < kc; s += 4) {
+      T be[TP], bo[TP];
+#pragma unroll
+      for (int b = 0; b < TP; ++b) {
+        const int at = ROWS ? (16 * b + li) * LDX + s + lk : (s + lk) * LDC + 16 * b + li;
+        be[b] = xe[at];
+        bo[b] = xo[at];
+      }
+#pragma unroll
+      for (int t = 0; t < TO; ++t) {
+        const T se = tab[ie[t]], so = tab[io[t]];
+        ie[t] += de[t];
+        io[t] += dd[t];
+        ie[t] = min(ie[t], ie[t] - (unsigned)two_n);
+        io[t] = min(io[t], io[t] - (unsigned)two_n);
+#pragma unroll
+        for (int b = 0; b < TP; ++b) {
+          if (ROWS) {
+            ae[t][b] = S::mfma(be[b], se, ae[t][b]);
+            ao[t][b] = S::mfma(bo[b], so, ao[t][b]);
+          } else {
+            ae[t][b] = S::mfma(se, be[b], ae[t][b]);
+            ao[t][b] = S::mfma(so, bo[b], ao[t][b]);
+          }
+        }
+      }
+    }
+  }
+  if (gridDim.y == 1) __syncthreads();  // in place: every read of the tile before its writes
+#pragma unroll
+  for (int b = 0; b < TP; ++b) {
+    T A = 1, B = 0, sc = 1;
+    if (!ROWS && a.scaled) {
+      const long long col = c0 + 16 * b + li;
+      const long long ib = col / a.fs.na;
+      const long long ia = col - ib * a.fs.na;
+      sc = a.fs.scale;
+      if (col < a.inner && ia < a.fs.nva) {
+        const T sa = a.fs.s_a[ia];
+        const T sb = a.fs.s_b ? a.fs.s_b[ib] : T(0);
+        A = sa + sb + a.fs.c_ab * sa * sb + a.fs.a0 + a.fs.ka * sa + a.fs.kb * sb;
+        B = T(1) + a.fs.c_ta * sa + a.fs.c_tb * sb + a.fs.kt;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < TO; ++t) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int p = 16 * b + (ROWS ? S::row(lk, r) : li);
+        const int k = 2 * (16 * (p0 + t) + (ROWS ? li : S::row(lk, r)));  // positions k, k + 1 (from 0)
+        if (p >= ncols) continue;
+        T ve = ae[t][b][r], vo = ao[t][b][r];
+        if (!ROWS && a.scaled) {
+          if (k < L) ve *= sc / (A + B * a.fs.s_this[k]);
+          if (k + 1 < L) vo *= sc / (A + B * a.fs.s_this[k + 1]);
+        }
+        T* op = ROWS ? a.out + (base + p) * a.pitch + k : a.out + base + (long long)k * a.inner + p;
+        if (k < L) op[0] = ve;
+        if (k + 1 < L) op[ROWS ? 1 : a.inner] = vo;
+      }
+    }
+  }
+}
+
 constexpr size_t DIRECT_LDS_MAX = 160 * 1024;
 
 template <typename T> void set_direct_lds_attr() {
@@ -139,15 +330,80 @@ template <typename T> void set_direct_lds_attr() {
   });
 }
 
+template <typename T, bool ROWS, int TO, int TP>
+int sine_launch(const SineArgs<T>& a, long long tiles, int groups, int waves, hipStream_t st) {
+  if (tiles > 0x7fffffffLL || groups > 65535) return ST_UNSUPPORTED;
+  const size_t lds = sizeof(T) * (2 * (size_t)sine_half<T, ROWS, TP>() + 2 * (size_t)a.N);
+  if (lds > DIRECT_LDS_MAX) return ST_UNSUPPORTED;
+  if (lds > 64 * 1024) {
+    static std::once_flag once;
+    std::call_once(once, [] {
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dst_sine<T, ROWS, TO, TP>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)DIRECT_LDS_MAX);
+    });
+  }
+  hipLaunchKernelGGL((k_dst_sine<T, ROWS, TO, TP>), dim3((unsigned)tiles, (unsigned)groups), dim3(64 * waves), lds,
+                     st, a);
+  AHOC_HIP_TRY(hipGetLastError());
+  return ST_OK;
+}
+
+// Tiles of 32 pencils share each gathered sine between two MFMAs, 16-pencil tiles double the
+// work-groups: 32 from two work-groups per CU upward.  A pass that writes elsewhere than it
+// reads splits its outputs over work-groups of four wavefronts (each re-reads the tile) while
+// whole pencils would give fewer than that.
+template <typename T, bool ROWS>
+int sine_pass(SineArgs<T>& a, bool disjoint, hipStream_t st) {
+  const int pairs = (a.N / 2 + 15) / 16;
+  auto tiles = [&](int P) {
+    a.ntile_inner = ROWS ? 1 : (a.inner + P - 1) / P;
+    return ROWS ? (a.outer + P - 1) / P : a.outer * a.ntile_inner;
+  };
+  if (disjoint && (pairs > 64 || (pairs > 4 && tiles(16) < 512))) {
+    if (pairs > 64) return sine_launch<T, ROWS, 2, 2>(a, tiles(32), (pairs + 15) / 16, 8, st);
+    return sine_launch<T, ROWS, 1, 1>(a, tiles(16), (pairs + 3) / 4, 4, st);
+  }
+  if (pairs > 64) return ST_UNSUPPORTED;  // in place: one work-group holds every output of a tile
+  const bool wide = tiles(32) >= 512;
+  if (pairs <= 16)
+    return wide ? sine_launch<T, ROWS, 1, 2>(a, tiles(32), 1, pairs, st)
+                : sine_launch<T, ROWS, 1, 1>(a, tiles(16), 1, pairs, st);
+  if (pairs <= 32)
+    return wide ? sine_launch<T, ROWS, 2, 2>(a, tiles(32), 1, (pairs + 1) / 2, st)
+                : sine_launch<T, ROWS, 2, 1>(a, tiles(16), 1, (pairs + 1) / 2, st);
+  return sine_launch<T, ROWS, 4, 1>(a, tiles(16), 1, (pairs + 3) / 4, st);
+}
+
 }  // namespace
 
 template <typename T>
 int dst_direct_pass(int N, const T* sn2, const T* in, T* out, long long outer, long long inner, long long pitch,
-                    const DstScale<T>* fused, hipStream_t st) {
+                    const DstScale<T>* fused, hipStream_t st, T* tmp) {
   if (N < 2 || N > DST_MAX_N || !sn2 || !in || !out || outer < 0 || inner < 1) return ST_INVALID;
   const int L = N - 1;
   if (inner == 1 && (pitch < L || fused)) return ST_INVALID;
   if (outer == 0) return ST_OK;
+  {
+    const long long extent = inner == 1 ? (outer - 1) * pitch + L : outer * (long long)L * inner;
+    auto apart = [&](const T* x, const T* y) { return x + extent <= y || y + extent <= x; };
+    auto run = [&](const T* src, T* dst, const DstScale<T>* f) {
+      SineArgs<T> s;
+      s.in = src;
+      s.out = dst;
+      s.sn2 = sn2;
+      s.N = N;
+      s.outer = outer;
+      s.inner = inner;
+      s.pitch = pitch;
+      s.scaled = f != nullptr;
+      if (f) s.fs = *f;
+      return inner == 1 ? sine_pass<T, true>(s, apart(src, dst), st) : sine_pass<T, false>(s, apart(src, dst), st);
+    };
+    T* mid = tmp && apart(in, tmp) && apart(out, tmp) ? tmp : out;
+    int rc = run(in, fused ? mid : out, fused);
+    if (rc == ST_OK && fused) rc = run(mid, out, nullptr);
+    if (rc != ST_UNSUPPORTED) return rc;  // refused before anything is launched
+  }
   const size_t per = (size_t)L * sizeof(T) * 2;  // x and y of one pencil
   int P = (int)std::min<size_t>(64, std::max<size_t>(1, (48 * 1024) / per));
   if ((size_t)P * per > DIRECT_LDS_MAX) return ST_UNSUPPORTED;
@@ -179,8 +435,8 @@ int dst_direct_pass(int N, const T* sn2, const T* in, T* out, long long outer, l
 }
 
 template int dst_direct_pass<float>(int, const float*, const float*, float*, long long, long long, long long,
-                                    const DstScale<float>*, hipStream_t);
+                                    const DstScale<float>*, hipStream_t, float*);
 template int dst_direct_pass<double>(int, const double*, const double*, double*, long long, long long, long long,
-                                     const DstScale<double>*, hipStream_t);
+                                     const DstScale<double>*, hipStream_t, double*);
 
 }  // namespace ahoc

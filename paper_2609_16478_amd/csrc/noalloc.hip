@@ -86,14 +86,16 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 // Dense FP64 interior rows (cols values each) into the padded work array (row pitch px),
 // writing the padding columns as zeros: the transform kernels read a row's padding slot with
 // a zero weight, so whatever an earlier call left there (a NaN bit pattern included) must not
-// survive into this one.
+// survive into this one.  scr, if any, gets the same zero padding columns.
 template <typename T>
-__global__ void k_load_padded(long long rows, int cols, int px, const double* __restrict__ in, T* __restrict__ out) {
+__global__ void k_load_padded(long long rows, int cols, int px, const double* __restrict__ in, T* __restrict__ out,
+                              T* __restrict__ scr) {
   const long long n = rows * px;
   for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
     const long long r = e / px;
     const int c = (int)(e - r * px);
     out[e] = c < cols ? (T)in[r * cols + c] : T(0);
+    if (scr && c >= cols) scr[e] = T(0);
   }
 }
 
@@ -145,6 +147,15 @@ int poisson_noalloc(int dim, const int* n, const double* lo, const double* hi, c
     AHOC_HIP_TRY(hipGetLastError());
   }
   T* buf = reinterpret_cast<T*>(p + NOALLOC_TABLE_BYTES);
+  // where the array has room for it, a second work array for the passes of an axis without an
+  // FFT plan, which then write elsewhere than they read (each such axis has two plain passes,
+  // so the result ends in buf)
+  bool plans = true;
+  for (int a = 0; a < dim; ++a) plans = plans && tb[a].ppt;
+  const size_t need = align256((size_t)nalloc * sizeof(T));
+  T* scr = !plans && NOALLOC_TABLE_BYTES + 2 * need <= NOALLOC_SCRATCH_BYTES
+               ? reinterpret_cast<T*>(p + NOALLOC_TABLE_BYTES + need)
+               : nullptr;
   // eigen scaling of the slowest-axis pass: lambda = A + B s_t with the other axes' s
   double norm = 1.0;
   for (int a = 0; a < dim; ++a) norm *= 2.0 / N[a];
@@ -168,20 +179,26 @@ int poisson_noalloc(int dim, const int* n, const double* lo, const double* hi, c
   {
     const long long n = rows * px;
     const unsigned blocks = (unsigned)std::min<long long>((n + 255) / 256, 65536);
-    hipLaunchKernelGGL((k_load_padded<T>), dim3(blocks), dim3(256), 0, st, rows, ni[0], (int)px, g, buf);
+    hipLaunchKernelGGL((k_load_padded<T>), dim3(blocks), dim3(256), 0, st, rows, ni[0], (int)px, g, buf,
+                       scr);
     AHOC_HIP_TRY(hipGetLastError());
   }
+  T* cur = buf;
+  auto pass = [&](int ax, long long outer, long long inner, const DstScale<T>* f) {
+    const T* src = cur;
+    T* other = scr ? (cur == buf ? scr : buf) : nullptr;
+    if (!tb[ax].ppt && !f && other) std::swap(cur, other);
+    return dst_pass<T>(tb[ax], src, cur, outer, inner, px, f, 0, st, nullptr, other);
+  };
+  TRY_ST(pass(0, rows, 1, nullptr));
   if (dim == 2) {
-    TRY_ST(dst_pass<T>(tb[0], buf, buf, ni[1], 1, px, nullptr, 0, st));
-    TRY_ST(dst_pass<T>(tb[1], buf, buf, 1, px, px, &sc, 0, st));
-    TRY_ST(dst_pass<T>(tb[0], buf, buf, ni[1], 1, px, nullptr, 0, st));
+    TRY_ST(pass(1, 1, px, &sc));
   } else {
-    TRY_ST(dst_pass<T>(tb[0], buf, buf, rows, 1, px, nullptr, 0, st));
-    TRY_ST(dst_pass<T>(tb[1], buf, buf, ni[2], px, px, nullptr, 0, st));
-    TRY_ST(dst_pass<T>(tb[2], buf, buf, 1, px * ni[1], px, &sc, 0, st));
-    TRY_ST(dst_pass<T>(tb[1], buf, buf, ni[2], px, px, nullptr, 0, st));
-    TRY_ST(dst_pass<T>(tb[0], buf, buf, rows, 1, px, nullptr, 0, st));
+    TRY_ST(pass(1, ni[2], px, nullptr));
+    TRY_ST(pass(2, 1, px * ni[1], &sc));
+    TRY_ST(pass(1, ni[2], px, nullptr));
   }
+  TRY_ST(pass(0, rows, 1, nullptr));
   TRY_ST((pitch_copy<T, double>(rows, ni[0], buf, px, w, ni[0], st)));
   // the tables point into the scratch array: nothing to release
   tb[0].tw = tb[1].tw = tb[2].tw = nullptr;
