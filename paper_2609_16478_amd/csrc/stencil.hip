@@ -174,274 +174,84 @@ __global__ void k_rhs_u(Geom g, Weights w, const T* __restrict__ V, const T* __r
   }
 }
 
-// 3-D rhs_u, one work-group per interior row (j, k).  Every neighbour row of the row is
-// contiguous in x whether it is interior V or a face of Q (y faces are [k][i], z faces
-// [j][i]), and so are the rows of nodal 1/alpha; the x faces contribute one value at each
-// end.  Row pointers are resolved once per row, so an element costs its loads and FMAs.
+// 3-D rhs_u: a work-group owns a tile of RBX x RBY columns and marches along z over kchunk
+// planes.  W = V / alpha (on a face Q / alpha) of a thread's own column at planes k-1, k, k+1
+// stays in registers, the next plane's value and its share of the tile's halo ring are
+// prefetched, and the x- and y-neighbours come from an LDS copy of plane k (two copies in
+// turn: one barrier per plane).  Memory bound: V, 1/alpha read (1 + 2/RBY + 2/kchunk) times.
+// FP64: 14 us at 128^3 and 2.42 ms at 768^3 (4.5 TB/s of V, 1/alpha and G once each); whole
+// rows of 512 threads over chunks of 32 planes took 121 us (128 work-groups with 3/4 of their
+// threads idle) and 3.18 ms.
 template <typename T>
-__global__ void k_rhs_u3(Geom g, Weights w, const T* __restrict__ V, const T* __restrict__ Q,
-                         const T* __restrict__ ia, const T* __restrict__ src, T* __restrict__ G) {
-  const T m0 = (T)w.m0, m1 = (T)w.m1;
-  const int ni0 = g.ni[0], ni1 = g.ni[1], ni2 = g.ni[2];
-  const long long plane = (long long)ni1 * g.px;
-  const long long nplane = (long long)g.nn[0] * g.nn[1];
-  const int nrow = ni1 * ni2;
-  // Work-groups are dealt to the 8 XCDs in turn; give each XCD a contiguous range of rows
-  // (in order) so that a row's j-neighbours are read through the same L2.
-  const int per = (nrow + 7) / 8;
-  const int r = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-  if (r < nrow) {
-    const int j = r % ni1 + 1, k = r / ni1 + 1;
-    const long long e0 = (long long)r * g.px;
-    // neighbour rows of V (or Q on a face), indexed by i - 1
-    const T* vc = V + e0;
-    const T* vjm = j > 1 ? vc - g.px : Q + g.face_off[2] + (long long)(k - 1) * ni0;
-    const T* vjp = j < ni1 ? vc + g.px : Q + g.face_off[3] + (long long)(k - 1) * ni0;
-    const T* vkm = k > 1 ? vc - plane : Q + g.face_off[4] + (long long)(j - 1) * ni0;
-    const T* vkp = k < ni2 ? vc + plane : Q + g.face_off[5] + (long long)(j - 1) * ni0;
-    // rows of nodal 1/alpha, indexed by i
-    const T* ac = ia + nod(g, 0, j, k);
-    const T* ajm = ac - g.nn[0];
-    const T* ajp = ac + g.nn[0];
-    const T* akm = ac - nplane;
-    const T* akp = ac + nplane;
-    // x faces: one node at each end of the row
-    const T wl = Q[g.face_off[0] + (long long)(k - 1) * ni1 + (j - 1)] * ac[0];
-    const T wr = Q[g.face_off[1] + (long long)(k - 1) * ni1 + (j - 1)] * ac[g.n[0]];
-    for (int c = threadIdx.x; c < g.px; c += blockDim.x) {
-      const long long e = e0 + c;
-      if (c >= ni0) {
-        G[e] = T(0);
-        continue;
-      }
-      const int i = c + 1;
-      const T left = c > 0 ? vc[c - 1] * ac[i - 1] : wl;
-      const T right = c + 1 < ni0 ? vc[c + 1] * ac[i + 1] : wr;
-      T nb = vjm[c] * ajm[i] + vjp[c] * ajp[i];
-      nb += vkm[c] * akm[i] + vkp[c] * akp[i];
-      nb += left + right;
-      T acc = m0 * vc[c] * ac[i] + m1 * nb;
-      if (src) acc += src[e];
-      G[e] = acc;
-    }
-  }
+__device__ __forceinline__ T w_at(const Geom& g, const T* __restrict__ V, const T* __restrict__ Q,
+                                  const T* __restrict__ ia, int i, int j, int k) {
+  // nodes with at most one boundary coordinate; 0 elsewhere (edges, past the far faces)
+  const bool bi = i == 0 || i == g.n[0], bj = j == 0 || j == g.n[1], bk = k == 0 || k == g.n[2];
+  if (i > g.n[0] || j > g.n[1] || k > g.n[2] || (int)bi + (int)bj + (int)bk > 1) return T(0);
+  const T* p;
+  if (bi) p = Q + g.face_off[i == 0 ? 0 : 1] + (long long)(k - 1) * g.ni[1] + (j - 1);
+  else if (bj) p = Q + g.face_off[j == 0 ? 2 : 3] + (long long)(k - 1) * g.ni[0] + (i - 1);
+  else if (bk) p = Q + g.face_off[k == 0 ? 4 : 5] + (long long)(j - 1) * g.ni[0] + (i - 1);
+  else p = V + inr(g, i, j, k);
+  return *p * ia[nod(g, i, j, k)];
 }
-
-// 3-D rhs_u marching along z: a work-group owns the x-row of one j over a chunk of planes,
-// a thread CPT columns of it.  W = V / alpha of its own row at planes k-1, k, k+1 stays in
-// registers (each V and 1/alpha value of the row is read once), the x-neighbours come
-// from an LDS copy of the row (with the two x-face values at its ends), and the rows
-// j-1, j+1 are read at plane k; work-groups are ordered so that those belong to
-// neighbouring work-groups of the same XCD, which read them at about the same time.
+constexpr int RBX = 64, RBY = 8;
 template <typename T>
-__device__ __forceinline__ const T* zm_row(const Geom& g, const T* V, const T* Q, int j, int k, bool& face) {
-  // V row (j, k) of the interior, or the row of the face that (j, k) lies on; indexed by i - 1
-  face = false;
-  if (j == 0 || j == g.n[1]) {
-    face = true;
-    return Q + g.face_off[j == 0 ? 2 : 3] + (long long)(k - 1) * g.ni[0];
-  }
-  if (k == 0 || k == g.n[2]) {
-    face = true;
-    return Q + g.face_off[k == 0 ? 4 : 5] + (long long)(j - 1) * g.ni[0];
-  }
-  return V + ((long long)(k - 1) * g.ni[1] + (j - 1)) * g.px;
-}
-
-template <typename T, int CPT>
-__global__ void __launch_bounds__(256) k_rhs_u_zm(Geom g, Weights w, const T* __restrict__ V, const T* __restrict__ Q,
-                                                  const T* __restrict__ ia, const T* __restrict__ src,
-                                                  T* __restrict__ G, int kchunk) {
-  __shared__ T row[CPT * 256 + 2];
+__global__ void __launch_bounds__(RBX * RBY) k_rhs_u_blk(Geom g, Weights w, const T* __restrict__ V,
+                                                         const T* __restrict__ Q, const T* __restrict__ ia,
+                                                         const T* __restrict__ src, T* __restrict__ G, int kchunk) {
+  constexpr int RING = 2 * RBX + 2 * RBY;
+  __shared__ T ws[2][RBY + 2][RBX + 2];
   const T m0 = (T)w.m0, m1 = (T)w.m1;
-  const int ni0 = g.ni[0], ni1 = g.ni[1], ni2 = g.ni[2];
-  const int nkc = (ni2 + kchunk - 1) / kchunk;
-  const int total = ni1 * nkc;
-  const int per = (total + 7) / 8;
-  const int idx = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-  if (idx >= total) return;
-  const int kc = idx / ni1, j = idx % ni1 + 1;
-  const int k0 = kc * kchunk + 1, k1 = min(ni2, k0 + kchunk - 1);
-  const long long nrowa = g.nn[0];  // nodal row length
-  auto arow = [&](int jj, int kk) { return ia + ((long long)kk * g.nn[1] + jj) * nrowa; };
-  auto wrow = [&](int kk, T* out) {  // W of the own row at plane kk (0 past the far face)
-    bool f;
-    if (kk > g.n[2]) {
-#pragma unroll
-      for (int q = 0; q < CPT; ++q) out[q] = T(0);
-      return;
-    }
-    const T* v = zm_row(g, V, Q, j, kk, f);
-    const T* a = arow(j, kk);
-#pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-      const int c = threadIdx.x + 256 * q;
-      out[q] = c < ni0 ? v[c] * a[c + 1] : T(0);
-    }
-  };
-  T wm[CPT], wc[CPT], wp[CPT];
-  wrow(k0 - 1, wm);
-  wrow(k0, wc);
-  wrow(k0 + 1, wp);
-  for (int k = k0; k <= k1; ++k) {
-    // neighbour rows j-1, j+1 at plane k, and the x-face ends of the own row
-    bool f;
-    const T* vjm = zm_row(g, V, Q, j - 1, k, f);
-    const T* vjp = zm_row(g, V, Q, j + 1, k, f);
-    const T* ajm = arow(j - 1, k);
-    const T* ajp = arow(j + 1, k);
-    const T* ac = arow(j, k);
-    T nj[CPT];
-#pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-      const int c = threadIdx.x + 256 * q;
-      nj[q] = c < ni0 ? vjm[c] * ajm[c + 1] + vjp[c] * ajp[c + 1] : T(0);
-    }
-    T wnext[CPT];
-    wrow(k + 2, wnext);
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-      const int c = threadIdx.x + 256 * q;
-      if (c < ni0) row[c + 1] = wc[q];
-    }
-    if (threadIdx.x == 0) {
-      row[0] = Q[g.face_off[0] + (long long)(k - 1) * ni1 + (j - 1)] * ac[0];
-      row[ni0 + 1] = Q[g.face_off[1] + (long long)(k - 1) * ni1 + (j - 1)] * ac[g.n[0]];
-    }
-    __syncthreads();
-    const long long e0 = ((long long)(k - 1) * ni1 + (j - 1)) * g.px;
-#pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-      const int c = threadIdx.x + 256 * q;
-      if (c < ni0) {
-        T acc = m0 * wc[q] + m1 * (row[c] + row[c + 2] + nj[q] + wm[q] + wp[q]);
-        if (src) acc += src[e0 + c];
-        G[e0 + c] = acc;
-      } else if (c < g.px) {
-        G[e0 + c] = T(0);
-      }
-      wm[q] = wc[q];
-      wc[q] = wp[q];
-      wp[q] = wnext[q];
-    }
-  }
-}
-
-// 3-D rhs_u marching along z over a tile of TJ consecutive rows: W = V / alpha of every
-// row of the tile at planes k-1, k, k+1 (and the prefetched k+2) stays in registers, so
-// the y-neighbours inside the tile come from registers and only the two halo rows are read
-// per plane (each V and 1/alpha value is read (TJ + 2) / TJ times instead of 3 times); the
-// x-neighbours come from an LDS copy of the tile's rows with their two x-face values.
-template <typename T, int CPT, int TJ>
-__global__ void __launch_bounds__(512) k_rhs_u_tile(Geom g, Weights w, const T* __restrict__ V,
-                                                    const T* __restrict__ Q, const T* __restrict__ ia,
-                                                    const T* __restrict__ src, T* __restrict__ G, int kchunk) {
-  constexpr int NT = 512;
-  constexpr int RL = CPT * NT + 2;  // LDS row: x-face value, ni0 interior values, x-face value
-  __shared__ T row[TJ][RL];
-  const T m0 = (T)w.m0, m1 = (T)w.m1;
-  const int ni0 = g.ni[0], ni1 = g.ni[1], ni2 = g.ni[2];
-  const int ntj = (ni1 + TJ - 1) / TJ;
-  const int nkc = (ni2 + kchunk - 1) / kchunk;
-  const int total = ntj * nkc;
+  const int ni1 = g.ni[1], ni2 = g.ni[2];
+  const int tx = (g.px + RBX - 1) / RBX, ty = (ni1 + RBY - 1) / RBY, tz = (ni2 + kchunk - 1) / kchunk;
+  const int total = tx * ty * tz;
   // work-groups are dealt round-robin to the 8 XCDs: give each XCD a contiguous range of
   // tiles, so that neighbouring tiles (sharing halo rows) meet in one L2
   const int per = (total + 7) / 8;
   const int idx = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-  if (idx >= total) return;
-  const int kc = idx / ntj, j0 = (idx % ntj) * TJ + 1;
-  const int k0 = kc * kchunk + 1, k1 = min(ni2, k0 + kchunk - 1);
-  const int nr = min(TJ, ni1 - j0 + 1);  // rows of this tile
-  const long long nrowa = g.nn[0];
-  auto arow = [&](int jj, int kk) { return ia + ((long long)kk * g.nn[1] + jj) * nrowa; };
-  // W of row jj at plane kk (0 past the far z face or for rows past the tile)
-  auto wload = [&](int jj, int kk, T* out) {
-    if (kk > g.n[2] || jj > g.n[1]) {
-#pragma unroll
-      for (int q = 0; q < CPT; ++q) out[q] = T(0);
-      return;
-    }
-    bool f;
-    const T* v = zm_row(g, V, Q, jj, kk, f);
-    const T* a = arow(jj, kk);
-#pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-      const int c = threadIdx.x + NT * q;
-      out[q] = c < ni0 ? v[c] * a[c + 1] : T(0);
-    }
-  };
-  T wm[TJ][CPT], wc[TJ][CPT], wp[TJ][CPT];
-#pragma unroll
-  for (int r = 0; r < TJ; ++r) {
-    if (r < nr) {
-      wload(j0 + r, k0 - 1, wm[r]);
-      wload(j0 + r, k0, wc[r]);
-      wload(j0 + r, k0 + 1, wp[r]);
-    } else {
-#pragma unroll
-      for (int q = 0; q < CPT; ++q) wm[r][q] = wc[r][q] = wp[r][q] = T(0);
-    }
+  if (blockIdx.x / 8 >= per || idx >= total) return;
+  const int bx = idx % tx, by = idx / tx % ty, bz = idx / (tx * ty);
+  const int lx = threadIdx.x % RBX, ly = threadIdx.x / RBX;
+  const int i = bx * RBX + lx + 1, j = by * RBY + ly + 1;
+  const int k0 = bz * kchunk + 1, k1 = min(ni2, k0 + kchunk - 1);
+  // this thread's ring node (threads beyond the ring have none): the rows below and above the
+  // tile, then the columns left and right of it
+  const bool ring = threadIdx.x < RING;
+  int hx = 0, hy = 0;
+  if (threadIdx.x < 2 * RBX) {
+    hx = lx + 1;
+    hy = threadIdx.x < RBX ? 0 : RBY + 1;
+  } else {
+    const int r = threadIdx.x - 2 * RBX;
+    hx = r < RBY ? 0 : RBX + 1;
+    hy = r % RBY + 1;
   }
+  const int hi = bx * RBX + hx, hj = by * RBY + hy;
+  T wm = w_at(g, V, Q, ia, i, j, k0 - 1), wc = w_at(g, V, Q, ia, i, j, k0), wp = w_at(g, V, Q, ia, i, j, k0 + 1);
+  T hv = ring ? w_at(g, V, Q, ia, hi, hj, k0) : T(0);
   for (int k = k0; k <= k1; ++k) {
-    // halo rows j0 - 1 and j0 + nr at plane k (face rows at the y faces)
-    T hl[CPT], hh[CPT];
-    wload(j0 - 1, k, hl);
-    wload(j0 + nr, k, hh);
-    // prefetch plane k + 2 of the tile's rows
-    T wn[TJ][CPT];
-#pragma unroll
-    for (int r = 0; r < TJ; ++r) {
-      if (r < nr) wload(j0 + r, k + 2, wn[r]);
-      else {
-#pragma unroll
-        for (int q = 0; q < CPT; ++q) wn[r][q] = T(0);
-      }
-    }
+    T(*row)[RBX + 2] = ws[k & 1];
+    row[ly + 1][lx + 1] = wc;
+    if (ring) row[hy][hx] = hv;
     __syncthreads();
-#pragma unroll
-    for (int r = 0; r < TJ; ++r) {
-#pragma unroll
-      for (int q = 0; q < CPT; ++q) {
-        const int c = threadIdx.x + NT * q;
-        if (c < ni0) row[r][c + 1] = wc[r][q];
+    T wn = T(0);
+    if (k < k1) {
+      wn = w_at(g, V, Q, ia, i, j, k + 2);
+      if (ring) hv = w_at(g, V, Q, ia, hi, hj, k + 1);
+    }
+    if (j <= ni1 && i <= g.px) {
+      const long long e = ((long long)(k - 1) * ni1 + (j - 1)) * g.px + (i - 1);
+      T acc = T(0);  // padding columns
+      if (i <= g.ni[0]) {
+        acc = m0 * wc + m1 * (row[ly + 1][lx] + row[ly + 1][lx + 2] + row[ly][lx + 1] + row[ly + 2][lx + 1] + wm + wp);
+        if (src) acc += src[e];
       }
+      G[e] = acc;
     }
-    if (threadIdx.x < nr) {
-      const int r = threadIdx.x, j = j0 + r;
-      const T* ac = arow(j, k);
-      row[r][0] = Q[g.face_off[0] + (long long)(k - 1) * ni1 + (j - 1)] * ac[0];
-      row[r][ni0 + 1] = Q[g.face_off[1] + (long long)(k - 1) * ni1 + (j - 1)] * ac[g.n[0]];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < TJ; ++r) {
-      if (r < nr) {
-        const long long e0 = ((long long)(k - 1) * ni1 + (j0 + r - 1)) * g.px;
-#pragma unroll
-        for (int q = 0; q < CPT; ++q) {
-          const int c = threadIdx.x + NT * q;
-          if (c < ni0) {
-            const T ylo = r == 0 ? hl[q] : wc[r > 0 ? r - 1 : 0][q];
-            const T yhi = r == nr - 1 ? hh[q] : wc[r < TJ - 1 ? r + 1 : r][q];
-            T acc = m0 * wc[r][q] + m1 * (row[r][c] + row[r][c + 2] + ylo + yhi + wm[r][q] + wp[r][q]);
-            if (src) acc += src[e0 + c];
-            G[e0 + c] = acc;
-          } else if (c < g.px) {
-            G[e0 + c] = T(0);
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < TJ; ++r) {
-#pragma unroll
-      for (int q = 0; q < CPT; ++q) {
-        wm[r][q] = wc[r][q];
-        wc[r][q] = wp[r][q];
-        wp[r][q] = wn[r][q];
-      }
-    }
+    wm = wc;
+    wc = wp;
+    wp = wn;
   }
 }
 
@@ -1004,42 +814,44 @@ __global__ void k_vapply(Geom g, Weights w, const double* __restrict__ X, const 
   }
 }
 
-// The same operator on the nodes whose whole stencil is interior (2 <= i <= n_x'-1, likewise
-// j, k; 3-D, homogeneous: no Q, no src), tiled: a work-group owns VTX x VTY columns and
-// marches along z over VKC planes, with the planes k-1, k, k+1 of its columns and their halo
-// in LDS and c X of plane k beside them, so every value is read from memory about once per
-// plane instead of once per stencil point.
-constexpr int VTX = 64, VTY = 8, VKC = 32;
+// The same operator without Q and src (3-D), tiled: a work-group owns VTX x VTY columns and
+// marches along z over kchunk planes, with the planes k-1, k, k+1 of its columns and their halo
+// in LDS (zero on the boundary) and c X of plane k beside them, so every value is read from
+// memory about once per plane instead of once per stencil point.  128^3: 24.6 us; 64.4 us with
+// chunks of 32 planes (128 work-groups), plus 11.3 us for a second kernel over the layer next
+// to the boundary, which the zero boundary values make unnecessary.
+constexpr int VTX = 64, VTY = 8;
 __global__ void __launch_bounds__(VTX * VTY) k_vapply_tile(Geom g, Weights w, const double* __restrict__ X,
-                                                           const double* __restrict__ c, double* __restrict__ y) {
+                                                           const double* __restrict__ c, double* __restrict__ y,
+                                                           int kchunk) {
   constexpr int HX = VTX + 2, HY = VTY + 2;
   __shared__ double xs[3][HY][HX];
   __shared__ double cs[HY][HX];
   const int ni0 = g.ni[0], ni1 = g.ni[1], ni2 = g.ni[2];
-  const int nx = ni0 - 2, ny = ni1 - 2, nz = ni2 - 2;  // extents of the region
-  const int tx = (nx + VTX - 1) / VTX, ty = (ny + VTY - 1) / VTY, tz = (nz + VKC - 1) / VKC;
+  const int tx = (ni0 + VTX - 1) / VTX, ty = (ni1 + VTY - 1) / VTY, tz = (ni2 + kchunk - 1) / kchunk;
   long long t = blockIdx.x;
   if (t >= (long long)tx * ty * tz) return;
   const int bx = (int)(t % tx);
   t /= tx;
   const int by = (int)(t % ty), bz = (int)(t / ty);
   const int lx = threadIdx.x % VTX, ly = threadIdx.x / VTX;
-  const int ib = 2 + bx * VTX, jb = 2 + by * VTY;  // first column of the tile
+  const int ib = 1 + bx * VTX, jb = 1 + by * VTY;  // first column of the tile
   const int i = ib + lx, j = jb + ly;
-  const bool mine = i <= ni0 - 1 && j <= ni1 - 1;
-  const int k0 = 2 + bz * VKC, k1 = min(ni2 - 1, k0 + VKC - 1);
+  const bool mine = i <= ni0 && j <= ni1;
+  const int k0 = 1 + bz * kchunk, k1 = min(ni2, k0 + kchunk - 1);
   const long long npl = (long long)g.nn[1] * g.nn[0];
-  // halo position (hx, hy) -> node (ib - 1 + hx, jb - 1 + hy), clamped into the interior
-  // (clamped positions feed only columns outside the region, whose outputs are not written)
+  // halo position (hx, hy) -> node (ib - 1 + hx, jb - 1 + hy), clamped to the far faces
+  // (positions beyond them feed only columns whose outputs are not written)
   auto hnode = [&](int h, int& gi, int& gj) {
-    gi = min(ib - 1 + h % HX, ni0);
-    gj = min(jb - 1 + h / HX, ni1);
+    gi = min(ib - 1 + h % HX, ni0 + 1);
+    gj = min(jb - 1 + h / HX, ni1 + 1);
   };
   auto load_plane = [&](int kk, int slot) {
     for (int h = threadIdx.x; h < HX * HY; h += VTX * VTY) {
       int gi, gj;
       hnode(h, gi, gj);
-      xs[slot][h / HX][h % HX] = X[((long long)(kk - 1) * ni1 + (gj - 1)) * g.px + (gi - 1)];
+      const bool in = gi >= 1 && gi <= ni0 && gj >= 1 && gj <= ni1 && kk >= 1 && kk <= ni2;
+      xs[slot][h / HX][h % HX] = in ? X[((long long)(kk - 1) * ni1 + (gj - 1)) * g.px + (gi - 1)] : 0.0;
     }
   };
   int s0 = 0, s1 = 1, s2 = 2;  // slots of planes k-1, k, k+1
@@ -1079,53 +891,6 @@ __global__ void __launch_bounds__(VTX * VTY) k_vapply_tile(Geom g, Weights w, co
       s1 = s2;
       s2 = tmp;
     }
-  }
-}
-
-// The nodes of the layer next to the boundary that k_vapply_tile leaves out (3-D,
-// homogeneous), one thread each: the full rows of the planes k = 1, n_z' and of the rows
-// j = 1, n_y' in between (padding columns skipped: they stay zero), then the nodes i = 1
-// and i = n_x' of every other row.
-__global__ void k_vapply_shell(Geom g, Weights w, const double* __restrict__ X, const double* __restrict__ c,
-                               double* __restrict__ y) {
-  const int ni0 = g.ni[0], ni1 = g.ni[1], ni2 = g.ni[2];
-  const long long full_rows = 2LL * ni1 + 2LL * (ni2 - 2);
-  const long long nfull = full_rows * ni0, nside = 2LL * (ni1 - 2) * (ni2 - 2);
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < nfull + nside;
-       e += (long long)gridDim.x * blockDim.x) {
-    int i, j, k;
-    if (e < nfull) {
-      const long long r = e / ni0;
-      i = (int)(e - r * ni0) + 1;
-      if (r < 2LL * ni1) {  // planes k = 1 and k = n_z'
-        k = r < ni1 ? 1 : ni2;
-        j = (int)(r % ni1) + 1;
-      } else {              // rows j = 1 and j = n_y' of the planes between
-        const long long q = r - 2LL * ni1;
-        k = (int)(q / 2) + 2;
-        j = (q & 1) ? ni1 : 1;
-      }
-    } else {
-      const long long q = e - nfull;
-      const long long rr = q / 2;  // row (j, k) with j in [2, n_y'-1], k in [2, n_z'-1]
-      i = (q & 1) ? ni0 : 1;
-      j = (int)(rr % (ni1 - 2)) + 2;
-      k = (int)(rr / (ni1 - 2)) + 2;
-    }
-    double lv = 0, mv = 0;
-    for (int dz = -1; dz <= 1; ++dz)
-      for (int dy = -1; dy <= 1; ++dy)
-        for (int dx = -1; dx <= 1; ++dx) {
-          const double wt = lw<3>(w, dx, dy, dz);
-          const int nzo = (dx != 0) + (dy != 0) + (dz != 0);
-          if (wt == 0.0 && nzo > 1) continue;
-          const int qi = i + dx, qj = j + dy, qk = k + dz;
-          if (nbnd<3>(g, qi, qj, qk) != 0) continue;  // homogeneous: boundary values are zero
-          const double vq = X[inr(g, qi, qj, qk)];
-          lv += wt * vq;
-          if (nzo <= 1) mv += (nzo == 0 ? w.m0 : w.m1) * c[nod(g, qi, qj, qk)] * vq;
-        }
-    y[inr(g, i, j, k)] = mv - lv;
   }
 }
 
@@ -1424,38 +1189,16 @@ int lift(const Geom& g, const Weights& w, const T* Q, const T* src, T* G, hipStr
 template <typename T>
 int rhs_u(const Geom& g, const Weights& w, const T* V, const T* Q, const T* ia, const T* src, T* G,
           hipStream_t st) {
-  if (g.dim == 3 && g.px <= 1024) {
-    // tiles of 4 rows marching along z, 512 threads, 2 columns per thread at most (8-row
-    // tiles and 64-plane chunks measured slower)
-    constexpr int TJ = 4;
-    const int cpt = (g.px + 511) / 512;
-    const int kchunk = 32;
-    const int total = ((g.ni[1] + TJ - 1) / TJ) * ((g.ni[2] + kchunk - 1) / kchunk);
-    const unsigned blocks = 8u * (unsigned)((total + 7) / 8);
-    if (cpt <= 1)
-      hipLaunchKernelGGL((k_rhs_u_tile<T, 1, TJ>), dim3(blocks), dim3(512), 0, st, g, w, V, Q, ia, src, G, kchunk);
-    else
-      hipLaunchKernelGGL((k_rhs_u_tile<T, 2, TJ>), dim3(blocks), dim3(512), 0, st, g, w, V, Q, ia, src, G, kchunk);
-    AHOC_HIP_TRY(hipGetLastError());
-    return ST_OK;
-  }
   if (g.dim == 3) {
-    const int cpt = (g.px + 255) / 256;
-    const int kchunk = 32;
-    const int total = g.ni[1] * ((g.ni[2] + kchunk - 1) / kchunk);
-    const unsigned blocks = 8u * (unsigned)((total + 7) / 8);
-#define AHOC_ZM(C) hipLaunchKernelGGL((k_rhs_u_zm<T, C>), dim3(blocks), dim3(256), 0, st, g, w, V, Q, ia, src, G, kchunk)
-    if (cpt <= 1) AHOC_ZM(1);
-    else if (cpt <= 2) AHOC_ZM(2);
-    else if (cpt <= 4) AHOC_ZM(4);
-    else if (cpt <= 8) AHOC_ZM(8);
-    else if (cpt <= 16) AHOC_ZM(16);
-    else {
-      const int nrow = g.ni[1] * g.ni[2];
-      hipLaunchKernelGGL((k_rhs_u3<T>), dim3(8u * (unsigned)((nrow + 7) / 8)), dim3(TPB), 0, st, g, w, V, Q, ia,
-                         src, G);
-    }
-#undef AHOC_ZM
+    // chunks of 32 planes, shorter (the halo planes are 2 / kchunk more reads) until four
+    // work-groups of 512 threads meet on every compute unit: at 128^3 chunks of 4 planes
+    // (14 us; 128 work-groups of 32-plane chunks 121 us)
+    const long long cols = (long long)((g.px + RBX - 1) / RBX) * ((g.ni[1] + RBY - 1) / RBY);
+    const int kchunk = (int)std::max<long long>(4, std::min<long long>(32, cols * g.ni[2] / 1024));
+    const long long total = cols * ((g.ni[2] + kchunk - 1) / kchunk);
+    if (total > 0x3fffffffLL) return ST_UNSUPPORTED;
+    hipLaunchKernelGGL((k_rhs_u_blk<T>), dim3(8u * (unsigned)((total + 7) / 8)), dim3(RBX * RBY), 0, st, g, w, V, Q,
+                       ia, src, G, kchunk);
     AHOC_HIP_TRY(hipGetLastError());
     return ST_OK;
   }
@@ -1566,14 +1309,12 @@ int vapply(const Geom& g, const Weights& w, const double* X, const double* Q, co
            double* y, hipStream_t st) {
   if (g.nb != 1) return ST_UNSUPPORTED;
   if (g.dim == 3 && !Q && !src) {
-    // interior nodes tiled, then the layer next to the boundary (the row padding of y is
-    // never written: the callers' output arrays keep it zero)
-    const long long tiles = (long long)((g.ni[0] - 2 + VTX - 1) / VTX) * ((g.ni[1] - 2 + VTY - 1) / VTY) *
-                            ((g.ni[2] - 2 + VKC - 1) / VKC);
-    hipLaunchKernelGGL(k_vapply_tile, dim3((unsigned)tiles), dim3(VTX * VTY), 0, st, g, w, X, c, y);
-    AHOC_HIP_TRY(hipGetLastError());
-    const long long shell = (2LL * g.ni[1] + 2LL * (g.ni[2] - 2)) * g.ni[0] + 2LL * (g.ni[1] - 2) * (g.ni[2] - 2);
-    hipLaunchKernelGGL(k_vapply_shell, dim3(nblocks(shell)), dim3(TPB), 0, st, g, w, X, c, y);
+    // (the row padding of y is never written: the callers' output arrays keep it zero); chunks
+    // of 32 planes, shorter until two work-groups of 512 threads meet on every compute unit
+    const long long cols = (long long)((g.ni[0] + VTX - 1) / VTX) * ((g.ni[1] + VTY - 1) / VTY);
+    const int kchunk = (int)std::max<long long>(4, std::min<long long>(32, cols * g.ni[2] / 512));
+    const long long tiles = cols * ((g.ni[2] + kchunk - 1) / kchunk);
+    hipLaunchKernelGGL(k_vapply_tile, dim3((unsigned)tiles), dim3(VTX * VTY), 0, st, g, w, X, c, y, kchunk);
     AHOC_HIP_TRY(hipGetLastError());
     return ST_OK;
   }
