@@ -144,6 +144,7 @@ struct ahoc_handle {
   ahoc::DstTables<double> ptb[3];
   bool ptb_own = false;
   int* act = nullptr;        // per instance: a mask (device; zeroing finished segments)
+  int* act0 = nullptr;       // scratch of arnoldi_step
   int* ist = nullptr;        // GMRES state per instance (device): [act | kk | nit | flag | hcnt]
   double* hist = nullptr;    // last 16 residual estimates per instance (device; FP32 stall rule)
   double* eres = nullptr;    // last residual estimate of each instance while active (device)
@@ -1260,11 +1261,9 @@ int gmres(ahoc_handle* h, Prec<T>& P, const double* b, double* x, double tol, in
   const bool pre = h->pc != nullptr;
   const int ns = h->g.nb;
   const long long nq = h->g.nq;
-  const int nbk = dot_blocks(h, nq);
   const long long nt = nq * ns;  // batch vector length
   const int m = h->m;
-  // device state per instance: [act | kk | nit | flag | hcnt] (see step_update)
-  int* act = h->ist;
+  // device state per instance: [act | kk | nit | flag | hcnt] (see arnoldi_step)
   int* kk = h->ist + ns;
   const int* hst = h->pinned_s;  // host image of [act | kk | nit | flag]
   res.assign(ns, GmresResult());
@@ -1339,14 +1338,10 @@ int gmres(ahoc_handle* h, Prec<T>& P, const double* b, double* x, double tol, in
       TRY(apply_op<T>(h, P, pre, vj, w, st));
       ++*matvecs;
       hipEvent_t ek = tbegin(h, st);
-      TRY(mdot(h->Vb, nt, j + 1, w, nq, ns, h->part, nbk, h->h1, m + 1, st));
-      TRY(maxpy(w, h->Vb, nt, j + 1, h->h1, m + 1, -1.0, nq, ns, st));
-      TRY(mdot(h->Vb, nt, j + 1, w, nq, ns, h->part, nbk, h->h2, m + 1, st));
-      TRY(maxpy(w, h->Vb, nt, j + 1, h->h2, m + 1, -1.0, nq, ns, st));
-      TRY(dot_dev(h, w, w, st, h->nrm));
-      TRY(givens_update(ns, h->H, m, h->h1, h->h2, h->nrm, h->cs, h->sn, h->gv, j, h->resid, h->bn, tol, max_iters,
-                        inexact, h->ist, h->hist, h->eres, st));
-      TRY(scale_by_inv(w, nq, ns, h->resid, act, st));
+      TRY(arnoldi_step(h->Vb, nt, nq,
+                       {ns, m, j, max_iters, inexact, tol, h->H, h->cs, h->sn, h->gv, h->resid, h->bn, h->ist, h->act0,
+                        h->hist, h->eres, h->h1, h->h2, h->nrm, h->part},
+                       st));
       // CGS2: 2 x (j+1) dot sweeps and 2 x (j+1) axpy sweeps over the basis, plus norm and scale
       tend(h, AHOC_K_KRYLOV, ek, 8.0 * nt * (4.0 * (j + 1) + 2.0 * 2 + 3.0), st);
       jmax = j + 1;
@@ -1597,8 +1592,9 @@ int setup_impl(const ahoc_problem* pbs, int count, hipStream_t st, ahoc_handle* 
   TRY(alloc_t(h, &h->resid, 2 * nb));
   TRY(alloc_t(h, &h->beta, nb));
   TRY(alloc_t(h, &h->y, nb * (m + 1)));
-  TRY(alloc_t(h, &h->part, nb * (m + 1) * dot_blocks(h, g.nq)));
+  TRY(alloc_t(h, &h->part, nb * (m + 1) * std::max(dot_blocks(h, g.nq), g.nq > ARN_ONE_MAX ? 2 * arnoldi_slices(g.nq) : 1)));
   TRY(alloc_t(h, &h->act, nb));
+  TRY(alloc_t(h, &h->act0, nb));
   TRY(alloc_t(h, &h->ist, 5 * nb));
   TRY(alloc_t(h, &h->hist, 16 * nb));
   TRY(alloc_t(h, &h->eres, nb));

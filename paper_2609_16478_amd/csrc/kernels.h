@@ -101,8 +101,6 @@ int mdot(const double* V, long long ld, int nvec, const double* w, long long n, 
          double* out, int ostride, hipStream_t st);
 int maxpy(double* w, const double* V, long long ld, int nvec, const double* coef, int cstride, double sign,
           long long n, int ns, hipStream_t st);
-int givens_step(int ns, double* H, int m, const double* h1, const double* h2, const double* nrm2, double* cs,
-                double* sn, double* gv, int j, double* resid, hipStream_t st);
 int axpby(long long n, double a, const double* x, double b, double* y, hipStream_t st);
 // y += a x with the per-work-group partial sums of <u, y> (u null: 0) and <y, y>, in part[0..nbk)
 // and part[nbk..2 nbk) (reduce with mdot_reduce, nvec 2)
@@ -110,7 +108,6 @@ int axpy_dot2(long long n, double a, const double* x, double* y, const double* u
               hipStream_t st);
 // w = a x + b y + c w
 int lin3(long long n, double a, const double* x, double b, const double* y, double c, double* w, hipStream_t st);
-int scale_by_inv(double* w, long long n, int ns, const double* s, const int* act, hipStream_t st);
 // Segment-wise batch utilities (grid.y = segment): x_s = 0 where keep[s] == 0; gather of
 // per-instance arrays (device table of device pointers, null = zeros); scatter to them.
 int zero_masked(double* x, long long n, int ns, const int* keep, hipStream_t st);
@@ -118,14 +115,26 @@ int gather_ptrs(const double* const* src, long long n, int ns, double* out, hipS
 int scatter_ptrs(const double* in, long long n, int ns, double* const* dst, hipStream_t st);
 int back_solve(int ns, const double* H, int m, const double* gv, const int* kk, int kmax, double* y,
                hipStream_t st);
-// device-side convergence bookkeeping of Arnoldi step j (see krylov.hip); ist = [act | kk |
-// nit | flag | hcnt], ns ints each; hist: 16 doubles per instance; eres: last active estimate
-int step_update(int ns, int j, const double* resid, const double* bnorm, double tol, int max_iters, bool inexact,
-                int* ist, double* hist, double* eres, hipStream_t st);
-// givens_step and step_update in one launch
-int givens_update(int ns, double* H, int m, const double* h1, const double* h2, const double* nrm2, double* cs,
-                  double* sn, double* gv, int j, double* resid, const double* bnorm, double tol, int max_iters,
-                  bool inexact, int* ist, double* hist, double* eres, hipStream_t st);
+// Arnoldi step j of ns segments of length n, ld apart in the basis V: classical Gram-Schmidt
+// twice, the Givens rotation with the device-side convergence bookkeeping (see rotate_and_update in
+// krylov.hip; ist = [act | kk | nit | flag | hcnt], ns ints each; hist: 16 doubles per
+// instance; eres: last active estimate) and the scaling of V_{j+1}, which holds the operator's
+// output on entry.  part: 2 ns (m + 1) arnoldi_slices(n) doubles; act0: ns ints of scratch.
+struct ArnoldiArgs {
+  int ns, m, j, max_iters;
+  bool inexact;
+  double tol;
+  double *H, *cs, *sn, *gv, *resid;
+  const double* bnorm;
+  int *ist, *act0;
+  double *hist, *eres, *h1, *h2, *nrm, *part;
+};
+// a segment up to here is one work-group's step: 28 us at 4092 unknowns, the sliced step's four
+// launches about 30 us; longer ones leave the one compute unit behind
+constexpr long long ARN_ONE_MAX = 4096;
+constexpr int ARN_INLINE = 256;          // most partial sums that every work-group adds up itself
+int arnoldi_slices(long long n);
+int arnoldi_step(double* V, long long ld, long long n, const ArnoldiArgs& a, hipStream_t st);
 int fill_int(int* p, long long n, int v, hipStream_t st);
 int start_cycle(double* v0, const double* r, long long n, int ns, const double* nrm2, double* gv, int m,
                 double* beta, hipStream_t st);
