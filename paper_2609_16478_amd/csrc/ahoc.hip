@@ -61,6 +61,10 @@ template <typename T> struct Prec {
   // 3-D spectral matvec with the weighting operator M in spectral form: the U-solve's face
   // layers m1 Q_b / alpha_b (layouts as Fx, Fy, Fz) and the scale with the symbol of M
   bool mspec = false;
+  // the face transforms as a few launches of sine products: second arrays of the layouts of
+  // (Fx, Fy, Fz) and (Ux, Uy, Uz) that their passes alternate with, null where the FFT passes
+  // are the faster ones (see face_jobs_pay)
+  T* ft[2][3] = {{nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}};
   T* ptab = nullptr;  // per z position: s_z, layer sine, face weights low/high
   T* Ux = nullptr;
   T* Uy = nullptr;
@@ -125,7 +129,8 @@ struct ahoc_handle {
   double *h1 = nullptr, *h2 = nullptr, *nrm = nullptr, *part = nullptr, *y = nullptr;
   double *resid = nullptr, *beta = nullptr, *bvec = nullptr, *dq = nullptr, *rvec = nullptr, *R = nullptr;
   double* zvec = nullptr;    // preconditioned Krylov vector
-  double* zt = nullptr;      // scratch of the preconditioner's face transforms (an axis without an FFT plan)
+  double* zt = nullptr;      // scratch of the preconditioner's face transforms (passes not in place)
+  bool pjobs = false;        // its face transforms run as sine products
   // GMRES operator (preconditioner and Schur matvec) captured as a HIP graph per operator
   // precision ([0] FP32, [1] FP64), replayed once per Krylov step from the fixed input gin
   // to the fixed output gout; captured on its second use, eager when capture fails
@@ -331,6 +336,29 @@ bool has_plans(const Geom& g) {
   return true;
 }
 
+// Whether the transforms of a grid's faces run as sine products, all faces in one launch per
+// axis pass, instead of one FFT pass per face pair and axis.  A launch of its own costs an FFT
+// pass of a small face 6 to 10 us whatever its work; the products' work grows with N.  Mixed
+// solves, FFT passes against products: 128^3 9.7 and 5.5 ms, 256^3 15.7 and 11.3, 384^3 36.6 and
+// 31.1, 512^3 (1.6e9 flops) 63.0 and 59.5; at 768^3 (5.4e9 flops, 50 us of FP64 a pass) the two
+// meet.
+constexpr double FACE_JOBS_FLOPS = 3e9;
+bool face_jobs_pay(const Geom& g) {
+  double f = 0;
+  int nmax = 0;
+  for (int a = 0; a < g.dim; ++a) nmax = std::max(nmax, g.n[a]);
+  if (g.dim == 3)
+    for (int a = 0; a < 3; ++a) {
+      const int b = (a + 1) % 3;
+      f += dst_sine_flops(g.n[a], 2LL * g.ni[b], 1) + dst_sine_flops(g.n[b], 2, g.ni[a]);
+    }
+  else
+    f = dst_sine_flops(g.n[0], 2LL * g.nb, 1) + dst_sine_flops(g.n[1], 2LL * g.nb, 1);
+  return nmax <= DST_SINE_JOBS_MAX_N && f <= FACE_JOBS_FLOPS;
+}
+// (the test switch's other kernel families keep their own face passes)
+bool face_jobs_on() { return dst_get_variant() == 0 || dst_get_variant() == 5; }
+
 template <typename T> int prec_init(ahoc_handle* h, Prec<T>& P, int tile_opt, hipStream_t st) {
   const Geom& g = h->g;
   for (int a = 0; a < g.dim; ++a) {
@@ -412,6 +440,19 @@ template <typename T> int prec_init(ahoc_handle* h, Prec<T>& P, int tile_opt, hi
     TRY(alloc_t(h, &P.ptab, 4LL * nt));
     AHOC_HIP_TRY(hipMemcpyAsync(P.ptab, pt.data(), sizeof(T) * 4 * nt, hipMemcpyHostToDevice, st));
     AHOC_HIP_TRY(hipStreamSynchronize(st));
+    if (face_jobs_pay(g)) {
+      const long long sx = g.dim == 3 ? 2LL * g.ni[1] * g.ni[2] : 2LL * g.nb * g.ni[1];
+      const long long sy[2] = {g.dim == 3 ? 2LL * g.px * g.ni[2] : 2LL * g.nb * g.px,
+                               g.dim == 3 ? 2LL * g.ni[0] * g.ni[2] : 2LL * g.nb * g.px};
+      const long long sz = g.dim == 3 ? 2LL * g.px * g.ni[1] : 0;
+      for (int k = 0; k < 2; ++k) {
+        const long long n = sx + sy[k] + sz;
+        TRY(alloc_t(h, &P.ft[k][0], n));
+        P.ft[k][1] = P.ft[k][0] + sx;
+        P.ft[k][2] = P.ft[k][1] + sy[k];
+        AHOC_HIP_TRY(hipMemsetAsync(P.ft[k][0], 0, sizeof(T) * n, st));  // zero row padding
+      }
+    }
     const long long inner = g.dim == 3 ? (long long)g.px * g.ni[1] : g.px;
     P.mspec = dst_pipe_mpass_ok<T>(g.n[t], inner, g.px, mspec_gen<T>(g, P));
   }
@@ -663,25 +704,66 @@ template <typename T> int usolve(ahoc_handle* h, Prec<T>& P, const T* Q, const T
   return poisson<T>(h, P, P.bufB, P.scU, st);
 }
 
-// 2-D DST-I of every face array, in place (the unnormalised transform is its own inverse
-// up to the factor folded into the eigen scaling).
-template <typename T> int face_dst2(ahoc_handle* h, Prec<T>& P, T* Fx, T* Fy, T* Fz, hipStream_t st) {
-  const Geom& g = h->g;
-  if (g.dim == 3) {
-    TRY(dst_pass<T>(P.tb[0], Fz, Fz, 2LL * g.ni[1], 1, g.px, nullptr, 0, st));
-    TRY(dst_pass<T>(P.tb[1], Fz, Fz, 2, g.px, g.px, nullptr, 0, st));
-    TRY(dst_pass<T>(P.tb[2], Fx, Fx, 2LL * g.ni[1], 1, g.ni[2], nullptr, 0, st));
-    TRY(dst_pass<T>(P.tb[1], Fx, Fx, 2, g.ni[2], g.ni[2], nullptr, 0, st));
-    TRY(dst_pass<T>(P.tb[0], Fy, Fy, 2LL * g.ni[2], 1, g.px, nullptr, 0, st));
-    TRY(dst_pass<T>(P.tb[2], Fy, Fy, 2, g.px, g.px, nullptr, 0, st));
-  } else {
-    TRY(dst_pass<T>(P.tb[0], Fy, Fy, 2LL * g.nb, 1, g.px, nullptr, 0, st));
-    TRY(dst_pass<T>(P.tb[1], Fx, Fx, 2LL * g.nb, 1, g.ni[1], nullptr, 0, st));
-  }
-  return ST_OK;
+// Transforms of the face arrays along their own axes (unnormalised: the transform is its own
+// inverse up to the factor folded into the eigen scaling): 2-D DST-I of every face in 3-D, 1-D
+// in 2-D.  sets: bit 0 the arrays Fx, Fy, Fz, bit 1 Ux, Uy, Uz.  As sine products a pass goes
+// from one array of a pair to the other: 3-D ends where it began, 2-D goes from F to P.ft (or,
+// with from_ft, back); as FFT passes it works in place.
+template <typename T> T* const* face_arrays(Prec<T>& P, int set, T* (&f)[3]) {
+  f[0] = set ? P.Ux : P.Fx;
+  f[1] = set ? P.Uy : P.Fy;
+  f[2] = set ? P.Uz : P.Fz;
+  return f;
 }
-template <typename T> int face_dst2(ahoc_handle* h, Prec<T>& P, hipStream_t st) {
-  return face_dst2<T>(h, P, P.Fx, P.Fy, P.Fz, st);
+template <typename T> bool face_jobs(const Prec<T>& P) { return P.ft[0][0] && face_jobs_on(); }
+template <typename T>
+int face_dst2(ahoc_handle* h, Prec<T>& P, int sets, hipStream_t st, bool from_ft = false) {
+  const Geom& g = h->g;
+  const DstTables<T>* tb = P.tb;
+  SineJob<T> r[6], c[6];
+  int n = 0;
+  for (int k = 0; k < 2; ++k) {
+    if (!((sets >> k) & 1)) continue;
+    T* f[3];
+    face_arrays(P, k, f);
+    T* const* t = P.ft[k];
+    if (g.dim == 3) {
+      // rows, then strided; y faces of the second set are [2][n_x'][n_z'] (z rows)
+      const long long yr = k ? 2LL * g.ni[0] : 2LL * g.ni[2], yp = k ? g.ni[2] : g.px;
+      if (face_jobs(P)) {
+        r[n] = {&tb[0], f[2], t[2], 2LL * g.ni[1], 1, g.px};
+        c[n++] = {&tb[1], t[2], f[2], 2, g.px, g.px};
+        r[n] = {&tb[2], f[0], t[0], 2LL * g.ni[1], 1, g.ni[2]};
+        c[n++] = {&tb[1], t[0], f[0], 2, g.ni[2], g.ni[2]};
+        r[n] = {&tb[k ? 2 : 0], f[1], t[1], yr, 1, yp};
+        c[n++] = {&tb[k ? 0 : 2], t[1], f[1], 2, yp, yp};
+      } else {
+        TRY(dst_pass<T>(tb[0], f[2], f[2], 2LL * g.ni[1], 1, g.px, nullptr, 0, st));
+        TRY(dst_pass<T>(tb[1], f[2], f[2], 2, g.px, g.px, nullptr, 0, st));
+        TRY(dst_pass<T>(tb[2], f[0], f[0], 2LL * g.ni[1], 1, g.ni[2], nullptr, 0, st));
+        TRY(dst_pass<T>(tb[1], f[0], f[0], 2, g.ni[2], g.ni[2], nullptr, 0, st));
+        TRY(dst_pass<T>(tb[k ? 2 : 0], f[1], f[1], yr, 1, yp, nullptr, 0, st));
+        TRY(dst_pass<T>(tb[k ? 0 : 2], f[1], f[1], 2, yp, yp, nullptr, 0, st));
+      }
+    } else if (face_jobs(P)) {
+      r[n++] = {&tb[0], from_ft ? t[1] : f[1], from_ft ? f[1] : t[1], 2LL * g.nb, 1, g.px};
+      r[n++] = {&tb[1], from_ft ? t[0] : f[0], from_ft ? f[0] : t[0], 2LL * g.nb, 1, g.ni[1]};
+    } else {
+      TRY(dst_pass<T>(tb[0], f[1], f[1], 2LL * g.nb, 1, g.px, nullptr, 0, st));
+      TRY(dst_pass<T>(tb[1], f[0], f[0], 2LL * g.nb, 1, g.ni[1], nullptr, 0, st));
+    }
+  }
+  TRY(dst_sine_jobs<T>(r, n, st));
+  return g.dim == 3 ? dst_sine_jobs<T>(c, n, st) : ST_OK;
+}
+// Whether the layers of a 2-D lift go to P.ft, from where face_dst2 takes them to F and U.
+template <typename T> bool lift_to_ft(const ahoc_handle* h, const Prec<T>& P) { return h->g.dim == 2 && face_jobs(P); }
+// Boundary residual from the face sums in F, through their transforms.
+template <typename T>
+int gather_sums(ahoc_handle* h, Prec<T>& P, const T* Q, const T* srcq, double* R, hipStream_t st) {
+  TRY(face_dst2<T>(h, P, 1, st));
+  if (lift_to_ft(h, P)) return gather_faces<T>(h->g, P.ft[0][0], P.ft[0][1], nullptr, Q, P.af, srcq, R, st);
+  return gather_faces<T>(h->g, P.Fx, P.Fy, P.Fz, Q, P.af, srcq, R, st);
 }
 
 // Homogeneous V-solve V = -L^{-1} L_h^bnd[Q] into P.bufA through the spectral lift: face
@@ -693,8 +775,9 @@ int vsolve_spec(ahoc_handle* h, Prec<T>& P, const T* Q, hipStream_t st, bool ski
   const Geom& g = h->g;
   if (!lifted) {  // (else the face layers are in Fx, Fy, Fz already)
     hipEvent_t e = tbegin(h, st);
-    TRY(face_lift<T>(g, h->wv, Q, P.Fx, P.Fy, P.Fz, st));
-    TRY(face_dst2<T>(h, P, st));
+    const bool ft = lift_to_ft(h, P);
+    TRY(face_lift<T>(g, h->wv, Q, ft ? P.ft[0][0] : P.Fx, ft ? P.ft[0][1] : P.Fy, P.Fz, st));
+    TRY(face_dst2<T>(h, P, 1, st, ft));
     tend(h, AHOC_K_LIFT, e, (double)TQ(g) * 2.0 * sizeof(T), st);
   }
   const double pass_bytes = 2.0 * (double)g.nint * g.nb * sizeof(T);
@@ -805,28 +888,22 @@ template <typename T> int matvec_mspec(ahoc_handle* h, Prec<T>& P, const T* Q, d
   const Geom& g = h->g;
   const bool d3 = g.dim == 3;
   const bool tiled = d3 && P.mq;
-  if (tiled) {
-    // both face-layer sets in one pass over Q, then the V-solve's layer spectra
-    hipEvent_t e = tbegin(h, st);
-    TRY(face_lifts3<T>(g, h->wv, Q, P.mq, P.Fx, P.Fy, P.Fz, P.Ux, P.Uy, P.Uz, st));
-    TRY(face_dst2<T>(h, P, st));
-    tend(h, AHOC_K_LIFT, e, (double)TQ(g) * 4.0 * sizeof(T), st);
-  }
-  TRY(vsolve_spec<T>(h, P, Q, st, true, tiled));
+  const bool ft = lift_to_ft(h, P);
+  // both face-layer sets and their spectra: 3-D in one tiled pass over Q, 2-D in one pass of
+  // its own
   hipEvent_t el = tbegin(h, st);
-  if (!tiled) TRY(face_lift_m<T>(g, h->w, Q, P.ia, P.Ux, P.Uy, P.Uz, st));
-  if (d3) {
-    // 2-D spectra: x and z faces as the lift's; y faces [2][n_x'][n_z'] (z rows, x strided)
-    TRY(dst_pass<T>(P.tb[0], P.Uz, P.Uz, 2LL * g.ni[1], 1, g.px, nullptr, 0, st));
-    TRY(dst_pass<T>(P.tb[1], P.Uz, P.Uz, 2, g.px, g.px, nullptr, 0, st));
-    TRY(dst_pass<T>(P.tb[2], P.Ux, P.Ux, 2LL * g.ni[1], 1, g.ni[2], nullptr, 0, st));
-    TRY(dst_pass<T>(P.tb[1], P.Ux, P.Ux, 2, g.ni[2], g.ni[2], nullptr, 0, st));
-    TRY(dst_pass<T>(P.tb[2], P.Uy, P.Uy, 2LL * g.ni[0], 1, g.ni[2], nullptr, 0, st));
-    TRY(dst_pass<T>(P.tb[0], P.Uy, P.Uy, 2, g.ni[2], g.ni[2], nullptr, 0, st));
+  if (tiled) {
+    TRY(face_lifts3<T>(g, h->wv, Q, P.mq, P.Fx, P.Fy, P.Fz, P.Ux, P.Uy, P.Uz, st));
+  } else if (!d3) {
+    TRY(face_lifts2<T>(g, h->wv, Q, P.ia, ft ? P.ft[0][0] : P.Fx, ft ? P.ft[0][1] : P.Fy, ft ? P.ft[1][0] : P.Ux,
+                       ft ? P.ft[1][1] : P.Uy, st));
   } else {
-    TRY(face_dst2<T>(h, P, P.Ux, P.Uy, nullptr, st));
+    TRY(face_lift<T>(g, h->wv, Q, P.Fx, P.Fy, P.Fz, st));
+    TRY(face_lift_m<T>(g, h->w, Q, P.ia, P.Ux, P.Uy, P.Uz, st));
   }
-  tend(h, AHOC_K_LIFT, el, (double)TQ(g) * 3.0 * sizeof(T), st);
+  TRY(face_dst2<T>(h, P, 3, st, ft));
+  tend(h, AHOC_K_LIFT, el, (double)TQ(g) * 7.0 * sizeof(T), st);
+  TRY(vsolve_spec<T>(h, P, Q, st, true, true));
   T* buf = P.bufA;
   const double vol = (double)g.nint * g.nb * sizeof(T);
   const long long rows = d3 ? (long long)g.ni[1] * g.ni[2] : (long long)g.nb * g.ni[1];
@@ -865,8 +942,7 @@ template <typename T> int matvec_mspec(ahoc_handle* h, Prec<T>& P, const T* Q, d
                        2LL * g.ni[1], 1, st));
   tend(h, AHOC_K_FACE_REDUCE, er, vol, st);
   hipEvent_t ef = tbegin(h, st);
-  TRY(face_dst2<T>(h, P, st));
-  TRY(gather_faces<T>(g, P.Fx, P.Fy, P.Fz, Q, P.af, nullptr, y, st));
+  TRY(gather_sums<T>(h, P, Q, nullptr, y, st));
   tend(h, AHOC_K_GATHER, ef, (double)TQ(g) * (5 * sizeof(T) + sizeof(double)), st);
   return ST_OK;
 }
@@ -874,8 +950,8 @@ template <typename T> int matvec_mspec(ahoc_handle* h, Prec<T>& P, const T* Q, d
 // U-solve for the boundary residual only: U = L^{-1}(M(V/alpha) + src) is never formed.
 // The forward transforms run as usual; the slowest-axis pass scales the spectrum, forms
 // the face sums along its own axis and stores the scaled spectrum; one streaming
-// reduction forms the sums along the other two axes, and 2-D inverse transforms of the
-// face arrays give the combination 6 U_1 - 3/2 U_2 + 2/9 U_3 next to each face.
+// reduction forms the sums along the other two axes, and the inverse transforms of the
+// face arrays (gather_sums) give the combination 6 U_1 - 3/2 U_2 + 2/9 U_3 next to each face.
 template <typename T> int usolve_spec(ahoc_handle* h, Prec<T>& P, const T* Q, const T* src, hipStream_t st) {
   const Geom& g = h->g;
   hipEvent_t e = tbegin(h, st);
@@ -915,9 +991,6 @@ template <typename T> int usolve_spec(ahoc_handle* h, Prec<T>& P, const T* Q, co
                        2LL * g.ni[1], 1, st));
     tend(h, AHOC_K_FACE_REDUCE, er, (double)g.nint * g.nb * sizeof(T), st);
   }
-  hipEvent_t ef = tbegin(h, st);
-  TRY(face_dst2<T>(h, P, st));
-  tend(h, AHOC_K_GATHER, ef, (double)TQ(g) * 2.0 * sizeof(T), st);
   return ST_OK;
 }
 
@@ -964,29 +1037,39 @@ int precond_init(ahoc_handle* h, hipStream_t st) {
   return ST_OK;
 }
 
-// 2-D DST-I of every face block of a Q-layout vector, from x into y (y may equal x; the
-// first pass of each face reads x, in 3-D it writes `mid`, which may be y).  Faces x-, x+ hold
-// [k][j], y-, y+ [k][i], z-, z+ [j][i] (lower axis fastest, no padding).  A square 2-D
-// batch (N_x = N_y) is one row pass: its Q vector is 4 nb rows of N-1 entries.
-int face_dst_q(ahoc_handle* h, const double* x, double* y, double* mid, hipStream_t st) {
+// DST-I of every face block of a Q-layout vector along the face's own axes, from x into y (y may
+// equal x where no pass runs as sine products; the first pass of each face reads x, in 3-D it
+// writes `mid`).  Faces x-, x+ hold [k][j], y-, y+ [k][i], z-, z+ [j][i] (lower axis fastest, no
+// padding).  A square 2-D batch (N_x = N_y) is one row pass: its Q vector is 4 nb rows of N-1
+// entries.
+int face_dst_q(ahoc_handle* h, const double* x, double* y, double* mid, bool jobs, hipStream_t st) {
   const Geom& g = h->g;
   const DstTables<double>* tb = h->ptb;
-  const long long ox = g.face_off[0], oy = g.face_off[2];
+  const long long ox = g.face_off[0], oy = g.face_off[2], oz = g.face_off[4];
+  SineJob<double> r[4], c[3];
+  int nr = 0, nc = 0;
   if (g.dim == 3) {
-    const long long oz = g.face_off[4];
-    TRY(dst_pass<double>(tb[1], x + ox, mid + ox, 2LL * g.ni[2], 1, g.ni[1], nullptr, 0, st));
-    TRY(dst_pass<double>(tb[2], mid + ox, y + ox, 2, g.ni[1], g.ni[1], nullptr, 0, st));
-    TRY(dst_pass<double>(tb[0], x + oy, mid + oy, 2LL * g.ni[2], 1, g.ni[0], nullptr, 0, st));
-    TRY(dst_pass<double>(tb[2], mid + oy, y + oy, 2, g.ni[0], g.ni[0], nullptr, 0, st));
-    TRY(dst_pass<double>(tb[0], x + oz, mid + oz, 2LL * g.ni[1], 1, g.ni[0], nullptr, 0, st));
-    TRY(dst_pass<double>(tb[1], mid + oz, y + oz, 2, g.ni[0], g.ni[0], nullptr, 0, st));
+    r[nr++] = {&tb[1], x + ox, mid + ox, 2LL * g.ni[2], 1, g.ni[1]};
+    c[nc++] = {&tb[2], mid + ox, y + ox, 2, g.ni[1], g.ni[1]};
+    r[nr++] = {&tb[0], x + oy, mid + oy, 2LL * g.ni[2], 1, g.ni[0]};
+    c[nc++] = {&tb[2], mid + oy, y + oy, 2, g.ni[0], g.ni[0]};
+    r[nr++] = {&tb[0], x + oz, mid + oz, 2LL * g.ni[1], 1, g.ni[0]};
+    c[nc++] = {&tb[1], mid + oz, y + oz, 2, g.ni[0], g.ni[0]};
   } else if (g.n[0] == g.n[1] && g.nq == 4LL * g.ni[0]) {
-    TRY(dst_pass<double>(tb[0], x, y, 4LL * g.nb, 1, g.ni[0], nullptr, 0, st));
+    r[nr++] = {&tb[0], x, y, 4LL * g.nb, 1, g.ni[0]};
   } else {  // each face line of every instance of a batch (instances nq apart)
-    TRY(dst_pass<double>(tb[1], x + ox, y + ox, g.nb, 1, g.nq, nullptr, 0, st));
-    TRY(dst_pass<double>(tb[1], x + ox + g.ni[1], y + ox + g.ni[1], g.nb, 1, g.nq, nullptr, 0, st));
-    TRY(dst_pass<double>(tb[0], x + oy, y + oy, g.nb, 1, g.nq, nullptr, 0, st));
-    TRY(dst_pass<double>(tb[0], x + oy + g.ni[0], y + oy + g.ni[0], g.nb, 1, g.nq, nullptr, 0, st));
+    for (int s = 0; s < 2; ++s) {
+      r[nr++] = {&tb[1], x + ox + s * g.ni[1], y + ox + s * g.ni[1], g.nb, 1, g.nq};
+      r[nr++] = {&tb[0], x + oy + s * g.ni[0], y + oy + s * g.ni[0], g.nb, 1, g.nq};
+    }
+  }
+  if (jobs) {
+    TRY(dst_sine_jobs<double>(r, nr, st));
+    return dst_sine_jobs<double>(c, nc, st);
+  }
+  for (int i = 0; i < nr; ++i) {
+    TRY(dst_pass<double>(*r[i].tb, r[i].in, r[i].out, r[i].outer, 1, r[i].pitch, nullptr, 0, st));
+    if (i < nc) TRY(dst_pass<double>(*c[i].tb, c[i].in, c[i].out, 2, c[i].inner, c[i].inner, nullptr, 0, st));
   }
   return ST_OK;
 }
@@ -995,12 +1078,14 @@ int face_dst_q(ahoc_handle* h, const double* x, double* y, double* mid, hipStrea
 int precond_apply(ahoc_handle* h, const double* v, double* y, hipStream_t st) {
   const Geom& g = h->g;
   hipEvent_t e = tbegin(h, st);
-  // with a scratch vector (an axis without an FFT plan) no pass works in place
+  const bool jobs = h->pjobs && face_jobs_on();
+  // with the scratch vector (sine products of all faces, or an axis without an FFT plan) no
+  // pass works in place
   double* mid = h->zt ? h->zt : y;
   double* f = g.dim == 3 ? y : mid;
-  TRY(face_dst_q(h, v, f, mid, st));
+  TRY(face_dst_q(h, v, f, mid, jobs, st));
   TRY(precond_modes<double>(g, h->pc, h->qc, f, st));
-  TRY(face_dst_q(h, f, y, mid, st));
+  TRY(face_dst_q(h, f, y, mid, jobs, st));
   tend(h, AHOC_K_PRECOND, e, (double)TQ(g) * 16.0, st);
   return ST_OK;
 }
@@ -1063,8 +1148,8 @@ template <typename T> int matvec(ahoc_handle* h, Prec<T>& P, const double* q, do
     TRY(vsolve_spec<T>(h, P, qT, st));
     TRY(usolve_spec<T>(h, P, qT, nullptr, st));
     hipEvent_t eg = tbegin(h, st);
-    TRY(gather_faces<T>(h->g, P.Fx, P.Fy, P.Fz, qT, P.af, nullptr, y, st));
-    tend(h, AHOC_K_GATHER, eg, (double)TQ(h->g) * (3 * sizeof(T) + sizeof(double)), st);
+    TRY(gather_sums<T>(h, P, qT, nullptr, y, st));
+    tend(h, AHOC_K_GATHER, eg, (double)TQ(h->g) * (5 * sizeof(T) + sizeof(double)), st);
   } else {
     TRY(vsolve<T>(h, P, qT, nullptr, st));
     TRY(usolve<T>(h, P, qT, nullptr, st));
@@ -1100,7 +1185,7 @@ int schur_rhs(ahoc_handle* h, Prec<T>& P, const T* sv, const T* su, const T* sq,
   TRY(vsolve<T>(h, P, P.zq, sv, st));
   if (P.spectral) {
     TRY(usolve_spec<T>(h, P, P.zq, su, st));
-    TRY(gather_faces<T>(h->g, P.Fx, P.Fy, P.Fz, P.zq, P.af, sq, h->R, st));
+    TRY(gather_sums<T>(h, P, P.zq, sq, h->R, st));
   } else {
     TRY(usolve<T>(h, P, P.zq, su, st));
     TRY(gather<T>(h->g, h->w, P.bufB, P.zq, P.af, sq, h->R, st));
@@ -1603,7 +1688,8 @@ int setup_impl(const ahoc_problem* pbs, int count, hipStream_t st, ahoc_handle* 
   TRY(alloc_t(h, &h->dq, TQ(g)));
   TRY(alloc_t(h, &h->rvec, TQ(g)));
   TRY(alloc_t(h, &h->zvec, TQ(g)));
-  if (!has_plans(g)) TRY(alloc_t(h, &h->zt, TQ(g)));
+  h->pjobs = face_jobs_pay(g);
+  if (h->pjobs || !has_plans(g)) TRY(alloc_t(h, &h->zt, TQ(g)));
   if (h->opt.use_graph) {
     TRY(alloc_t(h, &h->gin, TQ(g)));
     TRY(alloc_t(h, &h->gout, TQ(g)));

@@ -310,6 +310,19 @@ int dst_ppt(int N);
 template <typename T>
 int dst_direct_pass(int N, const T* sn2, const T* in, T* out, long long outer, long long inner, long long pitch,
                     const DstScale<T>* fused, hipStream_t st, T* tmp = nullptr);
+// Plain passes of any lengths in as few launches as their number allows, as sine products on
+// the matrix cores (dst_direct.hip): all of rows or all of strided pencils, each writing an
+// array apart from every job's input.  Refused (ST_UNSUPPORTED) before anything is launched
+// where a length's tables exceed the LDS (N > DST_SINE_JOBS_MAX_N).
+template <typename T> struct SineJob {
+  const DstTables<T>* tb;
+  const T* in;
+  T* out;
+  long long outer, inner, pitch;
+};
+template <typename T> int dst_sine_jobs(const SineJob<T>* jobs, int count, hipStream_t st);
+constexpr int DST_SINE_JOBS_MAX_N = 1024;
+double dst_sine_flops(int N, long long outer, long long inner);
 int dst_default_tile(int N, int elem_bytes);
 
 }  // namespace ahoc

@@ -21,11 +21,15 @@
 // Against one thread per output (the form this replaces): FP32 along y of 199 x 149 x 119
 // points 549 -> 19 us a call, an FP64 Poisson solve of 99 x 89 x 74 points 227 -> 61 us, a 2-D
 // 500 x 300 FP64 solve (25 GMRES iterations) 118.8 -> 7.4 ms; errors against 64-bit sums no
-// larger (FP32 2.2e-7 -> 1.6e-7).
+// larger (FP32 2.2e-7 -> 1.6e-7).  Where a pass has few pencils (lines of 2-D faces) its time
+// is latency: four lines of N = 1024 in FP64 took 25 us with a 128-step sum per wavefront and
+// staging loops that waited for each load, 10.7 us with the sum split over four wavefronts and
+// one trip to memory.
 // k_dst_direct, one thread per output and the whole pencil in LDS, remains for in-place
 // passes of N > 2048, whose outputs k_dst_sine could not hold in registers.
 #include "common.h"
 
+#include <algorithm>
 #include <mutex>
 
 namespace ahoc {
@@ -164,99 +168,118 @@ template <> struct SineOps<double> {
 template <typename T> struct SineArgs {
   const T* in;
   T* out;
-  const T* sn2;       // sin(pi j / N), j = 0..2N-1
+  const T* sn;        // sin(pi j / N): j = 0..2N-1, or (half, even N) j = 0..N/2
   int N;
+  int half;
   long long outer, inner, pitch;
   long long ntile_inner;
-  bool scaled;        // multiply by the eigen scaling before the store (strided pencils)
-  DstScale<T> fs;
 };
 
-// m values of one LDS chunk, and the words of one half's (e or o) tile
-template <int TP> constexpr int sine_chunk() { return 2048 / (16 * TP); }
-template <typename T, bool ROWS, int TP> constexpr int sine_half() {
-  return ROWS ? 16 * TP * (sine_chunk<TP>() + SineOps<T>::PAD) : sine_chunk<TP>() * (TP == 1 ? 16 : 16 * TP + 16);
+// Words of one half's (e or o) tile of mc values of m (a multiple of 64: conflict-free rows)
+template <typename T, bool ROWS, int TP> constexpr int sine_half(int mc) {
+  return ROWS ? 16 * TP * (mc + SineOps<T>::PAD) : mc * (TP == 1 ? 16 : 16 * TP + 16);
 }
+// Period table in LDS: one word of padding every 32, so that the strides 2 m of the 16 lanes'
+// indices do not meet in one bank where m is a multiple of a power of two
+__host__ __device__ constexpr int sine_pad(int j) { return j + (j >> 5); }
 
-// grid.x: tiles of 16 TP pencils; grid.y: groups of blockDim.x / 64 * TO output pairs (one
-// group when the pass runs in place: the tile's reads end, at a barrier, before its writes).
-template <typename T, bool ROWS, int TO, int TP>
-__global__ void __launch_bounds__(1024) k_dst_sine(SineArgs<T> a) {
+// The outputs of TO pairs per KS wavefronts, from pair `first` on, of tile `tile` of 16 TP
+// pencils.  KS wavefronts take every KS-th step of the sum over m and add their sums up at the
+// end (in wavefront order): where a pass has so few pencils that most of the chip is idle, its
+// time is the length of that chain.  mc: values of m staged at a time.
+// In place (one work-group holds every output of the tile) the tile's reads end, at a barrier,
+// before its writes.  scaled (strided pencils): eigen scaling by fs before the store.
+template <typename T, bool ROWS, int TO, int TP, int KS>
+__device__ __forceinline__ void sine_tile(const SineArgs<T>& a, const DstScale<T>& fs, bool scaled, long long tile,
+                                          int first, bool in_place, int mc) {
   using S = SineOps<T>;
   using v4 = typename S::v4;
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int P = 16 * TP, MC = sine_chunk<TP>(), HALF = sine_half<T, ROWS, TP>();
-  constexpr int LDX = MC + S::PAD;             // rows: [pencil][m]
+  constexpr int P = 16 * TP;
+  const int LDX = mc + S::PAD;                 // rows: [pencil][m]
   constexpr int LDC = TP == 1 ? 16 : P + 16;   // strided: [m][pencil]
   T* xe = reinterpret_cast<T*>(smem);
-  T* xo = xe + HALF;
-  T* tab = xo + HALF;
+  T* xo = xe + sine_half<T, ROWS, TP>(mc);
+  T* tab = xo + sine_half<T, ROWS, TP>(mc);
   const int N = a.N, L = N - 1, two_n = 2 * N, Hm = N / 2;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nt = blockDim.x;
   const int li = lane & 15, lk = lane >> 4;
   long long base, c0 = 0;
   int ncols;
   if (ROWS) {
-    base = (long long)blockIdx.x * P;
+    base = tile * P;
     const long long left = a.outer - base;
     ncols = left < P ? (int)left : P;
   } else {
-    const long long o = blockIdx.x / a.ntile_inner;
-    c0 = (blockIdx.x - o * a.ntile_inner) * (long long)P;
+    const long long o = tile / a.ntile_inner;
+    c0 = (tile - o * a.ntile_inner) * (long long)P;
     base = o * (long long)L * a.inner + c0;
     const long long left = a.inner - c0;
     ncols = left < P ? (int)left : P;
   }
-  for (int i = threadIdx.x; i < two_n; i += nt) tab[i] = a.sn2[i];
+  for (int i = threadIdx.x; i < two_n; i += nt) {
+    if (a.half) {  // sin(pi + t) = -sin t, sin(pi - t) = sin t
+      const int j = i >= N ? i - N : i;
+      const T v = a.sn[j > Hm ? N - j : j];
+      tab[sine_pad(i)] = i >= N ? -v : v;
+    } else {
+      tab[sine_pad(i)] = a.sn[i];
+    }
+  }
   // this lane's outputs of pair t: k = 2 j + 1 (odd) and 2 j + 2 (even), j = j0[t] + li; its
-  // sine index starts at m = 1 + lk and advances by 4 k per step, modulo the period
-  const int p0 = (blockIdx.y * (nt >> 6) + w) * TO;
+  // sine index starts at m = 1 + lk (the wavefront's first step) and advances by 4 KS k per
+  // step, modulo the period
+  const int wk = KS > 1 ? w % KS : 0;
+  const int p0 = first + w / KS * TO;
   unsigned ie[TO], io[TO], de[TO], dd[TO];
 #pragma unroll
   for (int t = 0; t < TO; ++t) {
     const unsigned k = 2u * (16u * (p0 + t) + li) + 1u;
-    ie[t] = (k % two_n) * (1u + lk) % two_n;
-    io[t] = ((k + 1u) % two_n) * (1u + lk) % two_n;
-    de[t] = 4u * (k % two_n) % two_n;
-    dd[t] = 4u * ((k + 1u) % two_n) % two_n;
+    ie[t] = (k % two_n) * (1u + lk + 4u * wk) % two_n;
+    io[t] = ((k + 1u) % two_n) * (1u + lk + 4u * wk) % two_n;
+    de[t] = 4u * KS * (k % two_n) % two_n;
+    dd[t] = 4u * KS * ((k + 1u) % two_n) % two_n;
   }
   v4 ae[TO][TP], ao[TO][TP];
 #pragma unroll
   for (int t = 0; t < TO; ++t)
 #pragma unroll
     for (int b = 0; b < TP; ++b) ae[t][b] = ao[t][b] = v4{T(0), T(0), T(0), T(0)};
-  for (int m0 = 0; m0 < Hm; m0 += MC) {
-    const int kc = Hm - m0 < MC ? (Hm - m0 + 3) & ~3 : MC;
+  for (int m0 = 0; m0 < Hm; m0 += mc) {
+    const int kc = Hm - m0 < mc ? (Hm - m0 + 3) & ~3 : mc;
     if (m0) __syncthreads();  // the last chunk's reads are done
-    for (int e = threadIdx.x; e < kc * P; e += nt) {
-      int p, q;
-      if (ROWS) {
-        p = e / kc;
-        q = e - p * kc;
-      } else {
-        q = e / P;
-        p = e - q * P;
+    // eight positions per thread and step, their sixteen loads in flight together (four in the
+    // FP64 row passes of up to 1024 threads, whose registers hold no more)
+    constexpr int U = ROWS && sizeof(T) == 8 && KS == 1 ? 4 : 8;
+    // (rows past the last are left as they are: a pencil's sums read only its own tile entries)
+    const int todo = kc * (ROWS ? ncols : P);
+    for (int e0 = threadIdx.x; e0 < todo; e0 += U * nt) {
+      T x[U], y[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = e0 + u * nt;
+        const int p = ROWS ? e / kc : e % P, q = ROWS ? e - p * kc : e / P;
+        const int m = m0 + q + 1;
+        const bool ok = e < todo && m <= Hm && p < ncols;
+        const T* src = ROWS ? a.in + (base + p) * a.pitch : a.in + base + p;
+        const long long st = ROWS ? 1 : a.inner;
+        x[u] = ok ? src[(m - 1) * st] : T(0);
+        y[u] = ok && 2 * m != N ? src[(N - m - 1) * st] : T(0);
       }
-      const int m = m0 + q + 1;
-      T x = 0, y = 0;
-      if (m <= Hm && p < ncols) {
-        if (ROWS) {
-          const T* rp = a.in + (base + p) * a.pitch;
-          x = rp[m - 1];
-          if (2 * m != N) y = rp[N - m - 1];
-        } else {
-          const T* cp = a.in + base + p;
-          x = cp[(long long)(m - 1) * a.inner];
-          if (2 * m != N) y = cp[(long long)(N - m - 1) * a.inner];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = e0 + u * nt;
+        const int p = ROWS ? e / kc : e % P, q = ROWS ? e - p * kc : e / P;
+        if (e < todo) {
+          const int at = ROWS ? p * LDX + q : q * LDC + p;
+          xe[at] = x[u] + y[u];
+          xo[at] = x[u] - y[u];
         }
       }
-      const int at = ROWS ? p * LDX + q : q * LDC + p;
-      xe[at] = x + y;
-      xo[at] = x - y;
     }
     __syncthreads();
 #pragma unroll 4
-    for (int s = 0; s < kc; s += 4) {
+    for (int s = 4 * wk; s < kc; s += 4 * KS) {
       T be[TP], bo[TP];
 #pragma unroll
       for (int b = 0; b < TP; ++b) {
@@ -266,7 +289,7 @@ __global__ void __launch_bounds__(1024) k_dst_sine(SineArgs<T> a) {
       }
 #pragma unroll
       for (int t = 0; t < TO; ++t) {
-        const T se = tab[ie[t]], so = tab[io[t]];
+        const T se = tab[sine_pad(ie[t])], so = tab[sine_pad(io[t])];
         ie[t] += de[t];
         io[t] += dd[t];
         ie[t] = min(ie[t], ie[t] - (unsigned)two_n);
@@ -284,20 +307,49 @@ __global__ void __launch_bounds__(1024) k_dst_sine(SineArgs<T> a) {
       }
     }
   }
-  if (gridDim.y == 1) __syncthreads();  // in place: every read of the tile before its writes
+  if (in_place) __syncthreads();
+  if constexpr (KS > 1) {
+    // [output group][wavefront][value][lane] over the tile's LDS
+    constexpr int NV = TO * TP * 8;
+    __syncthreads();
+    T* red = xe + (w / KS) * (KS - 1) * NV * 64;
+#pragma unroll
+    for (int t = 0; t < TO; ++t)
+#pragma unroll
+      for (int b = 0; b < TP; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (wk) {
+            red[((wk - 1) * NV + (t * TP + b) * 8 + r) * 64 + lane] = ae[t][b][r];
+            red[((wk - 1) * NV + (t * TP + b) * 8 + 4 + r) * 64 + lane] = ao[t][b][r];
+          }
+    __syncthreads();
+    if (wk) return;
+#pragma unroll
+    for (int k = 0; k < KS - 1; ++k)
+#pragma unroll
+      for (int t = 0; t < TO; ++t)
+#pragma unroll
+        for (int b = 0; b < TP; ++b)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            ae[t][b][r] += red[(k * NV + (t * TP + b) * 8 + r) * 64 + lane];
+            ao[t][b][r] += red[(k * NV + (t * TP + b) * 8 + 4 + r) * 64 + lane];
+          }
+  }
 #pragma unroll
   for (int b = 0; b < TP; ++b) {
     T A = 1, B = 0, sc = 1;
-    if (!ROWS && a.scaled) {
+    if (!ROWS && scaled) {
       const long long col = c0 + 16 * b + li;
-      const long long ib = col / a.fs.na;
-      const long long ia = col - ib * a.fs.na;
-      sc = a.fs.scale;
-      if (col < a.inner && ia < a.fs.nva) {
-        const T sa = a.fs.s_a[ia];
-        const T sb = a.fs.s_b ? a.fs.s_b[ib] : T(0);
-        A = sa + sb + a.fs.c_ab * sa * sb + a.fs.a0 + a.fs.ka * sa + a.fs.kb * sb;
-        B = T(1) + a.fs.c_ta * sa + a.fs.c_tb * sb + a.fs.kt;
+      const long long ib = col / fs.na;
+      const long long ia = col - ib * fs.na;
+      sc = fs.scale;
+      if (col < a.inner && ia < fs.nva) {
+        const T sa = fs.s_a[ia];
+        const T sb = fs.s_b ? fs.s_b[ib] : T(0);
+        A = sa + sb + fs.c_ab * sa * sb + fs.a0 + fs.ka * sa + fs.kb * sb;
+        B = T(1) + fs.c_ta * sa + fs.c_tb * sb + fs.kt;
       }
     }
 #pragma unroll
@@ -308,9 +360,9 @@ __global__ void __launch_bounds__(1024) k_dst_sine(SineArgs<T> a) {
         const int k = 2 * (16 * (p0 + t) + (ROWS ? li : S::row(lk, r)));  // positions k, k + 1 (from 0)
         if (p >= ncols) continue;
         T ve = ae[t][b][r], vo = ao[t][b][r];
-        if (!ROWS && a.scaled) {
-          if (k < L) ve *= sc / (A + B * a.fs.s_this[k]);
-          if (k + 1 < L) vo *= sc / (A + B * a.fs.s_this[k + 1]);
+        if (!ROWS && scaled) {
+          if (k < L) ve *= sc / (A + B * fs.s_this[k]);
+          if (k + 1 < L) vo *= sc / (A + B * fs.s_this[k + 1]);
         }
         T* op = ROWS ? a.out + (base + p) * a.pitch + k : a.out + base + (long long)k * a.inner + p;
         if (k < L) op[0] = ve;
@@ -320,7 +372,32 @@ __global__ void __launch_bounds__(1024) k_dst_sine(SineArgs<T> a) {
   }
 }
 
+// grid.x: tiles; grid.y: groups of blockDim.x / 64 / KS * TO output pairs (one group in place)
+template <typename T, bool ROWS, int TO, int TP, int KS>
+__global__ void __launch_bounds__(KS > 1 ? 256 : 1024) k_dst_sine(SineArgs<T> a, DstScale<T> fs, int scaled, int mc) {
+  sine_tile<T, ROWS, TO, TP, KS>(a, fs, scaled != 0, blockIdx.x, blockIdx.y * ((blockDim.x >> 6) / KS) * TO,
+                                 gridDim.y == 1, mc);
+}
+
+// Several passes in one launch (the faces of a grid: a few thousand pencils in up to six
+// arrays, whose separate launches each cost more than their work).  Work-groups of four
+// wavefronts, 128 / KS outputs of 16 pencils each.
+constexpr int SINE_JOBS_MAX = 6;
+template <typename T> struct SineJobs {
+  SineArgs<T> job[SINE_JOBS_MAX];
+  int end[SINE_JOBS_MAX];     // end of the job's work-groups
+  int groups[SINE_JOBS_MAX];  // output groups of a tile
+  int mc;
+};
+template <typename T, bool ROWS, int KS> __global__ void __launch_bounds__(256) k_dst_sine_jobs(SineJobs<T> s) {
+  int j = 0;
+  while ((int)blockIdx.x >= s.end[j]) ++j;
+  const int b = (int)blockIdx.x - (j ? s.end[j - 1] : 0), g = s.groups[j];
+  sine_tile<T, ROWS, 1, 1, KS>(s.job[j], DstScale<T>(), false, b / g, b % g * (4 / KS), false, s.mc);
+}
+
 constexpr size_t DIRECT_LDS_MAX = 160 * 1024;
+constexpr long long SINE_CHAIN_WGS = 256;  // fewer work-groups than this: the sums over m are split too
 
 template <typename T> void set_direct_lds_attr() {
   static std::once_flag once;
@@ -330,20 +407,37 @@ template <typename T> void set_direct_lds_attr() {
   });
 }
 
-template <typename T, bool ROWS, int TO, int TP>
-int sine_launch(const SineArgs<T>& a, long long tiles, int groups, int waves, hipStream_t st) {
-  if (tiles > 0x7fffffffLL || groups > 65535) return ST_UNSUPPORTED;
-  const size_t lds = sizeof(T) * (2 * (size_t)sine_half<T, ROWS, TP>() + 2 * (size_t)a.N);
+template <typename K> int sine_lds(K* kernel, size_t lds, std::once_flag& once) {
   if (lds > DIRECT_LDS_MAX) return ST_UNSUPPORTED;
-  if (lds > 64 * 1024) {
-    static std::once_flag once;
-    std::call_once(once, [] {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dst_sine<T, ROWS, TO, TP>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)DIRECT_LDS_MAX);
+  if (lds > 64 * 1024)
+    std::call_once(once, [&] {
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)DIRECT_LDS_MAX);
     });
-  }
-  hipLaunchKernelGGL((k_dst_sine<T, ROWS, TO, TP>), dim3((unsigned)tiles, (unsigned)groups), dim3(64 * waves), lds,
-                     st, a);
+  return ST_OK;
+}
+template <typename T, bool ROWS, int TP> size_t sine_lds_bytes(int N, int mc) {
+  return sizeof(T) * (2 * (size_t)sine_half<T, ROWS, TP>(mc) + sine_pad(2 * N));
+}
+// m values staged at a time: 2048 / P for the passes that fill the chip (32 KB of FP64, several
+// work-groups per CU); where one chain is the time, as many as there are up to 512 (one trip to
+// memory).
+int sine_mc(int N, int P, bool chain) {
+  const int full = chain ? 512 : 2048 / P;
+  int mc = 64;
+  while (mc < full && mc < N / 2) mc *= 2;
+  return mc;
+}
+
+template <typename T, bool ROWS, int TO, int TP, int KS = 1>
+int sine_launch(const SineArgs<T>& a, const DstScale<T>* fs, long long tiles, int groups, int waves, hipStream_t st) {
+  if (tiles > 0x7fffffffLL || groups > 65535) return ST_UNSUPPORTED;
+  const int mc = sine_mc(a.N, 16 * TP, KS > 1);
+  const size_t lds = sine_lds_bytes<T, ROWS, TP>(a.N, mc);
+  static std::once_flag once;
+  TRY_ST(sine_lds(&k_dst_sine<T, ROWS, TO, TP, KS>, lds, once));
+  hipLaunchKernelGGL((k_dst_sine<T, ROWS, TO, TP, KS>), dim3((unsigned)tiles, (unsigned)groups), dim3(64 * waves),
+                     lds, st, a, fs ? *fs : DstScale<T>(), fs ? 1 : 0, mc);
   AHOC_HIP_TRY(hipGetLastError());
   return ST_OK;
 }
@@ -351,27 +445,40 @@ int sine_launch(const SineArgs<T>& a, long long tiles, int groups, int waves, hi
 // Tiles of 32 pencils share each gathered sine between two MFMAs, 16-pencil tiles double the
 // work-groups: 32 from two work-groups per CU upward.  A pass that writes elsewhere than it
 // reads splits its outputs over work-groups of four wavefronts (each re-reads the tile) while
-// whole pencils would give fewer than that.
+// whole pencils would give fewer than that, and their sums over the four wavefronts while even
+// those would leave compute units idle.
 template <typename T, bool ROWS>
-int sine_pass(SineArgs<T>& a, bool disjoint, hipStream_t st) {
+int sine_pass(SineArgs<T>& a, const DstScale<T>* fs, bool disjoint, hipStream_t st) {
   const int pairs = (a.N / 2 + 15) / 16;
   auto tiles = [&](int P) {
     a.ntile_inner = ROWS ? 1 : (a.inner + P - 1) / P;
     return ROWS ? (a.outer + P - 1) / P : a.outer * a.ntile_inner;
   };
-  if (disjoint && (pairs > 64 || (pairs > 4 && tiles(16) < 512))) {
-    if (pairs > 64) return sine_launch<T, ROWS, 2, 2>(a, tiles(32), (pairs + 15) / 16, 8, st);
-    return sine_launch<T, ROWS, 1, 1>(a, tiles(16), (pairs + 3) / 4, 4, st);
+  if (disjoint && pairs > 64) return sine_launch<T, ROWS, 2, 2>(a, fs, tiles(32), (pairs + 15) / 16, 8, st);
+  if (disjoint && pairs > 1 && tiles(16) < 512) {
+    if (a.N <= 1024 && tiles(16) * ((pairs + 3) / 4) < SINE_CHAIN_WGS)
+      return sine_launch<T, ROWS, 1, 1, 4>(a, fs, tiles(16), pairs, 4, st);
+    if (pairs > 4) return sine_launch<T, ROWS, 1, 1>(a, fs, tiles(16), (pairs + 3) / 4, 4, st);
   }
   if (pairs > 64) return ST_UNSUPPORTED;  // in place: one work-group holds every output of a tile
   const bool wide = tiles(32) >= 512;
   if (pairs <= 16)
-    return wide ? sine_launch<T, ROWS, 1, 2>(a, tiles(32), 1, pairs, st)
-                : sine_launch<T, ROWS, 1, 1>(a, tiles(16), 1, pairs, st);
+    return wide ? sine_launch<T, ROWS, 1, 2>(a, fs, tiles(32), 1, pairs, st)
+                : sine_launch<T, ROWS, 1, 1>(a, fs, tiles(16), 1, pairs, st);
   if (pairs <= 32)
-    return wide ? sine_launch<T, ROWS, 2, 2>(a, tiles(32), 1, (pairs + 1) / 2, st)
-                : sine_launch<T, ROWS, 2, 1>(a, tiles(16), 1, (pairs + 1) / 2, st);
-  return sine_launch<T, ROWS, 4, 1>(a, tiles(16), 1, (pairs + 3) / 4, st);
+    return wide ? sine_launch<T, ROWS, 2, 2>(a, fs, tiles(32), 1, (pairs + 1) / 2, st)
+                : sine_launch<T, ROWS, 2, 1>(a, fs, tiles(16), 1, (pairs + 1) / 2, st);
+  return sine_launch<T, ROWS, 4, 1>(a, fs, tiles(16), 1, (pairs + 3) / 4, st);
+}
+
+template <typename T, bool ROWS, int KS> int sine_jobs_launch(SineJobs<T>& s, int blocks, int nmax, hipStream_t st) {
+  s.mc = sine_mc(nmax, 16, KS > 1);
+  const size_t lds = sine_lds_bytes<T, ROWS, 1>(nmax, s.mc);
+  static std::once_flag once;
+  TRY_ST(sine_lds(&k_dst_sine_jobs<T, ROWS, KS>, lds, once));
+  hipLaunchKernelGGL((k_dst_sine_jobs<T, ROWS, KS>), dim3(blocks), dim3(256), lds, st, s);
+  AHOC_HIP_TRY(hipGetLastError());
+  return ST_OK;
 }
 
 }  // namespace
@@ -390,14 +497,14 @@ int dst_direct_pass(int N, const T* sn2, const T* in, T* out, long long outer, l
       SineArgs<T> s;
       s.in = src;
       s.out = dst;
-      s.sn2 = sn2;
+      s.sn = sn2;
       s.N = N;
+      s.half = 0;
       s.outer = outer;
       s.inner = inner;
       s.pitch = pitch;
-      s.scaled = f != nullptr;
-      if (f) s.fs = *f;
-      return inner == 1 ? sine_pass<T, true>(s, apart(src, dst), st) : sine_pass<T, false>(s, apart(src, dst), st);
+      return inner == 1 ? sine_pass<T, true>(s, f, apart(src, dst), st)
+                        : sine_pass<T, false>(s, f, apart(src, dst), st);
     };
     T* mid = tmp && apart(in, tmp) && apart(out, tmp) ? tmp : out;
     int rc = run(in, fused ? mid : out, fused);
@@ -433,6 +540,56 @@ int dst_direct_pass(int N, const T* sn2, const T* in, T* out, long long outer, l
   AHOC_HIP_TRY(hipGetLastError());
   return ST_OK;
 }
+
+// Flops of a pass as sine products, its pencils rounded up to the tile.
+double dst_sine_flops(int N, long long outer, long long inner) {
+  const double pencils = inner == 1 ? (double)((outer + 15) / 16 * 16) : (double)outer * ((inner + 15) / 16 * 16);
+  return pencils * N * N;
+}
+
+template <typename T> int dst_sine_jobs(const SineJob<T>* jobs, int count, hipStream_t st) {
+  if (count < 1) return ST_OK;
+  const bool rows = jobs[0].inner == 1;
+  for (int j0 = 0; j0 < count; j0 += SINE_JOBS_MAX) {
+    SineJobs<T> s;
+    int nmax = 0;
+    const int n = std::min(SINE_JOBS_MAX, count - j0);
+    long long tiles[SINE_JOBS_MAX] = {0}, wg = 0;
+    for (int j = 0; j < SINE_JOBS_MAX; ++j) {
+      const SineJob<T>& q = jobs[j0 + std::min(j, n - 1)];
+      SineArgs<T>& a = s.job[j];
+      a.in = q.in;
+      a.out = q.out;
+      a.sn = q.tb->sn;
+      a.N = q.tb->N;
+      a.half = q.tb->ppt != 0;
+      if (a.N > DST_SINE_JOBS_MAX_N) return ST_UNSUPPORTED;
+      a.outer = q.outer;
+      a.inner = q.inner;
+      a.pitch = q.pitch;
+      if (!a.sn || (q.inner == 1) != rows || (rows && q.pitch < a.N - 1)) return ST_INVALID;
+      a.ntile_inner = rows ? 1 : (q.inner + 15) / 16;
+      s.groups[j] = (a.N / 2 + 15) / 16;  // pairs
+      if (j < n) tiles[j] = rows ? (q.outer + 15) / 16 : q.outer * a.ntile_inner;
+      wg += tiles[j] * ((s.groups[j] + 3) / 4);
+      nmax = std::max(nmax, a.N);
+    }
+    const bool chain = wg < SINE_CHAIN_WGS;
+    long long blocks = 0;
+    for (int j = 0; j < SINE_JOBS_MAX; ++j) {
+      if (!chain) s.groups[j] = (s.groups[j] + 3) / 4;
+      blocks += tiles[j] * s.groups[j];
+      if (blocks > 0x7fffffffLL) return ST_UNSUPPORTED;
+      s.end[j] = (int)blocks;
+    }
+    if (blocks == 0) continue;
+    if (rows) TRY_ST(chain ? sine_jobs_launch<T, true, 4>(s, (int)blocks, nmax, st) : sine_jobs_launch<T, true, 1>(s, (int)blocks, nmax, st));
+    else TRY_ST(chain ? sine_jobs_launch<T, false, 4>(s, (int)blocks, nmax, st) : sine_jobs_launch<T, false, 1>(s, (int)blocks, nmax, st));
+  }
+  return ST_OK;
+}
+template int dst_sine_jobs<float>(const SineJob<float>*, int, hipStream_t);
+template int dst_sine_jobs<double>(const SineJob<double>*, int, hipStream_t);
 
 template int dst_direct_pass<float>(int, const float*, const float*, float*, long long, long long, long long,
                                     const DstScale<float>*, hipStream_t, float*);

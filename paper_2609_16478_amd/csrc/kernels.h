@@ -26,6 +26,9 @@ template <typename T> struct FaceLiftW {
 template <typename T>
 int face_lifts3(const Geom& g, const Weights& wv, const T* Q, const T* mq, T* Lx, T* Ly, T* Lz, T* Ux, T* Uy,
                 T* Uz, hipStream_t st);
+// 2-D: the same two sets (layouts of face_lift; ia nodal 1/alpha) in one pass over Q
+template <typename T>
+int face_lifts2(const Geom& g, const Weights& wv, const T* Q, const T* ia, T* Lx, T* Ly, T* Ux, T* Uy, hipStream_t st);
 // out[q] = s * nodal(boundary node of q): a nodal field in Q layout
 template <typename T>
 int nodal_to_q(const Geom& g, double s, const T* nodal, T* out, hipStream_t st);

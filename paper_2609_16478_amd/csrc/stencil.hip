@@ -372,6 +372,35 @@ __global__ void k_face_lift(Geom g, Weights w, const T* __restrict__ Q, T* __res
   }
 }
 
+// 2-D: the V-solve's lift layers (couplings w0 across the face and wt to its two neighbours
+// along it) and the U-solve's m1 Q_b / alpha_b, of every instance, in one pass over the lines
+// of both axes.  Rows [2][n_y'] of the x faces, then [2][px] of the y faces (padding zero).
+template <typename T>
+__global__ void k_face_lifts2(Geom g, T w0x, T w0y, T wt, T m1, const T* __restrict__ Q, const T* __restrict__ ia,
+                              T* __restrict__ Lx, T* __restrict__ Ly, T* __restrict__ Ux, T* __restrict__ Uy) {
+  const long long b_ = blockIdx.y;
+  Q += b_ * g.nq;
+  ia += b_ * g.nnodal;
+  const int nx = 2 * g.ni[1], tot = nx + 2 * g.px;
+  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < tot; e += gridDim.x * blockDim.x) {
+    const bool xf = e < nx;
+    const int r = xf ? e : e - nx, len = xf ? g.ni[1] : g.px, n = xf ? g.ni[1] : g.ni[0];
+    const int sd = r >= len, t = r - sd * len;  // face side, position along it (from 0)
+    T l = 0, u = 0;
+    if (t < n) {
+      const T* q = Q + g.face_off[(xf ? 0 : 2) + sd];
+      l = (xf ? w0x : w0y) * q[t];
+      if (t > 0) l += wt * q[t - 1];
+      if (t + 1 < n) l += wt * q[t + 1];
+      const int i = xf ? (sd ? g.n[0] : 0) : t + 1, j = xf ? t + 1 : (sd ? g.n[1] : 0);
+      u = m1 * q[t] * ia[(long long)j * g.nn[0] + i];
+    }
+    (xf ? Lx : Ly)[b_ * 2 * len + r] = l;
+    (xf ? Ux : Uy)[b_ * 2 * len + r] = u;
+  }
+}
+
+
 // Face layers of the U-solve's source M(V / alpha) in the homogeneous matvec: the 7-point M
 // couples an interior node next to a face only to the face node along the normal, where
 // V = Q, so the layer value is m1 Q_b / alpha_b (alpha_b from the nodal 1/alpha).  Layouts as
@@ -1255,6 +1284,15 @@ int face_lifts3(const Geom& g, const Weights& wv, const T* Q, const T* mq, T* Lx
 }
 
 template <typename T>
+int face_lifts2(const Geom& g, const Weights& wv, const T* Q, const T* ia, T* Lx, T* Ly, T* Ux, T* Uy, hipStream_t st) {
+  if (g.dim != 2) return ST_UNSUPPORTED;
+  hipLaunchKernelGGL((k_face_lifts2<T>), dim3(nblocks(2LL * (g.ni[1] + g.px)), g.nb), dim3(TPB), 0, st, g, (T)wv.cf[0],
+                     (T)wv.cf[1], (T)wv.ce[0], (T)wv.m1, Q, ia, Lx, Ly, Ux, Uy);
+  AHOC_HIP_TRY(hipGetLastError());
+  return ST_OK;
+}
+
+template <typename T>
 int nodal_to_q(const Geom& g, double s, const T* nodal, T* out, hipStream_t st) {
   LAUNCH_TDIM(k_nodal_to_q, T, dim3(nblocks(g.nq), g.nb), g, (T)s, nodal, out);
   return ST_OK;
@@ -1421,6 +1459,7 @@ int fill(long long n, double v, double* x, hipStream_t st) {
 #define INST_T(T)                                                                                  \
   template int face_lift<T>(const Geom&, const Weights&, const T*, T*, T*, T*, hipStream_t);       \
   template int face_lift_m<T>(const Geom&, const Weights&, const T*, const T*, T*, T*, T*, hipStream_t); \
+  template int face_lifts2<T>(const Geom&, const Weights&, const T*, const T*, T*, T*, T*, T*, hipStream_t);   \
   template int face_lifts3<T>(const Geom&, const Weights&, const T*, const T*, T*, T*, T*, T*, T*, T*,        \
                               hipStream_t);                                                        \
   template int nodal_to_q<T>(const Geom&, double, const T*, T*, hipStream_t);                      \

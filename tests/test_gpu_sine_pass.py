@@ -81,3 +81,26 @@ def test_poisson_mixed_length_axes(ah, n, prec):
         outs = [s.poisson(g), s.poisson(g), ah.poisson_noalloc(n, (0.0,) * len(n), hi, torch.from_numpy(g).cuda(), precision=p)]
     for w in outs:  # the bars of the other Poisson parity tests
         assert np.abs(w.cpu().numpy() - ref).max() <= (1e-12 if prec == "fp64" else 1e-5) * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("n", [(32, 32), (32, 1024), (1024, 64), (192, 256), (2048, 64), (32, 64, 96), (256, 32, 64),
+                               (64, 512, 128)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_face_transforms_match_fft_passes(ah, n, prec):
+    """The Schur operator and the preconditioner with all face transforms in one launch per pass
+    (split sums and not; 2048: beyond its lengths) against the one-tile FFT family, which transforms
+    each face pair by its own passes.  Bars of the Schur parity tests."""
+    hi = tuple(m / max(n) for m in n)
+    p = (W.manufactured("1 + 0.5*sin(2*pi*x)*cos(2*pi*y)", "sin(pi*x)**2*sin(pi*y)**2*exp(x)", n, (0.0,) * 2, hi)
+         if len(n) == 2 else W.manufactured(W.C3_ALPHA, "sin(pi*x)*sin(pi*y)*cos(pi*z)*exp(x)", n, (0.0,) * 3, hi))
+    tol = 1e-11 if prec == "fp64" else 1e-4
+    with ah.Solver(p, precision=ah.FP64 if prec == "fp64" else ah.MIXED) as s:
+        q = np.random.default_rng(4).standard_normal(s.nq)
+        got = [s.schur_apply(q), s.precond_apply(q)]
+        try:
+            ah.set_dst_variant(3)
+            ref = [s.schur_apply(q), s.precond_apply(q)]
+        finally:
+            ah.set_dst_variant(0)
+    for k, (a, b) in enumerate(zip(got, ref)):
+        assert float((a - b).abs().max()) <= (tol if k == 0 else 1e-11) * float(b.abs().max()), (n, k)
