@@ -884,7 +884,11 @@ template <typename T> DstGen<T> mspec_gen(const Geom& g, Prec<T>& P) {
 //   y forward; z forward with mu_M / lambda_L, the face-layer term and the z-face sums;
 //   x/y-face sums of the scaled spectrum; 2-D inverse transforms of the face sums; gather.
 // The volume is read and written in place in bufA.
-template <typename T> int matvec_mspec(ahoc_handle* h, Prec<T>& P, const T* Q, double* y, hipStream_t st) {
+// With `lines` (a 2-D grid that lines2d takes) the boundary steps run one work-group per
+// instance from the FP64 vector q (with pre, preconditioned first), and Q is not read.
+template <typename T>
+int matvec_mspec(ahoc_handle* h, Prec<T>& P, const T* Q, double* y, hipStream_t st, bool lines = false,
+                 const double* q = nullptr, bool pre = false) {
   const Geom& g = h->g;
   const bool d3 = g.dim == 3;
   const bool tiled = d3 && P.mq;
@@ -892,7 +896,33 @@ template <typename T> int matvec_mspec(ahoc_handle* h, Prec<T>& P, const T* Q, d
   // both face-layer sets and their spectra: 3-D in one tiled pass over Q, 2-D in one pass of
   // its own
   hipEvent_t el = tbegin(h, st);
-  if (tiled) {
+  const T* zq = Q;  // the operator's argument in T
+  if (lines) {
+    Front2d<T> f;
+    f.q = q;
+    f.z = sizeof(T) == 8 && pre ? h->zvec : nullptr;
+    f.zt = sizeof(T) == 8 ? nullptr : P.qT;
+    f.pc = pre ? h->pc : nullptr;
+    f.qc = pre ? h->qc : nullptr;
+    f.twd = pre ? h->ptb[0].tw : nullptr;
+    f.snd = pre ? h->ptb[0].sn : nullptr;
+    f.tw = P.tb[0].tw;
+    f.sn = P.tb[0].sn;
+    f.ia = P.ia;
+    f.nnodal = g.nnodal;
+    f.w0x = (T)h->wv.cf[0];
+    f.w0y = (T)h->wv.cf[1];
+    f.wt = (T)h->wv.ce[0];
+    f.m1 = (T)h->w.m1;
+    f.Fx = P.Fx;
+    f.Fy = P.Fy;
+    f.Ux = P.Ux;
+    f.Uy = P.Uy;
+    f.px = g.px;
+    TRY(front2d<T>(g.n[0], f, g.nb, st));
+    if constexpr (sizeof(T) == 8) zq = pre ? h->zvec : q;
+    else zq = P.qT;
+  } else if (tiled) {
     TRY(face_lifts3<T>(g, h->wv, Q, P.mq, P.Fx, P.Fy, P.Fz, P.Ux, P.Uy, P.Uz, st));
   } else if (!d3) {
     TRY(face_lifts2<T>(g, h->wv, Q, P.ia, ft ? P.ft[0][0] : P.Fx, ft ? P.ft[0][1] : P.Fy, ft ? P.ft[1][0] : P.Ux,
@@ -901,9 +931,9 @@ template <typename T> int matvec_mspec(ahoc_handle* h, Prec<T>& P, const T* Q, d
     TRY(face_lift<T>(g, h->wv, Q, P.Fx, P.Fy, P.Fz, st));
     TRY(face_lift_m<T>(g, h->w, Q, P.ia, P.Ux, P.Uy, P.Uz, st));
   }
-  TRY(face_dst2<T>(h, P, 3, st, ft));
+  if (!lines) TRY(face_dst2<T>(h, P, 3, st, ft));
   tend(h, AHOC_K_LIFT, el, (double)TQ(g) * 7.0 * sizeof(T), st);
-  TRY(vsolve_spec<T>(h, P, Q, st, true, true));
+  TRY(vsolve_spec<T>(h, P, zq, st, true, true));
   T* buf = P.bufA;
   const double vol = (double)g.nint * g.nb * sizeof(T);
   const long long rows = d3 ? (long long)g.ni[1] * g.ni[2] : (long long)g.nb * g.ni[1];
@@ -942,7 +972,13 @@ template <typename T> int matvec_mspec(ahoc_handle* h, Prec<T>& P, const T* Q, d
                        2LL * g.ni[1], 1, st));
   tend(h, AHOC_K_FACE_REDUCE, er, vol, st);
   hipEvent_t ef = tbegin(h, st);
-  TRY(gather_sums<T>(h, P, Q, nullptr, y, st));
+  if (lines)
+    TRY(back2d<T>(g.n[0],
+                  {P.Fx, P.Fy, zq, P.af, P.tb[0].tw, P.tb[0].sn, y, (T)(1.0 / (g.h[0] * g.h[0])),
+                   (T)(1.0 / (g.h[1] * g.h[1])), g.px},
+                  g.nb, st));
+  else
+    TRY(gather_sums<T>(h, P, Q, nullptr, y, st));
   tend(h, AHOC_K_GATHER, ef, (double)TQ(g) * (5 * sizeof(T) + sizeof(double)), st);
   return ST_OK;
 }
@@ -1123,10 +1159,23 @@ template <typename T> int tri_gather(ahoc_handle* h, Prec<T>& P, const T* Q, con
   return ST_OK;
 }
 
-// y = S_h q  (homogeneous Lemma-1 form)
-template <typename T> int matvec(ahoc_handle* h, Prec<T>& P, const double* q, double* y, hipStream_t st) {
+// Whether the operator's boundary steps run one work-group per instance: square 2-D grids of
+// the specialised lengths up to 1024 (the longest whose lines fit in LDS).
+template <typename T> bool lines_ok(const ahoc_handle* h, const Prec<T>& P) {
+  const Geom& g = h->g;
+  return g.dim == 2 && g.n[0] == g.n[1] && P.mspec && !h->tri && face_jobs_on() && lines2d_supported(g.n[0]);
+}
+
+// y = S_h q  (homogeneous Lemma-1 form); with pre, y = S_h P^-1 q where lines_ok
+template <typename T>
+int matvec(ahoc_handle* h, Prec<T>& P, const double* q, double* y, hipStream_t st, bool pre = false) {
   int rc = 0;
   hipEvent_t e = tbegin(h, st);
+  if (lines_ok(h, P)) {
+    TRY(matvec_mspec<T>(h, P, nullptr, y, st, true, q, pre));
+    tend(h, AHOC_K_MATVEC, e, (double)sizeof(T) * (6.0 * h->g.nint + h->g.nnodal) * h->g.nb, st);
+    return ST_OK;
+  }
   const T* qT = q_in<T>(h, P, q, st, &rc);
   TRY(rc);
   if (h->tri) {
@@ -1294,11 +1343,11 @@ template <typename T>
 int apply_op(ahoc_handle* h, Prec<T>& P, bool pre, const double* v, double* w, hipStream_t st) {
   const int pi = sizeof(T) == 8 ? 1 : 0;
   auto body = [&](const double* in, double* out) -> int {
-    if (pre) {
+    if (pre && !lines_ok(h, P)) {
       TRY(precond_apply(h, in, h->zvec, st));
       return matvec<T>(h, P, h->zvec, out, st);
     }
-    return matvec<T>(h, P, in, out, st);
+    return matvec<T>(h, P, in, out, st, pre);
   };
   const bool graph = h->opt.use_graph && h->gin && !h->prof && !h->opg_failed[pi];
   if (graph && !h->opg[pi] && h->opg_uses[pi]++ >= 1) {

@@ -92,6 +92,37 @@ template <typename Tx>
 int absmax_partial(long long n, const Tx* x, double* bmax, int nb, hipStream_t st);
 int fill(long long n, double v, double* x, hipStream_t st);
 
+// faces2d.hip ----------------------------------------------------------------------------
+// The boundary lines of a 2-D operator application on a square grid of one of the specialised
+// lengths up to 1024 (lines2d_supported), one work-group per instance: everything before the
+// V-solve's spectrum is generated, and everything after the face sums (see the file).
+template <typename T> struct Front2d {
+  const double* q;        // nb x 4 (N-1)
+  double* z;              // P^-1 q, or null
+  T* zt;                  // the same in T, or null
+  const double *pc, *qc;  // mode blocks (Q layout), null without the preconditioner
+  const cx<double>* twd;
+  const double* snd;
+  const cx<T>* tw;
+  const T* sn;
+  const T* ia;            // nodal 1/alpha
+  long long nnodal;
+  T w0x, w0y, wt, m1;
+  T *Fx, *Fy, *Ux, *Uy;
+  int px;
+};
+template <typename T> struct Back2d {
+  const T *Fx, *Fy, *z, *af;
+  const cx<T>* tw;
+  const T* sn;
+  double* R;
+  T ihx2, ihy2;
+  int px;
+};
+bool lines2d_supported(int N);
+template <typename T> int front2d(int N, const Front2d<T>& a, int nb, hipStream_t st);
+template <typename T> int back2d(int N, const Back2d<T>& a, int nb, hipStream_t st);
+
 // krylov.hip --------------------------------------------------------------------------
 // partial dot products of nvec basis vectors (row stride ld) with w: part[v * nb + b]
 int mdot_partial(const double* V, long long ld, int nvec, const double* w, long long n, int ns, double* part,
