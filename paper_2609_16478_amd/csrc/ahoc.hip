@@ -166,6 +166,15 @@ struct ahoc_handle {
   std::vector<void*> ptab_host;
   std::vector<void*> allocs;
   size_t dev_bytes = 0;      // device memory held by allocs
+  // small arrays are cut from blocks of ARENA_BYTES (a setup makes some sixty of them, each a
+  // call into the caller's allocator otherwise)
+  char* arena = nullptr;
+  size_t arena_left = 0;
+  // setup: quarter-wave sines per axis, and the host images of uploads until the stream is
+  // waited for
+  std::vector<ahoc::SineBase> base;
+  int base_of[3] = {0, 0, 0};
+  ahoc::HostImages images;
   // optional per-kernel-class timing with HIP events on the work stream
   bool prof = false;
   std::vector<hipEvent_t> evpool;
@@ -180,8 +189,24 @@ struct ahoc_handle {
 namespace ahoc {
 namespace {
 
+constexpr size_t ARENA_BYTES = 512 << 10, ARENA_MOST = 64 << 10;
 int dalloc(ahoc_handle* h, void** p, size_t bytes) {
   if (bytes == 0) bytes = 8;
+  if (bytes <= ARENA_MOST) {
+    bytes = (bytes + 255) & ~(size_t)255;
+    if (h->arena_left < bytes) {
+      void* a = nullptr;
+      TRY_ST(dev_alloc(h->al, &a, ARENA_BYTES));
+      h->allocs.push_back(a);
+      h->dev_bytes += ARENA_BYTES;
+      h->arena = static_cast<char*>(a);
+      h->arena_left = ARENA_BYTES;
+    }
+    *p = h->arena;
+    h->arena += bytes;
+    h->arena_left -= bytes;
+    return ST_OK;
+  }
   TRY_ST(dev_alloc(h->al, p, bytes));
   h->allocs.push_back(*p);
   h->dev_bytes += bytes;
@@ -251,6 +276,17 @@ template <typename T> int alloc_int(ahoc_handle* h, T** p, hipStream_t st) {
   int rc = alloc_t(h, p, TA(h->g));
   if (rc) return rc;
   AHOC_HIP_TRY(hipMemsetAsync(*p, 0, sizeof(T) * (size_t)TA(h->g), st));
+  return ST_OK;
+}
+
+// Device copy of a host array, uploaded on `st`; the host image stays with the handle until the
+// end of its setup.
+template <typename T> int upload(ahoc_handle* h, T** p, const std::vector<T>& v, hipStream_t st) {
+  TRY(alloc_t(h, p, (long long)v.size()));
+  std::vector<char> img(sizeof(T) * v.size());
+  std::memcpy(img.data(), v.data(), img.size());
+  AHOC_HIP_TRY(hipMemcpyAsync(*p, img.data(), img.size(), hipMemcpyHostToDevice, st));
+  h->images.push_back(std::move(img));
   return ST_OK;
 }
 
@@ -361,41 +397,43 @@ bool face_jobs_on() { return dst_get_variant() == 0 || dst_get_variant() == 5; }
 
 template <typename T> int prec_init(ahoc_handle* h, Prec<T>& P, int tile_opt, hipStream_t st) {
   const Geom& g = h->g;
+  std::vector<T> pt;
   for (int a = 0; a < g.dim; ++a) {
-    TRY(dst_tables_init<T>(P.tb[a], g.n[a], st, &h->al));
+    const SineBase& sb = h->base[h->base_of[a]];
+    TRY(dst_tables_init<T>(P.tb[a], g.n[a], st, &h->al, &sb, &h->images));
     P.tile[a] = tile_opt > 0 ? tile_opt : 0;  // 0: each kernel picks its default tile
-    // eigenvalues of the 1-D second difference on sine mode k: -(4/h^2) sin^2(k pi / (2N))
-    std::vector<T> s(g.ni[a]);
-    const long double pi = 3.141592653589793238462643383279502884L;
-    for (int k = 1; k <= g.ni[a]; ++k) {
-      const long double sv = sinl(pi * k / (2.0L * g.n[a]));
-      s[k - 1] = (T)(-4.0L * sv * sv / ((long double)g.h[a] * g.h[a]));
-    }
-    TRY(alloc_t(h, &P.s[a], g.ni[a]));
-    AHOC_HIP_TRY(hipMemcpyAsync(P.s[a], s.data(), sizeof(T) * g.ni[a], hipMemcpyHostToDevice, st));
-    AHOC_HIP_TRY(hipStreamSynchronize(st));
-    // 6 U_1 - 3/2 U_2 + 2/9 U_3 of a sine mode k, for the low face (nodes 1,2,3) and the
-    // high face (nodes N-1, N-2, N-3, where sin(pi k (N-m)/N) = (-1)^(k+1) sin(pi k m/N))
-    std::vector<T> wv(2 * g.ni[a]);
-    for (int k = 1; k <= g.ni[a]; ++k) {
+    // one block: s, wf, wl (each from a 256-byte boundary)
+    const int n = g.ni[a];
+    const size_t al = 256 / sizeof(T), o_wf = (n + al - 1) / al * al, o_wl = o_wf + (2 * (size_t)n + al - 1) / al * al;
+    std::vector<T> v(o_wl + 2 * (size_t)n);
+    for (int k = 1; k <= n; ++k) {
+      // eigenvalue of the 1-D second difference on sine mode k: -(4/h^2) sin^2(k pi / (2N))
+      const long double sv = sb.at(k);
+      v[k - 1] = (T)(-4.0L * sv * sv / ((long double)g.h[a] * g.h[a]));
+      // 6 U_1 - 3/2 U_2 + 2/9 U_3 of the mode, for the low face (nodes 1,2,3) and the high face
+      // (nodes N-1, N-2, N-3, where sin(pi k (N-m)/N) = (-1)^(k+1) sin(pi k m/N))
       long double acc = 0;
-      for (int m = 1; m <= 3; ++m) acc += (long double)h->w.os[m] * sinl(pi * k * m / (long double)g.n[a]);
-      wv[k - 1] = (T)acc;
-      wv[g.ni[a] + k - 1] = (T)((k % 2 == 1) ? acc : -acc);
+      for (int m = 1; m <= 3; ++m) acc += (long double)h->w.os[m] * sb.at(2LL * k * m);
+      v[o_wf + k - 1] = (T)acc;
+      v[o_wf + n + k - 1] = (T)((k % 2 == 1) ? acc : -acc);
+      // its sine at the interior layer next to the low face (node 1) and the high face (node
+      // N-1): the normal factor of a face layer's spectrum
+      const long double ls = sb.at(2LL * k);
+      v[o_wl + k - 1] = (T)ls;
+      v[o_wl + n + k - 1] = (T)((k % 2 == 1) ? ls : -ls);
     }
-    TRY(alloc_t(h, &P.wf[a], 2 * g.ni[a]));
-    AHOC_HIP_TRY(hipMemcpyAsync(P.wf[a], wv.data(), sizeof(T) * 2 * g.ni[a], hipMemcpyHostToDevice, st));
-    AHOC_HIP_TRY(hipStreamSynchronize(st));
-    // sine of mode k at the interior layer next to the low face (node 1) and the high face
-    // (node N-1): the normal factor of a face layer's spectrum
-    for (int k = 1; k <= g.ni[a]; ++k) {
-      const long double sv = sinl(pi * k / (long double)g.n[a]);
-      wv[k - 1] = (T)sv;
-      wv[g.ni[a] + k - 1] = (T)((k % 2 == 1) ? sv : -sv);
+    TRY(upload(h, &P.s[a], v, st));
+    P.wf[a] = P.s[a] + o_wf;
+    P.wl[a] = P.s[a] + o_wl;
+    if (a == g.dim - 1) {  // 4-tuples of the slowest axis (allocated with the spectral arrays)
+      pt.resize(4 * (size_t)n);
+      for (int k = 0; k < n; ++k) {
+        pt[4 * k] = v[k];
+        pt[4 * k + 1] = v[o_wl + k];
+        pt[4 * k + 2] = v[o_wf + k];
+        pt[4 * k + 3] = v[o_wf + n + k];
+      }
     }
-    TRY(alloc_t(h, &P.wl[a], 2 * g.ni[a]));
-    AHOC_HIP_TRY(hipMemcpyAsync(P.wl[a], wv.data(), sizeof(T) * 2 * g.ni[a], hipMemcpyHostToDevice, st));
-    AHOC_HIP_TRY(hipStreamSynchronize(st));
   }
   if (g.dim == 3) {
     TRY(alloc_t(h, &P.Fx, 2LL * g.ni[1] * g.ni[2]));
@@ -425,21 +463,7 @@ template <typename T> int prec_init(ahoc_handle* h, Prec<T>& P, int tile_opt, hi
     }
     // (s, layer sine, face weight low, high) per position of the slowest axis, from the
     // tables above
-    const int nt = g.ni[t];
-    std::vector<T> hs(nt), hl(2 * nt), hw(2 * nt), pt(4 * (size_t)nt);
-    AHOC_HIP_TRY(hipMemcpyAsync(hs.data(), P.s[t], sizeof(T) * nt, hipMemcpyDeviceToHost, st));
-    AHOC_HIP_TRY(hipMemcpyAsync(hl.data(), P.wl[t], sizeof(T) * 2 * nt, hipMemcpyDeviceToHost, st));
-    AHOC_HIP_TRY(hipMemcpyAsync(hw.data(), P.wf[t], sizeof(T) * 2 * nt, hipMemcpyDeviceToHost, st));
-    AHOC_HIP_TRY(hipStreamSynchronize(st));
-    for (int k = 0; k < nt; ++k) {
-      pt[4 * k] = hs[k];
-      pt[4 * k + 1] = hl[k];
-      pt[4 * k + 2] = hw[k];
-      pt[4 * k + 3] = hw[nt + k];
-    }
-    TRY(alloc_t(h, &P.ptab, 4LL * nt));
-    AHOC_HIP_TRY(hipMemcpyAsync(P.ptab, pt.data(), sizeof(T) * 4 * nt, hipMemcpyHostToDevice, st));
-    AHOC_HIP_TRY(hipStreamSynchronize(st));
+    TRY(upload(h, &P.ptab, pt, st));
     if (face_jobs_pay(g)) {
       const long long sx = g.dim == 3 ? 2LL * g.ni[1] * g.ni[2] : 2LL * g.nb * g.ni[1];
       const long long sy[2] = {g.dim == 3 ? 2LL * g.px * g.ni[2] : 2LL * g.nb * g.px,
@@ -1035,28 +1059,26 @@ template <typename T> int usolve_spec(ahoc_handle* h, Prec<T>& P, const T* Q, co
 int precond_init(ahoc_handle* h, hipStream_t st) {
   const Geom& g = h->g;
   std::vector<double*> tabs(12, nullptr);
-  const long double pi = 3.141592653589793238462643383279502884L;
   for (int a = 0; a < g.dim; ++a) {
     const int L = g.ni[a];
+    const SineBase& sb = h->base[h->base_of[a]];
     std::vector<double> tv(4 * (size_t)L);
     for (int k = 1; k <= L; ++k) {
-      const long double sh = sinl(pi * k / (2.0L * g.n[a]));
+      const long double sh = sb.at(k);
       tv[k - 1] = (double)(-4.0L * sh * sh / ((long double)g.h[a] * g.h[a]));
-      tv[L + k - 1] = (double)cosl(pi * k / (long double)g.n[a]);
-      tv[2 * L + k - 1] = (double)sinl(pi * k / (long double)g.n[a]);
+      tv[L + k - 1] = (double)sb.at(2LL * k + g.n[a]);
+      tv[2 * L + k - 1] = (double)sb.at(2LL * k);
       long double acc = 0;
       if (h->tri) {  // the triharmonic q-row's fourth-derivative combination of U_1..U_4
         const long double a4[4] = {-104.0L, 57.0L / 2.0L, -56.0L / 9.0L, 11.0L / 16.0L};
-        for (int m = 1; m <= 4; ++m) acc += a4[m - 1] * sinl(pi * k * m / (long double)g.n[a]);
+        for (int m = 1; m <= 4; ++m) acc += a4[m - 1] * sb.at(2LL * k * m);
       } else {
-        for (int m = 1; m <= 3; ++m) acc += (long double)h->w.os[m] * sinl(pi * k * m / (long double)g.n[a]);
+        for (int m = 1; m <= 3; ++m) acc += (long double)h->w.os[m] * sb.at(2LL * k * m);
       }
       tv[3 * L + k - 1] = (double)acc;
     }
     double* d = nullptr;
-    TRY(alloc_t(h, &d, 4LL * L));
-    AHOC_HIP_TRY(hipMemcpyAsync(d, tv.data(), sizeof(double) * tv.size(), hipMemcpyHostToDevice, st));
-    AHOC_HIP_TRY(hipStreamSynchronize(st));
+    TRY(upload(h, &d, tv, st));
     for (int r = 0; r < 4; ++r) tabs[4 * a + r] = d + (long long)r * L;
   }
   TRY(alloc_t(h, &h->pc, g.nq));
@@ -1067,9 +1089,9 @@ int precond_init(ahoc_handle* h, hipStream_t st) {
     h->ptb_own = false;
   } else {
     h->ptb_own = true;
-    for (int a = 0; a < g.dim; ++a) TRY(dst_tables_init<double>(h->ptb[a], g.n[a], st, &h->al));
+    for (int a = 0; a < g.dim; ++a)
+      TRY(dst_tables_init<double>(h->ptb[a], g.n[a], st, &h->al, &h->base[h->base_of[a]], &h->images));
   }
-  AHOC_HIP_TRY(hipStreamSynchronize(st));
   return ST_OK;
 }
 
@@ -1558,6 +1580,15 @@ int setup_impl(const ahoc_problem* pbs, int count, hipStream_t st, ahoc_handle* 
   g.nb = count;
   make_weights(g, h->w);
   h->wv = h->w;
+  for (int a = 0; a < g.dim; ++a) {
+    h->base_of[a] = -1;
+    for (int b = 0; b < a; ++b)
+      if (g.n[b] == g.n[a]) h->base_of[a] = h->base_of[b];
+    if (h->base_of[a] < 0) {
+      h->base_of[a] = (int)h->base.size();
+      h->base.emplace_back(g.n[a]);
+    }
+  }
   h->m = h->opt.restart;
   h->tri = pb->equation == AHOC_TRIHARMONIC;
   if (h->tri) {
@@ -1746,12 +1777,16 @@ int setup_impl(const ahoc_problem* pbs, int count, hipStream_t st, ahoc_handle* 
   if (nb > 1) TRY(alloc_t(h, &h->ubuf, TN(g)));
   AHOC_HIP_TRY(hipMemsetAsync(h->H, 0, sizeof(double) * nb * (m + 1) * m, st));
   const size_t npin = (size_t)std::max<long long>(8, 2 * nb);
-  AHOC_HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&h->pinned), sizeof(double) * npin, hipHostMallocDefault));
-  AHOC_HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&h->pinned_i), sizeof(int) * npin, hipHostMallocDefault));
-  AHOC_HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&h->pinned_s), sizeof(int) * 4 * nb, hipHostMallocDefault));
-  AHOC_HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&h->pinned_b), sizeof(double) * nb, hipHostMallocDefault));
-  AHOC_HIP_TRY(hipStreamSynchronize(st));
+  // one block of pinned host memory: pinned, pinned_b, pinned_i, pinned_s
+  AHOC_HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&h->pinned),
+                             sizeof(double) * (npin + nb) + sizeof(int) * (npin + 4 * nb), hipHostMallocDefault));
+  h->pinned_b = h->pinned + npin;
+  h->pinned_i = reinterpret_cast<int*>(h->pinned_b + nb);
+  h->pinned_s = h->pinned_i + npin;
   if (h->opt.precond) TRY(precond_init(h, st));
+  AHOC_HIP_TRY(hipStreamSynchronize(st));
+  h->images.clear();
+  h->base.clear();
   return ST_OK;
 }
 
@@ -1811,9 +1846,6 @@ void ahoc_destroy(ahoc_handle* h) {
   for (hipEvent_t e : h->evpool) (void)hipEventDestroy(e);
   if (h->done_ev) (void)hipEventDestroy(h->done_ev);
   if (h->pinned) (void)hipHostFree(h->pinned);
-  if (h->pinned_i) (void)hipHostFree(h->pinned_i);
-  if (h->pinned_s) (void)hipHostFree(h->pinned_s);
-  if (h->pinned_b) (void)hipHostFree(h->pinned_b);
   if (h->bpin) (void)hipHostFree(h->bpin);
   delete h;
 }
@@ -1921,6 +1953,7 @@ static ahoc_status setup_n(const ahoc_problem* pbs, int count, const ahoc_option
   }
   const int rc = ahoc::setup_impl(pbs, count, (hipStream_t)stream, h);
   if (rc) {
+    (void)hipStreamSynchronize((hipStream_t)stream);  // uploads from the handle's host images
     ahoc_destroy(h);
     return (ahoc_status)rc;
   }

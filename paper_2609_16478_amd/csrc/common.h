@@ -11,6 +11,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 
 namespace ahoc {
 
@@ -85,9 +86,34 @@ void dev_free(const DevAlloc& a, void* p);
 // DST-I passes (dst.hip)
 // ------------------------------------------------------------------------------------
 
+// sin(pi j / (2N)) for any integer j, from a quarter wave evaluated once in extended precision:
+// every table of a grid axis is made of these (sines and cosines of multiples of pi / (2N)), so
+// a setup evaluates N sines per length instead of some thirty N.
+class SineBase {
+ public:
+  explicit SineBase(int N);
+  int n() const { return N_; }
+  long double at(long long j) const {
+    const long long period = 4LL * N_;
+    j %= period;
+    if (j < 0) j += period;
+    const bool neg = j >= 2LL * N_;
+    if (neg) j -= 2LL * N_;
+    const long double v = q_[(size_t)(j > N_ ? 2LL * N_ - j : j)];
+    return neg ? -v : v;
+  }
+
+ private:
+  int N_;
+  std::vector<long double> q_;  // j = 0..N
+};
+// Host images of uploads in flight: kept until the stream has been waited for.
+using HostImages = std::vector<std::vector<char>>;
+
 // Precomputed tables for one transform length N (pencil length N-1).
 template <typename T> struct DstTables {
-  DevAlloc al;        // provider of tw, sn, S (released through it)
+  DevAlloc al;        // provider of mem (released through it)
+  void* mem = nullptr;  // one block behind tw, sn and S (null where they are the caller's)
   int N = 0;
   int ppt = 0;        // points per thread (compile-time variant selector)
   int nrad = 0;
@@ -273,7 +299,7 @@ template <typename T> bool dst_pipe_mpass_ok(int N, long long inner, long long n
 constexpr int DST_GEMM_MAX_N = 128;
 bool dst_gemm_supported(int N);
 int dst_gemm_hp(int N);
-template <typename T> int dst_gemm_table(T** S, int N, hipStream_t st, const DevAlloc& al);
+template <typename T> std::vector<T> dst_gemm_table(const SineBase& b);
 template <typename T>
 int dst_gemm_pass(const T* S, int N, const T* in, T* out, long long outer, long long inner, long long pitch,
                   hipStream_t st);
@@ -293,10 +319,12 @@ int copy_bandwidth(int pattern, const float* in, float* out, int nx, int ny, int
 void dst_set_variant(int v);
 int dst_get_variant();
 
-// Tables for length N, uploaded on stream st (which is synchronised before returning),
-// allocated through `al` (null: hipMalloc).
+// Tables for length N, uploaded on stream st, allocated through `al` (null: hipMalloc).  With
+// `images` the upload's host image goes there and the caller waits for the stream before it
+// drops it; else the stream is synchronised before returning.
 template <typename T> int dst_tables_init(DstTables<T>& tb, int N, hipStream_t st = nullptr,
-                                          const DevAlloc* al = nullptr);
+                                          const DevAlloc* al = nullptr, const SineBase* base = nullptr,
+                                          HostImages* images = nullptr);
 template <typename T> void dst_tables_free(DstTables<T>& tb);
 // Only the radix plan of an FFT length (N, ppt, nrad, rad): no device memory.
 template <typename T> int dst_plan_only(DstTables<T>& tb, int N);

@@ -28,6 +28,7 @@
 
 #include <cmath>
 #include <cstdio>
+#include <cstring>
 #include <mutex>
 #include <vector>
 
@@ -482,51 +483,59 @@ int dst_default_tile(int N, int elem_bytes) {
   return nseq;
 }
 
-template <typename T> int dst_tables_init(DstTables<T>& tb, int N, hipStream_t st, const DevAlloc* al) {
+SineBase::SineBase(int N) : N_(N), q_((size_t)N + 1) {
+  const long double pi = 3.141592653589793238462643383279502884L;
+  for (int j = 0; j <= N; ++j) q_[j] = sinl(pi * (long double)j / (2.0L * N));
+}
+
+template <typename T>
+int dst_tables_init(DstTables<T>& tb, int N, hipStream_t st, const DevAlloc* al, const SineBase* base,
+                    HostImages* images) {
   dst_tables_free(tb);
   if (!dst_supported(N)) return ST_UNSUPPORTED;
   tb.al = al ? *al : DevAlloc();
+  SineBase own(base ? 1 : N);
+  const SineBase& sb = base ? *base : own;
   const int ppt = dst_ppt(N);
-  const long double pi = 3.141592653589793238462643383279502884L;
   tb.N = N;
   tb.ppt = ppt;
+  tb.nrad = 0;
+  std::vector<cx<T>> tw;
+  std::vector<T> sn, S;
   if (!ppt) {
-    // no FFT plan: the direct pass reads one full period of sin(pi j / N); the integer
-    // argument is reduced to [0, N] by the symmetries of the sine before evaluation
-    std::vector<T> sn2(2 * (size_t)N);
-    for (int j = 0; j < 2 * N; ++j) {
-      const int r = j <= N ? j : 2 * N - j;
-      const long double v = sinl(pi * (long double)(r <= N / 2 ? r : N - r) / (long double)N);
-      sn2[j] = (T)(j <= N ? v : -v);
-    }
-    tb.nrad = 0;
-    TRY_ST(dev_alloc(tb.al, reinterpret_cast<void**>(&tb.sn), sizeof(T) * 2 * (size_t)N));
-    AHOC_HIP_TRY(hipMemcpyAsync(tb.sn, sn2.data(), sizeof(T) * 2 * (size_t)N, hipMemcpyHostToDevice, st));
-    AHOC_HIP_TRY(hipStreamSynchronize(st));
+    // no FFT plan: the sine products read one full period of sin(pi j / N)
+    sn.resize(2 * (size_t)N);
+    for (int j = 0; j < 2 * N; ++j) sn[j] = (T)sb.at(2LL * j);
   } else {
     Plan pl;
     make_plan(N, ppt, pl);
     tb.nrad = pl.nrad;
     for (int i = 0; i < pl.nrad; ++i) tb.rad[i] = pl.rad[i];
-    std::vector<cx<T>> tw(N);
-    std::vector<T> sn(N / 2 + 1);
+    tw.resize(N);
+    sn.resize(N / 2 + 1);
     for (int k = 0; k < N; ++k) {
-      const long double ang = 2.0L * pi * (long double)k / (long double)N;
-      tw[k].x = (T)cosl(ang);
-      tw[k].y = (T)(-sinl(ang));
+      tw[k].x = (T)sb.at(4LL * k + N);  // cos(2 pi k / N)
+      tw[k].y = (T)(-sb.at(4LL * k));
     }
-    for (int m = 0; m <= N / 2; ++m) sn[m] = (T)sinl(pi * (long double)m / (long double)N);
-    TRY_ST(dev_alloc(tb.al, reinterpret_cast<void**>(&tb.tw), sizeof(cx<T>) * N));
-    TRY_ST(dev_alloc(tb.al, reinterpret_cast<void**>(&tb.sn), sizeof(T) * (N / 2 + 1)));
-    // stream-ordered uploads (no legacy-stream operation while other streams may be capturing)
-    AHOC_HIP_TRY(hipMemcpyAsync(tb.tw, tw.data(), sizeof(cx<T>) * N, hipMemcpyHostToDevice, st));
-    AHOC_HIP_TRY(hipMemcpyAsync(tb.sn, sn.data(), sizeof(T) * (N / 2 + 1), hipMemcpyHostToDevice, st));
-    AHOC_HIP_TRY(hipStreamSynchronize(st));
+    for (int m = 0; m <= N / 2; ++m) sn[m] = (T)sb.at(2LL * m);
   }
-  if (dst_gemm_supported(N)) {
-    const int rc = dst_gemm_table<T>(&tb.S, N, st, tb.al);
-    if (rc != ST_OK) return rc;
-  }
+  if (dst_gemm_supported(N)) S = dst_gemm_table<T>(sb);
+  // one block and one stream-ordered upload (no legacy-stream operation while other streams
+  // may be capturing)
+  auto up256 = [](size_t b) { return (b + 255) & ~(size_t)255; };
+  const size_t o_sn = up256(sizeof(cx<T>) * tw.size()), o_S = o_sn + up256(sizeof(T) * sn.size());
+  std::vector<char> img(o_S + sizeof(T) * S.size());
+  if (!tw.empty()) std::memcpy(img.data(), tw.data(), sizeof(cx<T>) * tw.size());
+  std::memcpy(img.data() + o_sn, sn.data(), sizeof(T) * sn.size());
+  if (!S.empty()) std::memcpy(img.data() + o_S, S.data(), sizeof(T) * S.size());
+  TRY_ST(dev_alloc(tb.al, &tb.mem, img.size()));
+  char* m = static_cast<char*>(tb.mem);
+  if (!tw.empty()) tb.tw = reinterpret_cast<cx<T>*>(m);
+  tb.sn = reinterpret_cast<T*>(m + o_sn);
+  if (!S.empty()) tb.S = reinterpret_cast<T*>(m + o_S);
+  AHOC_HIP_TRY(hipMemcpyAsync(m, img.data(), img.size(), hipMemcpyHostToDevice, st));
+  if (images) images->push_back(std::move(img));
+  else AHOC_HIP_TRY(hipStreamSynchronize(st));
   return ST_OK;
 }
 
@@ -543,9 +552,8 @@ template <typename T> int dst_plan_only(DstTables<T>& tb, int N) {
 }
 
 template <typename T> void dst_tables_free(DstTables<T>& tb) {
-  dev_free(tb.al, tb.tw);
-  dev_free(tb.al, tb.sn);
-  dev_free(tb.al, tb.S);
+  dev_free(tb.al, tb.mem);
+  tb.mem = nullptr;
   tb.tw = nullptr;
   tb.sn = nullptr;
   tb.S = nullptr;
@@ -629,8 +637,9 @@ int dst_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long 
   }
 }
 
-template int dst_tables_init<float>(DstTables<float>&, int, hipStream_t, const DevAlloc*);
-template int dst_tables_init<double>(DstTables<double>&, int, hipStream_t, const DevAlloc*);
+template int dst_tables_init<float>(DstTables<float>&, int, hipStream_t, const DevAlloc*, const SineBase*, HostImages*);
+template int dst_tables_init<double>(DstTables<double>&, int, hipStream_t, const DevAlloc*, const SineBase*,
+                                     HostImages*);
 template int dst_plan_only<float>(DstTables<float>&, int);
 template int dst_plan_only<double>(DstTables<double>&, int);
 template void dst_tables_free<float>(DstTables<float>&);

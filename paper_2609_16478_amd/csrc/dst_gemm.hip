@@ -212,26 +212,15 @@ bool dst_gemm_supported(int N) { return N >= 4 && N <= DST_GEMM_MAX_N && N % 2 =
 // padded half length HP = 16 ceil(N / 32)
 int dst_gemm_hp(int N) { return dst_gemm_supported(N) ? (N / 2 + 15) / 16 * 16 : 0; }
 
-template <typename T> int dst_gemm_table(T** S, int N, hipStream_t st, const DevAlloc& al) {
-  *S = nullptr;
-  const int HP = dst_gemm_hp(N);
-  if (!HP) return ST_UNSUPPORTED;
-  const int H = N / 2;
-  std::vector<T> h(2 * (size_t)HP * HP, T(0));
-  const long double pi = 3.141592653589793238462643383279502884L;
-  // sin(pi p / N) has period 2N in p: reduce the integer argument first
-  auto sn = [&](long long p) { return (T)sinl(pi * (long double)(p % (2LL * N)) / (long double)N); };
+template <typename T> std::vector<T> dst_gemm_table(const SineBase& b) {
+  const int N = b.n(), HP = dst_gemm_hp(N), H = N / 2;
+  std::vector<T> h(2 * (size_t)HP * HP, T(0)), per(2 * (size_t)N);
+  for (int j = 0; j < 2 * N; ++j) per[j] = (T)b.at(2LL * j);  // one period of sin(pi j / N)
   for (int m = 1; m <= H; ++m)
-    for (int j = 0; j < H; ++j) h[(size_t)(m - 1) * HP + j] = sn((long long)(2 * j + 1) * m);
+    for (int j = 0; j < H; ++j) h[(size_t)(m - 1) * HP + j] = per[((2 * j + 1) * m) % (2 * N)];
   for (int m = 1; m <= H - 1; ++m)
-    for (int j = 1; j <= H - 1; ++j) h[(size_t)HP * HP + (size_t)(m - 1) * HP + (j - 1)] = sn(2LL * j * m);
-  {
-    const int rc = dev_alloc(al, reinterpret_cast<void**>(S), sizeof(T) * h.size());
-    if (rc != ST_OK) return rc;
-  }
-  AHOC_HIP_TRY(hipMemcpyAsync(*S, h.data(), sizeof(T) * h.size(), hipMemcpyHostToDevice, st));
-  AHOC_HIP_TRY(hipStreamSynchronize(st));
-  return ST_OK;
+    for (int j = 1; j <= H - 1; ++j) h[(size_t)HP * HP + (size_t)(m - 1) * HP + (j - 1)] = per[(2 * j * m) % (2 * N)];
+  return h;
 }
 
 template <typename T>
@@ -248,8 +237,8 @@ int dst_gemm_pass(const T* S, int N, const T* in, T* out, long long outer, long 
   }
 }
 
-template int dst_gemm_table<float>(float**, int, hipStream_t, const DevAlloc&);
-template int dst_gemm_table<double>(double**, int, hipStream_t, const DevAlloc&);
+template std::vector<float> dst_gemm_table<float>(const SineBase&);
+template std::vector<double> dst_gemm_table<double>(const SineBase&);
 template int dst_gemm_pass<float>(const float*, int, const float*, float*, long long, long long, long long,
                                   hipStream_t);
 template int dst_gemm_pass<double>(const double*, int, const double*, double*, long long, long long, long long,
