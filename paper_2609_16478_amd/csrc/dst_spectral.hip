@@ -273,16 +273,22 @@ int gen_launch(const GenArgs<T>& a0, long long outer, hipStream_t st) {
   return ST_OK;
 }
 
-// Face contractions of whole planes (x-face row dots and y-face column sums), one wavefront
-// per row: a lane holds CPL = px / 64 columns, so a row's dot needs one wavefront reduction
-// for 64 * CPL values; the column sums accumulate per wavefront in registers and are
-// combined through LDS once per plane.
-template <typename T, int CPL>
-__global__ void __launch_bounds__(256) k_face_reduce_w(const T* __restrict__ W, long long planes, int ny, int nx,
-                                                       int px, const T* __restrict__ wx, const T* __restrict__ wy,
-                                                       T* __restrict__ fx, T* __restrict__ fy, long long fx_side,
-                                                       long long fx_plane, long long fx_row) {
-  __shared__ T col[4][2][CPL * 64];
+// Face contractions of whole planes (x-face row dots and y-face column sums), one work-group
+// per plane and one wavefront per row: a lane holds CPL columns, so a row's dot needs one
+// wavefront reduction for 64 CPL values; the column sums accumulate per wavefront in registers
+// and are combined through LDS once per plane.  A read of the volume, bound by the loads in
+// flight: there are about as many planes as compute units, so a plane takes the NW wavefronts
+// that its registers allow.  FP64 256^3 27 us (4.9 TB/s; 256-lane rows, one row at a time, 147),
+// 768^3 745 us (969); FP32 with four wavefronts per plane before: 128^3 22 -> 7.0 us, 768^3 394
+// -> 353.
+template <typename T, int CPL, int NW>
+__global__ void __launch_bounds__(64 * NW) k_face_reduce_w(const T* __restrict__ W, long long planes, int ny, int nx,
+                                                           int px, const T* __restrict__ wx,
+                                                           const T* __restrict__ wy, T* __restrict__ fx,
+                                                           T* __restrict__ fy, long long fx_side,
+                                                           long long fx_plane, long long fx_row) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  T* col = reinterpret_cast<T*>(smem);  // [NW][2][64 CPL]
   const long long o = blockIdx.x;
   const T* __restrict__ Wp = W + o * (long long)ny * px;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -294,40 +300,53 @@ __global__ void __launch_bounds__(256) k_face_reduce_w(const T* __restrict__ W, 
     wxh[j] = c < nx ? wx[nx + c] : T(0);
     accl[j] = acch[j] = T(0);
   }
-#pragma unroll 2
-  for (int ky = wv; ky < ny; ky += 4) {
-    const T* __restrict__ row = Wp + (long long)ky * px;
-    T v[CPL];
+  constexpr int RPT = CPL <= 4 ? 4 : 2;  // rows in flight per wavefront
+  for (int k0 = wv; k0 < ny; k0 += RPT * NW) {
+    T v[RPT][CPL], yl[RPT], yh[RPT];
 #pragma unroll
-    for (int j = 0; j < CPL; ++j) v[j] = __builtin_nontemporal_load(row + lane + 64 * j);  // read once
-    const T yl = wy[ky], yh = wy[ny + ky];
-    T dl = 0, dh = 0;
+    for (int r = 0; r < RPT; ++r) {
+      const int ky = min(k0 + r * NW, ny - 1);
+      const bool ok = k0 + r * NW < ny;
+      const T* __restrict__ row = Wp + (long long)ky * px;
 #pragma unroll
-    for (int j = 0; j < CPL; ++j) {
-      dl += v[j] * wxl[j];
-      dh += v[j] * wxh[j];
-      accl[j] += v[j] * yl;
-      acch[j] += v[j] * yh;
+      for (int j = 0; j < CPL; ++j) {
+        const int c = lane + 64 * j;
+        v[r][j] = c < px ? __builtin_nontemporal_load(row + c) : T(0);  // read once
+      }
+      yl[r] = ok ? wy[ky] : T(0);
+      yh[r] = ok ? wy[ny + ky] : T(0);
     }
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-      dl += __shfl_xor(dl, m, 64);
-      dh += __shfl_xor(dh, m, 64);
-    }
-    if (lane == 0) {
-      fx[o * fx_plane + ky * fx_row] = dl;
-      fx[fx_side + o * fx_plane + ky * fx_row] = dh;
+    for (int r = 0; r < RPT; ++r) {
+      T dl = 0, dh = 0;
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) {
+        dl += v[r][j] * wxl[j];
+        dh += v[r][j] * wxh[j];
+        accl[j] += v[r][j] * yl[r];
+        acch[j] += v[r][j] * yh[r];
+      }
+      // both sums in one reduction: the halves of the wavefront exchange first
+      const T send = lane < 32 ? dh : dl;
+      T d = (lane < 32 ? dl : dh) + __shfl_xor(send, 32, 64);
+#pragma unroll
+      for (int m = 16; m >= 1; m >>= 1) d += __shfl_xor(d, m, 64);
+      if ((lane & 31) == 0 && k0 + r * NW < ny)
+        fx[(lane ? fx_side : 0) + o * fx_plane + (k0 + r * NW) * fx_row] = d;
     }
   }
 #pragma unroll
   for (int j = 0; j < CPL; ++j) {
-    col[wv][0][lane + 64 * j] = accl[j];
-    col[wv][1][lane + 64 * j] = acch[j];
+    col[(wv * 2) * 64 * CPL + lane + 64 * j] = accl[j];
+    col[(wv * 2 + 1) * 64 * CPL + lane + 64 * j] = acch[j];
   }
   __syncthreads();
-  for (int c = threadIdx.x; c < px; c += 256) {
-    fy[o * px + c] = col[0][0][c] + col[1][0][c] + col[2][0][c] + col[3][0][c];
-    fy[(planes + o) * px + c] = col[0][1][c] + col[1][1][c] + col[2][1][c] + col[3][1][c];
+  for (int e = threadIdx.x; e < 2 * px; e += 64 * NW) {
+    const int sd = e >= px, c = e - sd * px;
+    T t = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) t += col[(w * 2 + sd) * 64 * CPL + c];
+    fy[(sd * planes + o) * px + c] = t;
   }
 }
 
@@ -429,28 +448,30 @@ template <typename T>
 int face_reduce(const T* W, long long planes, int ny, int nx, int px, const T* wx, const T* wy, T* fx, T* fy,
                 long long fx_side, long long fx_plane, long long fx_row, hipStream_t st) {
   if (planes <= 0 || ny <= 0) return ST_OK;
-  // FP32: one wavefront per row (the FP64 form keeps the 256-lane rows: its 16-column
-  // wavefront variant loses occupancy to registers and measured slower)
-  if (sizeof(T) == 4 && fy && px % 64 == 0 && px <= 1024 && planes <= 0x7fffffffLL) {
-#define AHOC_FRW(C)                                                                                     \
-  case C:                                                                                               \
-    hipLaunchKernelGGL((fast::k_face_reduce_w<T, C>), dim3((unsigned)planes), dim3(256), 0, st, W, planes, ny, \
-                       nx, px, wx, wy, fx, fy, fx_side, fx_plane, fx_row);                              \
-    AHOC_HIP_TRY(hipGetLastError());                                                                    \
-    return ST_OK
-    switch (px / 64) {
-      AHOC_FRW(1);
-      AHOC_FRW(2);
-      AHOC_FRW(3);
-      AHOC_FRW(4);
-      AHOC_FRW(6);
-      AHOC_FRW(8);
-      AHOC_FRW(12);
-      AHOC_FRW(16);
+  if (fy && px <= 1024 && planes <= 0x7fffffffLL) {
+    // 16 wavefronts per plane where a lane holds up to 4 columns, 8 beyond
+#define AHOC_FRW(C, NW)                                                                                          \
+  hipLaunchKernelGGL((fast::k_face_reduce_w<T, C, NW>), dim3((unsigned)planes), dim3(64 * NW),                   \
+                     sizeof(T) * 2 * NW * 64 * C, st, W, planes, ny, nx, px, wx, wy, fx, fy, fx_side, fx_plane, fx_row)
+    switch ((px + 63) / 64) {
+      case 1: AHOC_FRW(1, 16); break;
+      case 2: AHOC_FRW(2, 16); break;
+      case 3: AHOC_FRW(3, 16); break;
+      case 4: AHOC_FRW(4, 16); break;
+      case 5: case 6: AHOC_FRW(6, 8); break;
+      case 7: case 8: AHOC_FRW(8, 8); break;
+      case 9: case 10: case 11: case 12:
+        if (sizeof(T) == 8) AHOC_FRW(12, 4);
+        else AHOC_FRW(12, 8);
+        break;
       default:
+        if (sizeof(T) == 8) AHOC_FRW(16, 4);
+        else AHOC_FRW(16, 8);
         break;
     }
 #undef AHOC_FRW
+    AHOC_HIP_TRY(hipGetLastError());
+    return ST_OK;
   }
   if (!fy) {
     // row dots alone: one wavefront per 8 / CPL rows (CPL columns per lane and chunk)
