@@ -54,6 +54,41 @@ template <typename T, int N> constexpr int pipe_nseq() {
   return nseq;
 }
 
+// Narrow tiles for generation passes that would have fewer work-groups than PIPE_MIN_TILES (a
+// single 2-D plane of N columns has N / 32): as few pairs as fill one wavefront, at least 2.
+// Their row segments are shorter than a cache line, but such a plane lives in the caches.  One
+// FP32 plane at N = 1024: 18.3 us with 32 work-groups, 13.0 with 256.  The passes that read the
+// volume gain nothing from it (spectral M 21.4 and 21.0 us, FP64 Poisson 28.5 and 27.7): their
+// time there is the chain of one tile, whatever its width.
+constexpr long long PIPE_MIN_TILES = 128;
+template <typename T, int N> constexpr int pipe_narrow() {
+  constexpr int TPS = N / PipePlan<N>::PPT;
+  int nseq = 2;
+  while (nseq * TPS < 64) nseq *= 2;
+  return N >= 192 && nseq < pipe_nseq<T, N>() ? nseq : pipe_nseq<T, N>();
+}
+
+// A table of COUNT entries on its way to LDS through the registers of NT threads: every load of
+// every table of a kernel is in flight before the first is waited for.
+template <typename V, int COUNT, int NT> struct TabCopy {
+  static constexpr int IT = (COUNT + NT - 1) / NT;
+  V v[IT];
+  __device__ __forceinline__ void load(const V* __restrict__ src) {
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      const int j = (int)threadIdx.x + i * NT;
+      v[i] = src[j < COUNT ? j : COUNT - 1];
+    }
+  }
+  __device__ __forceinline__ void store(V* dst) const {
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      const int j = (int)threadIdx.x + i * NT;
+      if (j < COUNT) dst[j] = v[i];
+    }
+  }
+};
+
 // LDS of a tile (sequences and segment totals) and, in MODE 3, the face row and (where it
 // fits) the per-position table after it
 template <typename T, int N, int NSEQ> constexpr size_t pipe_tile_bytes() {
@@ -201,10 +236,8 @@ __global__ void __launch_bounds__(NSEQ*(N / PipePlan<N>::PPT)) k_dst_pipe(Args<T
   constexpr bool PTL = MODE == 3 && pipe_ptab_lds<T, N, NSEQ>();
   constexpr bool XLDS = MODE == 3 && pipe_xrow_lds<T, N, NSEQ>();
   cx<T>* ptl = xrow + L;  // [m - 1][2]
-  if constexpr (PTL) {
-    const cx<T>* pg = reinterpret_cast<const cx<T>*>(a.gn.ptab);
-    for (int j = threadIdx.x; j < 2 * L; j += NSEQ * TPS) ptl[j] = pg[j];
-  }
+  [[maybe_unused]] TabCopy<cx<T>, PTL ? 2 * L : 1, NSEQ * TPS> c_pt;
+  if constexpr (PTL) c_pt.load(reinterpret_cast<const cx<T>*>(a.gn.ptab));
   constexpr bool TWL = pipe_tab_lds<T, N, NSEQ, MODE>();
   constexpr bool STL = pipe_stab_lds<T, N, NSEQ, MODE>();
   constexpr bool WTL = pipe_wtab_lds<T, N, NSEQ, MODE>();
@@ -214,14 +247,21 @@ __global__ void __launch_bounds__(NSEQ*(N / PipePlan<N>::PPT)) k_dst_pipe(Args<T
   T* stl = reinterpret_cast<T*>(smem + pipe_tab_off<T, N, NSEQ, MODE>() + pipe_tab_bytes<T, N>());
   T* wtl = stl + align16((size_t)L * sizeof(T)) / sizeof(T);
   if constexpr (TWL) {
-    for (int j = threadIdx.x; j < NTW; j += NSEQ * TPS) twl[j] = a.tw[j];
-    for (int j = threadIdx.x; j <= HN; j += NSEQ * TPS) snl[j] = a.sn[j];
-    if constexpr (STL)
-      for (int j = threadIdx.x; j < L; j += NSEQ * TPS) stl[j] = a.fs.s_this[j];
-    if constexpr (WTL)
-      for (int j = threadIdx.x; j < 2 * L; j += NSEQ * TPS) wtl[j] = a.fc.w[j];
-    __syncthreads();
+    TabCopy<cx<T>, NTW, NSEQ * TPS> c_tw;
+    TabCopy<T, HN + 1, NSEQ * TPS> c_sn;
+    [[maybe_unused]] TabCopy<T, STL ? L : 1, NSEQ * TPS> c_st;
+    [[maybe_unused]] TabCopy<T, WTL ? 2 * L : 1, NSEQ * TPS> c_wt;
+    c_tw.load(a.tw);
+    c_sn.load(a.sn);
+    if constexpr (STL) c_st.load(a.fs.s_this);
+    if constexpr (WTL) c_wt.load(a.fc.w);
+    c_tw.store(twl);
+    c_sn.store(snl);
+    if constexpr (STL) c_st.store(stl);
+    if constexpr (WTL) c_wt.store(wtl);
   }
+  if constexpr (PTL) c_pt.store(ptl);
+  if constexpr (TWL || PTL) __syncthreads();
   const T* s_tab = STL ? stl : a.fs.s_this;
   const T* w_tab = WTL ? wtl : a.fc.w;
   constexpr int XR = MODE == 3 ? (L + NSEQ * TPS - 1) / (NSEQ * TPS) : 1;
@@ -801,17 +841,34 @@ __global__ void __launch_bounds__(NSEQ*(N / PipePlan<N>::PPT)) k_gen_pipe(GenPip
   const bool modd = ((1 + mi0) & 1) != 0;
 
   // tile-invariant tables of the pass axis
-  if constexpr (TLDS) {
-    for (int j = tid0; j < L; j += THREADS) {
-      cx<T> t;
-      t.x = g.wp[j];
-      t.y = a.fs.s_this[j];
-      tab[j] = t;
+  {
+    [[maybe_unused]] TabCopy<T, TLDS ? L : 1, THREADS> c_wp, c_st;
+    [[maybe_unused]] TabCopy<cx<T>, TWL ? NTW : 1, THREADS> c_tw;
+    [[maybe_unused]] TabCopy<T, TWL ? HN + 1 : 1, THREADS> c_sn;
+    if constexpr (TLDS) {
+      c_wp.load(g.wp);
+      c_st.load(a.fs.s_this);
     }
-  }
-  if constexpr (TWL) {
-    for (int j = tid0; j < NTW; j += THREADS) twl[j] = a.tw[j];
-    for (int j = tid0; j <= HN; j += THREADS) snl[j] = a.sn[j];
+    if constexpr (TWL) {
+      c_tw.load(a.tw);
+      c_sn.load(a.sn);
+    }
+    if constexpr (TLDS) {
+#pragma unroll
+      for (int i = 0; i < c_wp.IT; ++i) {
+        const int j = tid0 + i * THREADS;
+        if (j < L) {
+          cx<T> t;
+          t.x = c_wp.v[i];
+          t.y = c_st.v[i];
+          tab[j] = t;
+        }
+      }
+    }
+    if constexpr (TWL) {
+      c_tw.store(twl);
+      c_sn.store(snl);
+    }
   }
 
   // tile -> (slab o, first column c0 in the slab, row ib of the column decode), in 32-bit
@@ -1073,13 +1130,13 @@ __global__ void __launch_bounds__(NSEQ*(N / PipePlan<N>::PPT)) k_gen_pipe(GenPip
   }
 }
 
-template <typename T, int N> struct GenPipeLaunch {
-  static constexpr int NSEQ = pipe_nseq<T, N>();
+template <typename T, int N, int NSEQ = pipe_nseq<T, N>()> struct GenPipeLaunch {
+  static constexpr int NARROW = pipe_narrow<T, N>();
   static constexpr int TPS = N / PipePlan<N>::PPT;
   static constexpr int THREADS = NSEQ * TPS;
   static constexpr size_t LDS = GenShape<T, N, NSEQ>::LDS;
   // the non-temporal form exists where a volume can exceed the caches (N >= 384)
-  static constexpr bool HAS_NT = N >= 384;
+  static constexpr bool HAS_NT = N >= 384 && NSEQ == pipe_nseq<T, N>();
 
   template <bool NT> static int resident() {
     static std::once_flag once;
@@ -1098,6 +1155,12 @@ template <typename T, int N> struct GenPipeLaunch {
   }
 
   static int run(GenPipeArgs<T>& a, hipStream_t st) {
+    if constexpr (NARROW < NSEQ) {
+      if (a.outer * ((a.inner + 2LL * NSEQ - 1) / (2LL * NSEQ)) < PIPE_MIN_TILES) {
+        const int rc = GenPipeLaunch<T, N, NARROW>::run(a, st);
+        if (rc != ST_UNSUPPORTED) return rc;  // refused before anything is launched
+      }
+    }
     if (THREADS % 64 != 0 || THREADS > pipe_cap<T, N>() || LDS > 160 * 1024) return ST_UNSUPPORTED;
     // one row of the column decode per tile; pair loads of the y-face rows aligned
     if (a.fs.na % (2 * NSEQ) != 0 || (a.inner & 1)) return ST_UNSUPPORTED;
