@@ -583,6 +583,31 @@ int poisson(ahoc_handle* h, Prec<T>& P, T* buf, const DstScale<T>& sc, hipStream
   return ST_OK;
 }
 
+// Dirichlet solve between the caller's dense arrays (ahoc_poisson).
+template <typename T> int poisson_dense(ahoc_handle* h, Prec<T>& P, const double* gin, double* wout, hipStream_t st) {
+  // dense caller arrays (row length n_x - 1) <-> padded interior rows
+  const Geom& g = h->g;
+  const long long rows = (long long)g.ni[1] * g.ni[2];
+  if (g.dim == 2 && poisson_small_ok<T>(g.n[0], g.n[1])) {
+    PoissonSmall<T> a{};
+    a.g = gin;
+    a.w = wout;
+    for (int k = 0; k < 2; ++k) {
+      a.n[k] = g.n[k];
+      a.h[k] = g.h[k];
+      a.sn[k] = P.tb[k].sn;
+      a.s[k] = P.s[k];
+      a.half[k] = P.tb[k].ppt != 0;
+    }
+    a.c_ta = P.scP.c_ta;
+    a.scale = P.scP.scale;
+    return poisson_small<T>(a, st);
+  }
+  TRY((pitch_copy<double, T>(rows, g.ni[0], gin, g.ni[0], P.bufA, g.px, st)));
+  TRY(poisson<T>(h, P, P.bufA, P.scP, st));
+  return pitch_copy<T, double>(rows, g.ni[0], P.bufA, g.px, wout, g.ni[0], st);
+}
+
 // Variable beta (Remark 2): the interior V of -L_h V + M(c V) = src with V = Q on the face
 // interiors, c = beta / alpha nodal, into P.bufA.  BiCGSTAB on A x = src - A_IB Q (A the
 // interior operator), right-preconditioned by K = -L_h + cshift M, whose inverse is one
@@ -2015,19 +2040,8 @@ ahoc_status ahoc_poisson(ahoc_handle* h, const double* gin, double* wout, void* 
   if (!h || !gin || !wout) return AHOC_E_INVALID;
   hipStream_t st = (hipStream_t)stream;
   using namespace ahoc;
-  int rc;
-  // dense caller arrays (row length n_x - 1) <-> padded interior rows
-  const Geom& g = h->g;
-  const long long rows = (long long)g.ni[1] * g.ni[2];
-  if (h->opt.precision == AHOC_MIXED) {
-    rc = pitch_copy<double, float>(rows, g.ni[0], gin, g.ni[0], h->p32.bufA, g.px, st);
-    if (!rc) rc = poisson<float>(h, h->p32, h->p32.bufA, h->p32.scP, st);
-    if (!rc) rc = pitch_copy<float, double>(rows, g.ni[0], h->p32.bufA, g.px, wout, g.ni[0], st);
-  } else {
-    rc = pitch_copy<double, double>(rows, g.ni[0], gin, g.ni[0], h->p64.bufA, g.px, st);
-    if (!rc) rc = poisson<double>(h, h->p64, h->p64.bufA, h->p64.scP, st);
-    if (!rc) rc = pitch_copy<double, double>(rows, g.ni[0], h->p64.bufA, g.px, wout, g.ni[0], st);
-  }
+  int rc = h->opt.precision == AHOC_MIXED ? poisson_dense<float>(h, h->p32, gin, wout, st)
+                                          : poisson_dense<double>(h, h->p64, gin, wout, st);
   if (!rc) rc = mark_done(h, st);
   return (ahoc_status)rc;
 }

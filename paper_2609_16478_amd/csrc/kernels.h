@@ -123,6 +123,23 @@ bool lines2d_supported(int N);
 template <typename T> int front2d(int N, const Front2d<T>& a, int nb, hipStream_t st);
 template <typename T> int back2d(int N, const Back2d<T>& a, int nb, hipStream_t st);
 
+// poisson_small.hip ---------------------------------------------------------------------
+// w = L_int^{-1} g on the dense interior of a small 2-D grid (poisson_small_ok), one launch;
+// w may equal g.  sn, s: an axis's sine table (half: j <= N/2) and eigenvalues, or null, then
+// they are evaluated in FP64 from n and h.
+template <typename T> struct PoissonSmall {
+  const double* g;
+  double* w;
+  int n[2];
+  double h[2];
+  const T* sn[2];
+  const T* s[2];
+  int half[2];
+  T c_ta, scale;
+};
+template <typename T> bool poisson_small_ok(int n0, int n1);
+template <typename T> int poisson_small(const PoissonSmall<T>& a, hipStream_t st);
+
 // krylov.hip --------------------------------------------------------------------------
 // partial dot products of nvec basis vectors (row stride ld) with w: part[v * nb + b]
 int mdot_partial(const double* V, long long ld, int nvec, const double* w, long long n, int ns, double* part,

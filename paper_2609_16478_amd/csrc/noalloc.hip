@@ -119,6 +119,18 @@ int poisson_noalloc(int dim, const int* n, const double* lo, const double* hi, c
                    "ahoc_poisson_noalloc");
     return ST_INVALID;
   }
+  if (dim == 2 && poisson_small_ok<T>(N[0], N[1])) {  // one work-group, nothing in the array
+    PoissonSmall<T> a{};
+    a.g = g;
+    a.w = w;
+    for (int k = 0; k < 2; ++k) {
+      a.n[k] = N[k];
+      a.h[k] = h[k];
+    }
+    a.c_ta = (T)((h[1] * h[1] + h[0] * h[0]) / 12.0);
+    a.scale = (T)(2.0 / N[0] * (2.0 / N[1]));
+    return poisson_small<T>(a, st);
+  }
   unsigned char* p = static_cast<unsigned char*>(base);
   size_t off = 0;
   DstTables<T> tb[3];

@@ -104,3 +104,29 @@ def test_face_transforms_match_fft_passes(ah, n, prec):
             ah.set_dst_variant(0)
     for k, (a, b) in enumerate(zip(got, ref)):
         assert float((a - b).abs().max()) <= (tol if k == 0 else 1e-11) * float(b.abs().max()), (n, k)
+
+
+# the one-work-group solve at the edges of its tiles (16 pencils, 16 outputs of either parity)
+# and on both sides of its rule (64 x 64 in, 97 x 96 out; 20 x 130 the longest axis)
+@pytest.mark.parametrize("n", [(4, 4), (4, 33), (33, 5), (17, 16), (34, 31), (64, 64), (65, 64), (96, 96), (97, 96),
+                               (100, 96), (20, 130), (130, 20), (101, 101)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_small_plane_poisson(ah, n, prec):
+    hi = (1.0, 0.7)
+    shape = tuple(m + 1 for m in reversed(n))
+    pb = W.Problem(n, (0.0, 0.0), hi, np.ones(shape), np.zeros(shape))
+    ft = fast.FastTier(pb)
+    g = np.random.default_rng(n[0]).standard_normal(ft.g.interior_shape)
+    ref = ft.poisson(g)
+    p = ah.FP64 if prec == "fp64" else ah.MIXED
+    gt = torch.from_numpy(g).cuda()
+    with ah.Solver(pb, precision=p) as s:
+        outs = [s.poisson(gt), ah.poisson_noalloc(n, (0.0, 0.0), hi, gt, precision=p)]
+        ah.set_dst_variant(5)  # as separate passes
+        outs.append(s.poisson(gt))
+        ah.set_dst_variant(0)
+    inplace = gt.clone()
+    ah.poisson_noalloc(n, (0.0, 0.0), hi, inplace, precision=p, out=inplace)
+    assert torch.equal(inplace, outs[1])
+    for w in outs:
+        assert np.abs(w.cpu().numpy() - ref).max() <= (1e-12 if prec == "fp64" else 1e-5) * np.abs(ref).max()
