@@ -46,7 +46,8 @@ template <typename T> struct Prec {
   T* af = nullptr;    // alpha on face nodes (N_q)
   T* bufA = nullptr;  // interior work (V)
   T* bufB = nullptr;  // interior work (U)
-  T* scr = nullptr;   // interior work of the passes of lengths without an FFT plan (else null)
+  T* scr = nullptr;   // interior work of passes that write elsewhere than they read (else null)
+  bool planes = false;  // x and y of the Dirichlet solves in one launch (dst_plane.hip)
   T* qT = nullptr;    // N_q, Q in this precision
   T* zq = nullptr;    // N_q zeros
   T* wf[3] = {nullptr, nullptr, nullptr};  // per axis: one-sided face weights w_lo(k), w_hi(k)
@@ -372,6 +373,11 @@ bool has_plans(const Geom& g) {
   return true;
 }
 
+// Whether the Dirichlet solves of a 3-D grid take x and y of each plane in one launch.
+template <typename T> bool planes_pay(const Geom& g) {
+  return g.dim == 3 && dst_get_variant() == 0 && dst_plane_ok(g.n[0], g.n[1]);
+}
+
 // Whether the transforms of a grid's faces run as sine products, all faces in one launch per
 // axis pass, instead of one FFT pass per face pair and axis.  A launch of its own costs an FFT
 // pass of a small face 6 to 10 us whatever its work; the products' work grows with N.  Mixed
@@ -482,7 +488,8 @@ template <typename T> int prec_init(ahoc_handle* h, Prec<T>& P, int tile_opt, hi
   }
   TRY(alloc_int(h, &P.bufA, st));
   TRY(alloc_int(h, &P.bufB, st));
-  if (!has_plans(g)) TRY(alloc_int(h, &P.scr, st));
+  P.planes = planes_pay<T>(g);
+  if (!has_plans(g) || P.planes) TRY(alloc_int(h, &P.scr, st));
   // setup-time choice between the FFT and the matrix-core pass for the plain passes of the
   // operator, timed on their own shapes: the x (row) passes; in 3-D also the strided y passes
   if (g.dim == 2) {
@@ -545,7 +552,8 @@ template <typename T> void prec_free(Prec<T>& P) {
 // Dirichlet solve on an interior array: buf <- scale * S (S in / lambda), in place unless
 // `in` is given (then the first pass reads it and `in` is left unchanged).  The plain passes of
 // an axis without an FFT plan go from buf to P.scr or back (each such axis has two of them, so
-// the result ends in buf), its fused pass through the other of the two.
+// the result ends in buf), its fused pass through the other of the two.  Plane passes go from
+// the input to P.scr and from there to buf.
 template <typename T>
 int poisson(ahoc_handle* h, Prec<T>& P, T* buf, const DstScale<T>& sc, hipStream_t st, const T* in = nullptr,
             const RowLift<T>* lf = nullptr) {
@@ -572,6 +580,21 @@ int poisson(ahoc_handle* h, Prec<T>& P, T* buf, const DstScale<T>& sc, hipStream
     TRY(run(AHOC_K_DST_ROWS, P.tb[0], (long long)g.nb * g.ni[1], 1, nullptr, P.tile[0]));
     TRY(run(AHOC_K_DST_FUSED, P.tb[1], g.nb, g.px, &sc, P.tile[1]));
     TRY(run(AHOC_K_DST_ROWS, P.tb[0], (long long)g.nb * g.ni[1], 1, nullptr, P.tile[0]));
+  } else if (P.planes && dst_get_variant() == 0) {
+    hipEvent_t e = tbegin(h, st);
+    if (lf) {
+      TRY(dst_rows_lift_pass<T>(P.tb[0].N, P.tb[0].tw, P.tb[0].sn, src, P.scr, (long long)g.ni[1] * g.ni[2], g.px, *lf, st));
+      TRY(dst_pass<T>(P.tb[1], P.scr, P.scr, g.ni[2], g.px, g.px, nullptr, P.tile[1], st, nullptr, nullptr));
+    } else {
+      TRY((dst_plane_pass<T, T, T>(P.tb[0], P.tb[1], src, g.px, P.scr, g.px, g.ni[2], st)));
+    }
+    tend(h, AHOC_K_DST_ROWS, e, pass_bytes, st);
+    e = tbegin(h, st);
+    TRY(dst_solve_axis<T>(P.tb[2], P.scr, (long long)g.px * g.ni[1], g.px, sc, P.tile[2], buf, st));
+    tend(h, AHOC_K_DST_FUSED, e, pass_bytes, st);
+    e = tbegin(h, st);
+    TRY((dst_plane_pass<T, T, T>(P.tb[0], P.tb[1], P.scr, g.px, buf, g.px, g.ni[2], st)));
+    tend(h, AHOC_K_DST_ROWS, e, pass_bytes, st);
   } else {
     const long long rows = (long long)g.ni[1] * g.ni[2];
     TRY(run(AHOC_K_DST_ROWS, P.tb[0], rows, 1, nullptr, P.tile[0]));
@@ -602,6 +625,11 @@ template <typename T> int poisson_dense(ahoc_handle* h, Prec<T>& P, const double
     a.c_ta = P.scP.c_ta;
     a.scale = P.scP.scale;
     return poisson_small<T>(a, st);
+  }
+  if (P.planes && dst_get_variant() == 0) {  // the caller's rows are read and written by the plane passes
+    TRY((dst_plane_pass<T, double, T>(P.tb[0], P.tb[1], gin, g.ni[0], P.bufA, g.px, g.ni[2], st)));
+    TRY(dst_solve_axis<T>(P.tb[2], P.bufA, (long long)g.px * g.ni[1], g.px, P.scP, P.tile[2], P.scr, st));
+    return dst_plane_pass<T, T, double>(P.tb[0], P.tb[1], P.bufA, g.px, wout, g.ni[0], g.ni[2], st);
   }
   TRY((pitch_copy<double, T>(rows, g.ni[0], gin, g.ni[0], P.bufA, g.px, st)));
   TRY(poisson<T>(h, P, P.bufA, P.scP, st));

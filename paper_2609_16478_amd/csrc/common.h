@@ -350,6 +350,18 @@ template <typename T> struct SineJob {
 };
 template <typename T> int dst_sine_jobs(const SineJob<T>* jobs, int count, hipStream_t st);
 constexpr int DST_SINE_JOBS_MAX_N = 1024;
+// Both in-plane axes of a 3-D array (planes of [ty.N - 1][in_pitch]) in one launch, dst_plane.hip:
+// lengths of DST_PLANE_MAX_N intervals or fewer, `out` apart from `in`.  Columns from tx.N - 1 to
+// the output pitch (of at most the next multiple of 32) are written as zeros.
+constexpr int DST_PLANE_MAX_N = 128;
+bool dst_plane_ok(int n0, int n1);
+template <typename T, typename TI, typename TO>
+int dst_plane_pass(const DstTables<T>& tx, const DstTables<T>& ty, const TI* in, long long in_pitch, TO* out,
+                   long long out_pitch, int planes, hipStream_t st);
+// The fused pass of the slowest axis of a solve (one slab, in place); tile and tmp as for dst_pass.
+template <typename T>
+int dst_solve_axis(const DstTables<T>& tb, T* data, long long inner, long long pitch, const DstScale<T>& fs, int tile,
+                   T* tmp, hipStream_t st);
 double dst_sine_flops(int N, long long outer, long long inner);
 int dst_default_tile(int N, int elem_bytes);
 

@@ -28,6 +28,7 @@
 // k_dst_direct, one thread per output and the whole pencil in LDS, remains for in-place
 // passes of N > 2048, whose outputs k_dst_sine could not hold in registers.
 #include "common.h"
+#include "mfma_sine.h"
 
 #include <algorithm>
 #include <mutex>
@@ -146,25 +147,6 @@ template <typename T> __global__ void __launch_bounds__(256) k_dst_direct(Direct
   }
 }
 
-template <typename T> struct SineOps;
-template <> struct SineOps<float> {
-  typedef float v4 __attribute__((ext_vector_type(4)));
-  static __device__ __forceinline__ v4 mfma(float a, float b, v4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  // row of the 16x16 result held in element r of lane group lk = lane / 16
-  static __device__ __forceinline__ int row(int lk, int r) { return 4 * lk + r; }
-  static constexpr int PAD = 4;  // LDS row padding of the row-pass tile -> conflict-free reads
-};
-template <> struct SineOps<double> {
-  typedef double v4 __attribute__((ext_vector_type(4)));
-  static __device__ __forceinline__ v4 mfma(double a, double b, v4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int lk, int r) { return lk + 4 * r; }
-  static constexpr int PAD = 2;
-};
-
 template <typename T> struct SineArgs {
   const T* in;
   T* out;
@@ -179,10 +161,6 @@ template <typename T> struct SineArgs {
 template <typename T, bool ROWS, int TP> constexpr int sine_half(int mc) {
   return ROWS ? 16 * TP * (mc + SineOps<T>::PAD) : mc * (TP == 1 ? 16 : 16 * TP + 16);
 }
-// Period table in LDS: one word of padding every 32, so that the strides 2 m of the 16 lanes'
-// indices do not meet in one bank where m is a multiple of a power of two
-__host__ __device__ constexpr int sine_pad(int j) { return j + (j >> 5); }
-
 // The outputs of TO pairs per KS wavefronts, from pair `first` on, of tile `tile` of 16 TP
 // pencils.  KS wavefronts take every KS-th step of the sum over m and add their sums up at the
 // end (in wavefront order): where a pass has so few pencils that most of the chip is idle, its
@@ -222,12 +200,7 @@ __device__ __forceinline__ void sine_tile(const SineArgs<T>& a, const DstScale<T
   // 300 x 499, FP64: one wait on memory instead of two); the others have no registers for them.
   constexpr bool early = TO * TP <= 2;
   constexpr int TU = early ? 4 : 1;
-  auto entry = [&](int i) -> T {
-    if (!a.half) return a.sn[i];
-    const int j = i >= N ? i - N : i;  // sin(pi + t) = -sin t, sin(pi - t) = sin t
-    const T v = a.sn[j > Hm ? N - j : j];
-    return i >= N ? -v : v;
-  };
+  auto entry = [&](int i) { return sine_entry<T>(a.sn, N, a.half, i); };
   T tv[TU];
   if constexpr (early) {
 #pragma unroll

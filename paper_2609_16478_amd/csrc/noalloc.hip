@@ -188,6 +188,20 @@ int poisson_noalloc(int dim, const int* n, const double* lo, const double* hi, c
   }
   sc.scale = (T)norm;
   const long long rows = (long long)ni[1] * ni[2];
+  auto done = [&] {  // the tables point into the scratch array: nothing to release
+    for (int a = 0; a < 3; ++a) {
+      tb[a].tw = nullptr;
+      tb[a].sn = nullptr;
+    }
+    return ST_OK;
+  };
+  if (dim == 3 && dst_get_variant() == 0 && dst_plane_ok(N[0], N[1])) {
+    // the caller's rows are read and written by the passes over planes
+    TRY_ST((dst_plane_pass<T, double, T>(tb[0], tb[1], g, ni[0], buf, px, ni[2], st)));
+    TRY_ST(dst_solve_axis<T>(tb[2], buf, px * ni[1], px, sc, 0, scr, st));
+    TRY_ST((dst_plane_pass<T, T, double>(tb[0], tb[1], buf, px, w, ni[0], ni[2], st)));
+    return done();
+  }
   {
     const long long n = rows * px;
     const unsigned blocks = (unsigned)std::min<long long>((n + 255) / 256, 65536);
@@ -212,10 +226,7 @@ int poisson_noalloc(int dim, const int* n, const double* lo, const double* hi, c
   }
   TRY_ST(pass(0, rows, 1, nullptr));
   TRY_ST((pitch_copy<T, double>(rows, ni[0], buf, px, w, ni[0], st)));
-  // the tables point into the scratch array: nothing to release
-  tb[0].tw = tb[1].tw = tb[2].tw = nullptr;
-  tb[0].sn = tb[1].sn = tb[2].sn = nullptr;
-  return ST_OK;
+  return done();
 }
 
 }  // namespace
