@@ -101,9 +101,9 @@ struct ahoc_handle {
   bool cvar = false;
   double* cnod = nullptr;
   double* bk[7] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-  double* bdot = nullptr;    // device scalars of the BiCGSTAB dot products
-  double* bpart = nullptr;   // their partial sums
-  double* bpin = nullptr;    // host-pinned copies
+  double* bdot = nullptr;    // BiCGSTAB's alpha and omega on the device
+  double* bpart = nullptr;   // partial sums of its dot products
+  double* bpin = nullptr;    // sums and scalars, host-pinned
   long long vs_iters = 0;    // BiCGSTAB iterations so far (reported per solve)
   double vs_worst = 0;       // largest final relative residual of a V-solve since the last reset
   ahoc_options opt;
@@ -649,75 +649,69 @@ constexpr int VS_DOT_BLOCKS = 2048;  // work-groups of the V-solve's dot sweeps 
 int vsolve_var(ahoc_handle* h, Prec<double>& P, const double* Q, const double* src, hipStream_t st) {
   const Geom& g = h->g;
   const long long n = TA(g);
-  // rh, r, t are consecutive n-vectors so that <rh, r>, <r, r> and <r, t>, <t, t> are one
-  // two-vector sweep each
+  // r, t are consecutive n-vectors so that <r, t>, <t, t> are one two-vector sweep (2-D)
   double *x = P.bufA, *rh = h->bk[0], *r = h->bk[1], *t = h->bk[2], *p = h->bk[3], *v = h->bk[4],
          *y = h->bk[5], *z = h->bk[6];
   const int nbk = (int)std::max<long long>(1, std::min<long long>(VS_DOT_BLOCKS, n / 2048));
-  // <V_j, w> for the nv consecutive vectors V_0.. (n apart) into bpin[0..nv) (synchronising)
-  auto dots = [&](const double* V, int nv, const double* w) -> int {
-    TRY(mdot_partial(V, n, nv, w, n, 1, h->bpart, nbk, st));
-    TRY(mdot_reduce(h->bpart, nbk, nv, 1, h->bdot, nv, 0, st));
-    AHOC_HIP_TRY(hipMemcpyAsync(h->bpin, h->bdot, sizeof(double) * nv, hipMemcpyDeviceToHost, st));
+  const int nbv = vapply_dot_blocks(g), nb1 = nbv ? nbv : nbk;
+  double* part2 = h->bpart;              // parts of the dot products after a vector step
+  double* part = part2 + 2 * VS_DOT_BLOCKS;  // and of those with the operator's output
+  // out = A in with the parts of <u, out> (and <out, out>: nv = 2, out = u + n) in part
+  auto apply = [&](const double* in, double* out, const double* u, int nv) -> int {
+    if (nbv) return vapply_dot(g, h->w, in, h->cnod, out, u, part, st);
+    TRY(vapply(g, h->w, in, h->cnod, out, st));
+    return mdot_partial(u, n, nv, out, n, 1, part, nbk, st);
+  };
+  // the sums of part2 into bpin[0..nvec), alpha and omega into bpin[4..8) (synchronising)
+  auto sums = [&](int nvec) -> int {
+    TRY(bicg_to_host(part2, nbk, nvec, h->bdot, h->bpin, st));
     AHOC_HIP_TRY(hipStreamSynchronize(st));
     return ST_OK;
   };
-  // y += a x and the reduced <u, y>, <y, y> into bpin[0], bpin[1] (synchronising)
-  auto update_dots = [&](double a, const double* xv, double* yv, const double* u) -> int {
-    TRY(axpy_dot2(n, a, xv, yv, u, h->bpart, nbk, st));
-    TRY(mdot_reduce(h->bpart, nbk, 2, 1, h->bdot, 2, 0, st));
-    AHOC_HIP_TRY(hipMemcpyAsync(h->bpin, h->bdot, sizeof(double) * 2, hipMemcpyDeviceToHost, st));
-    AHOC_HIP_TRY(hipStreamSynchronize(st));
-    return ST_OK;
-  };
-  auto apply = [&](const double* in, double* out) { return vapply(g, h->w, in, nullptr, h->cnod, nullptr, out, st); };
   auto precond = [&](const double* in, double* out) { return poisson<double>(h, P, out, P.scV, st, in); };
   hipEvent_t e = tbegin(h, st);
-  // r = src - A_IB Q  (x = 0)
+  // r = src - A_IB Q  (x = 0), rh = p = r
   TRY(fill(n, 0.0, x, st));
-  TRY(vapply(g, h->w, x, Q, h->cnod, src, r, st));
-  TRY(axpby(n, 0.0, r, -1.0, r, st));
-  AHOC_HIP_TRY(hipMemcpyAsync(rh, r, sizeof(double) * n, hipMemcpyDeviceToDevice, st));
-  TRY(dots(rh, 2, r));  // <rh, r> = <r, r>
-  const double bnorm = std::sqrt(h->bpin[1]);
+  TRY(vstart(g, h->w, n, Q, h->cnod, src, r, rh, p, part2, nbk, st));
+  TRY(sums(1));
+  const double bnorm = std::sqrt(h->bpin[0]);
   if (bnorm == 0.0) {
     tend(h, AHOC_K_VSOLVE, e, 0.0, st);
     return ST_OK;
   }
-  TRY(fill(n, 0.0, p, st));
-  TRY(fill(n, 0.0, v, st));
   double rho = 1.0, alpha = 1.0, omega = 1.0, best = bnorm, rho1 = h->bpin[0];
   double last = bnorm;  // ||r|| of the current iterate
   int since = 0;
   const int cap = h->opt.vsolve_max_iters > 0 ? h->opt.vsolve_max_iters : 200;
   for (int it = 0; it < cap; ++it) {
     if (rho1 == 0.0 || !std::isfinite(rho1)) break;
-    const double beta = (rho1 / rho) * (alpha / omega);
-    TRY(lin3(n, 1.0, r, -beta * omega, v, beta, p, st));  // p = r + beta (p - omega v)
+    if (it) {
+      const double beta = (rho1 / rho) * (alpha / omega);
+      TRY(lin3(n, 1.0, r, -beta * omega, v, beta, p, st));  // p = r + beta (p - omega v)
+    }
     TRY(precond(p, y));
-    TRY(apply(y, v));
-    TRY(dots(v, 1, rh));
-    if (h->bpin[0] == 0.0 || !std::isfinite(h->bpin[0])) break;
-    alpha = rho1 / h->bpin[0];
-    TRY(update_dots(-alpha, v, r, nullptr));  // s = r - alpha v, in r; <s, s>
+    TRY(apply(y, v, rh, 1));
+    TRY(bicg_half(n, rho1, part, nb1, v, r, h->bdot, part2, nbk, st));  // s = r - alpha v, in r; <s, s>
+    TRY(sums(1));
+    if (h->bpin[5] == 0.0) break;  // <rh, v> zero or not finite
+    alpha = h->bpin[4];
     ++h->vs_iters;
-    double rn = std::sqrt(h->bpin[1]);
+    double rn = std::sqrt(h->bpin[0]);
     if (rn <= 1e-14 * bnorm) {
       TRY(axpby(n, alpha, y, 1.0, x, st));  // x += alpha y
       last = rn;
       break;
     }
     TRY(precond(r, z));
-    TRY(apply(z, t));
-    TRY(dots(r, 2, t));  // <s, t>, <t, t>
-    if (h->bpin[1] == 0.0 || !std::isfinite(h->bpin[0] / h->bpin[1])) {
-      TRY(axpby(n, alpha, y, 1.0, x, st));  // keep the half step
+    TRY(apply(z, t, r, 2));  // <s, t>, <t, t>
+    // x += alpha y + omega z, r = s - omega t; <rh, r> for the next step, <r, r>
+    TRY(bicg_full(n, part, nb1, y, z, t, rh, x, r, h->bdot, part2, nbk, st));
+    TRY(sums(2));
+    if (h->bpin[7] == 0.0) {  // <t, t> zero or omega not finite: the half step alone was taken
       last = rn;
       break;
     }
-    omega = h->bpin[0] / h->bpin[1];
-    TRY(lin3(n, alpha, y, omega, z, 1.0, x, st));  // x += alpha y + omega z
-    TRY(update_dots(-omega, t, r, rh));  // r = s - omega t; <rh, r> for the next step, <r, r>
+    omega = h->bpin[6];
     rn = std::sqrt(h->bpin[1]);
     last = rn;
     rho = rho1;
@@ -1740,7 +1734,8 @@ int setup_impl(const ahoc_problem* pbs, int count, hipStream_t st, ahoc_handle* 
           for (int k = 0; k < 7; ++k) h->bk[k] = blk + k * TA(g);
         }
         TRY(alloc_t(h, &h->bdot, 8));
-        TRY(alloc_t(h, &h->bpart, 2LL * VS_DOT_BLOCKS));
+        AHOC_HIP_TRY(hipMemsetAsync(h->bdot, 0, sizeof(double) * 8, st));
+        TRY(alloc_t(h, &h->bpart, 2LL * VS_DOT_BLOCKS + 2LL * std::max(VS_DOT_BLOCKS, vapply_dot_blocks(g))));
         AHOC_HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&h->bpin), sizeof(double) * 8, hipHostMallocDefault));
       } else if (pb->beta != 0.0) {
         // the v-equation -L_h V + (beta/alpha) M V = M f is solved by the sine transforms only

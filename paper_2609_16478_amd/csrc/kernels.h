@@ -58,10 +58,17 @@ int resid64(const Geom& g, const Weights& w, const double* U, const double* V, c
 int setup_inv_alpha(long long n, const double* alpha, double* ia64, float* ia32, double* bmin,
                     int nb, hipStream_t st);
 int setup_face_alpha(const Geom& g, const double* alpha, double* af64, float* af32, hipStream_t st);
-// variable shift c (nodal): y = -L_h[V] + M(c V) - src on the interior of a single problem
-// (3-D with Q and src null: tiled, and y's row padding is left as it is)
-int vapply(const Geom& g, const Weights& w, const double* X, const double* Q, const double* c, const double* src,
-           double* y, hipStream_t st);
+// variable shift c (nodal): y = -L_h[V] + M(c V) on the interior of a single problem, V = X there
+// and zero on the boundary: 2-D, and 3-D with the work-groups' parts of <u, y> in part[0..nb) and
+// of <y, y> in part[nb..2 nb), nb = vapply_dot_blocks (0 in 2-D; y's row padding is left as it is)
+int vapply(const Geom& g, const Weights& w, const double* X, const double* c, double* y, hipStream_t st);
+int vapply_dot_blocks(const Geom& g);
+int vapply_dot(const Geom& g, const Weights& w, const double* X, const double* c, double* y, const double* u,
+               double* part, hipStream_t st);
+// the V-solve's start on n = the padded interior: r = rh = p = src - A V with V = Q on the face
+// interiors and 0 inside (src may be null), and nb parts of <r, r>
+int vstart(const Geom& g, const Weights& w, long long n, const double* Q, const double* c, const double* src, double* r,
+           double* rh, double* p, double* part, int nb, hipStream_t st);
 // per-block min and max (part[2 b], part[2 b + 1]) of n doubles
 int minmax_partial(long long n, const double* x, double* part, int nblocks, hipStream_t st);
 // Navier faces (the same on every instance of a batch): af = 0 and src_q = -alpha g_L on
@@ -154,10 +161,19 @@ int maxpy(double* w, const double* V, long long ld, int nvec, const double* coef
           long long n, int ns, hipStream_t st);
 int axpby(long long n, double a, const double* x, double b, double* y, hipStream_t st);
 // y += a x with the per-work-group partial sums of <u, y> (u null: 0) and <y, y>, in part[0..nbk)
-// and part[nbk..2 nbk) (reduce with mdot_reduce, nvec 2)
-int axpy_dot2(long long n, double a, const double* x, double* y, const double* u, double* part, int nbk,
-              hipStream_t st);
-// w = a x + b y + c w
+// BiCGSTAB's vector steps with their scalars kept on the device.  part holds the nb1 work-groups'
+// parts of the dot products before the step (one vector after the other), part2 receives nb2
+// parts of those after it; coef = {alpha, alpha is good, omega, omega is good}.
+//   half:  alpha = rho / <rh, v>, r -= alpha v; <r, r>.  Neither r nor coef[0] is good where the
+//          divisor is zero or not finite.
+//   full:  omega = <r, t> / <t, t>, x += alpha y + omega z, r -= omega t; <rh, r>, <r, r>.  Where
+//          omega is not good, x += alpha y alone.
+//   to_host: the nvec sums of part and coef into the pinned out[0..nvec), out[4..8).
+int bicg_half(long long n, double rho, const double* part, int nb1, const double* v, double* r, double* coef,
+              double* part2, int nb2, hipStream_t st);
+int bicg_full(long long n, const double* part, int nb1, const double* y, const double* z, const double* t,
+              const double* rh, double* x, double* r, double* coef, double* part2, int nb2, hipStream_t st);
+int bicg_to_host(const double* part, int nb, int nvec, const double* coef, double* out, hipStream_t st);
 int lin3(long long n, double a, const double* x, double b, const double* y, double c, double* w, hipStream_t st);
 // Segment-wise batch utilities (grid.y = segment): x_s = 0 where keep[s] == 0; gather of
 // per-instance arrays (device table of device pointers, null = zeros); scatter to them.

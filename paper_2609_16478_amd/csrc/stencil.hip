@@ -789,70 +789,44 @@ __global__ void k_src_q(Geom g, Weights w, const double* __restrict__ alpha, con
 }
 
 // The v-equation's operator with a variable shift c = beta / alpha (nodal), on the interior:
-//   y = -L_h[V] + M(c V) - src
-// with V = X at interior nodes, Q at face-interior nodes (Q may be null: zero there) and 0
-// on edges and corners (their known values are part of src); src may be null.
-template <int DIM>
-__global__ void k_vapply(Geom g, Weights w, const double* __restrict__ X, const double* __restrict__ Q,
-                         const double* __restrict__ c, const double* __restrict__ src, double* __restrict__ y) {
-  const int nrow_ = DIM == 3 ? g.ni[1] * g.ni[2] : g.ni[1];
-  for (int r_ = blockIdx.x; r_ < nrow_; r_ += gridDim.x)
-  for (int i0_ = threadIdx.x; i0_ < g.px; i0_ += blockDim.x) {
-    const long long e = (long long)r_ * g.px + i0_;
-    const int i = i0_ + 1, j = (DIM == 3 ? r_ % g.ni[1] : r_) + 1, k = DIM == 3 ? r_ / g.ni[1] + 1 : 0;
-    if (i > g.ni[0]) {
-      y[e] = 0.0;
-      continue;
+//   y = -L_h[V] + M(c V),  V = X at interior nodes and 0 on the boundary (2-D)
+__global__ void k_vapply(Geom g, Weights w, const double* __restrict__ X, const double* __restrict__ c,
+                         double* __restrict__ y) {
+  for (int r_ = blockIdx.x; r_ < g.ni[1]; r_ += gridDim.x)
+    for (int i0_ = threadIdx.x; i0_ < g.px; i0_ += blockDim.x) {
+      const long long e = (long long)r_ * g.px + i0_;
+      const int i = i0_ + 1, j = r_ + 1;
+      if (i > g.ni[0]) {
+        y[e] = 0.0;
+        continue;
+      }
+      double lv = 0, mv = 0;
+#pragma unroll
+      for (int dy = -1; dy <= 1; ++dy)
+#pragma unroll
+        for (int dx = -1; dx <= 1; ++dx) {
+          const bool in = i + dx >= 1 && i + dx <= g.ni[0] && j + dy >= 1 && j + dy <= g.ni[1];
+          const double vq = in ? X[e + dy * g.px + dx] : 0.0;
+          lv += lw<2>(w, dx, dy, 0) * vq;
+          if (dx == 0 || dy == 0) mv += (dx == 0 && dy == 0 ? w.m0 : w.m1) * c[(long long)(j + dy) * g.nn[0] + i + dx] * vq;
+        }
+      y[e] = mv - lv;
     }
-    double lv = 0, mv = 0;
-    constexpr int zlo = DIM == 3 ? -1 : 0, zhi = DIM == 3 ? 1 : 0;
-    const bool inner = i >= 2 && i < g.ni[0] && j >= 2 && j < g.ni[1] && (DIM == 2 || (k >= 2 && k < g.ni[2]));
-    if (inner) {
-      // every neighbour is an interior node: fixed offsets, no classification
-      const long long ip = (long long)g.ni[1] * g.px, np = (long long)g.nn[1] * g.nn[0];
-      const long long b0 = nod(g, i, j, k);
-#pragma unroll
-      for (int dz = zlo; dz <= zhi; ++dz)
-#pragma unroll
-        for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-          for (int dx = -1; dx <= 1; ++dx) {
-            const int nzo = (dx != 0) + (dy != 0) + (dz != 0);
-            if (nzo == 3) continue;
-            const double vq = X[e + dz * ip + dy * g.px + dx];
-            lv += lw<DIM>(w, dx, dy, dz) * vq;
-            if (nzo <= 1) mv += (nzo == 0 ? w.m0 : w.m1) * c[b0 + dz * np + dy * g.nn[0] + dx] * vq;
-          }
-    } else {
-      for (int dz = zlo; dz <= zhi; ++dz)
-        for (int dy = -1; dy <= 1; ++dy)
-          for (int dx = -1; dx <= 1; ++dx) {
-            const double wt = lw<DIM>(w, dx, dy, dz);
-            const int nzo = (dx != 0) + (dy != 0) + (dz != 0);
-            if (wt == 0.0 && nzo > 1) continue;  // outside both stencils
-            const int qi = i + dx, qj = j + dy, qk = k + dz;
-            const int nb = nbnd<DIM>(g, qi, qj, qk);
-            double vq = 0;
-            if (nb == 0) vq = X[inr(g, qi, qj, DIM == 3 ? qk : 1)];
-            else if (nb == 1 && Q) vq = Q[qidx<DIM>(g, qi, qj, qk)];
-            lv += wt * vq;
-            if (nzo <= 1) mv += (nzo == 0 ? w.m0 : w.m1) * c[nod(g, qi, qj, qk)] * vq;
-          }
-    }
-    y[e] = mv - lv - (src ? src[e] : 0.0);
-  }
 }
 
-// The same operator without Q and src (3-D), tiled: a work-group owns VTX x VTY columns and
+// The same operator in 3-D, tiled: a work-group owns VTX x VTY columns and
 // marches along z over kchunk planes, with the planes k-1, k, k+1 of its columns and their halo
 // in LDS (zero on the boundary) and c X of plane k beside them, so every value is read from
-// memory about once per plane instead of once per stencil point.  128^3: 24.6 us; 64.4 us with
-// chunks of 32 planes (128 work-groups), plus 11.3 us for a second kernel over the layer next
-// to the boundary, which the zero boundary values make unnecessary.
+// memory about once per plane instead of once per stencil point.  The next plane's values are on
+// their way while a plane is summed: with loads waited for where they are stored, two trips to
+// memory per plane were the time (128^3: 27.0 us, 20.8 now; 64.4 with chunks of 32 planes, 128
+// work-groups).  part[b] and part[gridDim.x + b] are work-group b's parts of <u, y> and <y, y>: a
+// sweep of its own over u and y took 10 us and a launch.
 constexpr int VTX = 64, VTY = 8;
 __global__ void __launch_bounds__(VTX * VTY) k_vapply_tile(Geom g, Weights w, const double* __restrict__ X,
                                                            const double* __restrict__ c, double* __restrict__ y,
-                                                           int kchunk) {
+                                                           int kchunk, const double* __restrict__ u,
+                                                           double* __restrict__ part) {
   constexpr int HX = VTX + 2, HY = VTY + 2;
   __shared__ double xs[3][HY][HX];
   __shared__ double cs[HY][HX];
@@ -869,32 +843,53 @@ __global__ void __launch_bounds__(VTX * VTY) k_vapply_tile(Geom g, Weights w, co
   const bool mine = i <= ni0 && j <= ni1;
   const int k0 = 1 + bz * kchunk, k1 = min(ni2, k0 + kchunk - 1);
   const long long npl = (long long)g.nn[1] * g.nn[0];
-  // halo position (hx, hy) -> node (ib - 1 + hx, jb - 1 + hy), clamped to the far faces
-  // (positions beyond them feed only columns whose outputs are not written)
-  auto hnode = [&](int h, int& gi, int& gj) {
-    gi = min(ib - 1 + h % HX, ni0 + 1);
-    gj = min(jb - 1 + h / HX, ni1 + 1);
-  };
-  auto load_plane = [&](int kk, int slot) {
-    for (int h = threadIdx.x; h < HX * HY; h += VTX * VTY) {
-      int gi, gj;
-      hnode(h, gi, gj);
-      const bool in = gi >= 1 && gi <= ni0 && gj >= 1 && gj <= ni1 && kk >= 1 && kk <= ni2;
-      xs[slot][h / HX][h % HX] = in ? X[((long long)(kk - 1) * ni1 + (gj - 1)) * g.px + (gi - 1)] : 0.0;
-    }
-  };
+  // this thread's halo positions (hx, hy) -> nodes (ib - 1 + hx, jb - 1 + hy), clamped to the far
+  // faces (positions beyond them feed only columns whose outputs are not written)
+  constexpr int NH = (HX * HY + VTX * VTY - 1) / (VTX * VTY);
+  const long long xpl = (long long)ni1 * g.px;
+  long long xoff[NH], coff[NH];
+  bool xin[NH], used[NH];
+#pragma unroll
+  for (int q = 0; q < NH; ++q) {
+    const int h = threadIdx.x + q * VTX * VTY;
+    used[q] = h < HX * HY;
+    const int gi = min(ib - 1 + h % HX, ni0 + 1), gj = min(jb - 1 + h / HX, ni1 + 1);
+    xin[q] = used[q] && gi >= 1 && gi <= ni0 && gj >= 1 && gj <= ni1;
+    xoff[q] = xin[q] ? (long long)(gj - 1) * g.px + (gi - 1) : 0;
+    coff[q] = used[q] ? (long long)gj * g.nn[0] + gi : 0;
+  }
+  auto xval = [&](int q, int kk) { return xin[q] && kk >= 1 && kk <= ni2 ? X[(kk - 1) * xpl + xoff[q]] : 0.0; };
+  double* const csf = &cs[0][0];
+  double duy = 0, dyy = 0;
   int s0 = 0, s1 = 1, s2 = 2;  // slots of planes k-1, k, k+1
-  load_plane(k0 - 1, s0);
-  load_plane(k0, s1);
-  load_plane(k0 + 1, s2);
-  for (int k = k0; k <= k1; ++k) {
-    __syncthreads();  // planes loaded; the previous plane's cs no longer read
-    for (int h = threadIdx.x; h < HX * HY; h += VTX * VTY) {
-      int gi, gj;
-      hnode(h, gi, gj);
-      cs[h / HX][h % HX] = c[((long long)k * g.nn[1] + gj) * g.nn[0] + gi] * xs[s1][h / HX][h % HX];
+  const long long cown = mine ? (long long)j * g.nn[0] + i : 0, yown = mine ? (long long)(j - 1) * g.px + (i - 1) : 0;
+  double cm = c[(k0 - 1) * npl + cown], cp = c[(k0 + 1) * npl + cown], c1 = c[k0 * npl + cown];
+  double un = u[(k0 - 1) * xpl + yown];
+#pragma unroll
+  for (int q = 0; q < NH; ++q) {
+    const int h = threadIdx.x + q * VTX * VTY;
+    const double a = xval(q, k0 - 1), b = xval(q, k0), d = xval(q, k0 + 1), cq = c[k0 * npl + coff[q]];
+    if (used[q]) {
+      (&xs[s0][0][0])[h] = a;
+      (&xs[s1][0][0])[h] = b;
+      (&xs[s2][0][0])[h] = d;
+      csf[h] = cq * b;
     }
-    __syncthreads();
+  }
+  __syncthreads();
+  for (int k = k0; k <= k1; ++k) {
+    // the next plane's values on their way while this one is summed
+    double xn[NH], cn[NH], cnext = 0, unext = 0;
+    const bool more = k < k1;
+    if (more) {
+#pragma unroll
+      for (int q = 0; q < NH; ++q) {
+        xn[q] = xval(q, k + 2);
+        cn[q] = c[(k + 1) * npl + coff[q]];
+      }
+      cnext = c[(k + 2) * npl + cown];
+      unext = u[k * xpl + yown];
+    }
     if (mine) {
       const int hx = lx + 1, hy = ly + 1;
       const double (*pm)[HX] = xs[s0];
@@ -907,19 +902,102 @@ __global__ void __launch_bounds__(VTX * VTY) k_vapply_tile(Geom g, Weights w, co
       lv += w.ce[0] * (pc[hy - 1][hx - 1] + pc[hy - 1][hx + 1] + pc[hy + 1][hx - 1] + pc[hy + 1][hx + 1]);
       lv += w.ce[1] * (pm[hy][hx - 1] + pm[hy][hx + 1] + pp[hy][hx - 1] + pp[hy][hx + 1]);
       lv += w.ce[2] * (pm[hy - 1][hx] + pm[hy + 1][hx] + pp[hy - 1][hx] + pp[hy + 1][hx]);
-      const long long b0 = ((long long)k * g.nn[1] + j) * g.nn[0] + i;
       double mv = w.m0 * cs[hy][hx] + w.m1 * (cs[hy][hx - 1] + cs[hy][hx + 1] + cs[hy - 1][hx] + cs[hy + 1][hx]);
-      mv += w.m1 * (c[b0 - npl] * pm[hy][hx] + c[b0 + npl] * pp[hy][hx]);
-      y[((long long)(k - 1) * ni1 + (j - 1)) * g.px + (i - 1)] = mv - lv;
+      mv += w.m1 * (cm * pm[hy][hx] + cp * pp[hy][hx]);
+      const double out = mv - lv;
+      y[(k - 1) * xpl + yown] = out;
+      duy += un * out;
+      dyy += out * out;
     }
-    if (k < k1) {
-      __syncthreads();  // slot s0 (plane k-1) no longer read
-      load_plane(k + 2, s0);
+    if (more) {
+      __syncthreads();  // slot s0 (plane k-1) and cs no longer read
+#pragma unroll
+      for (int q = 0; q < NH; ++q) {
+        const int h = threadIdx.x + q * VTX * VTY;
+        if (used[q]) {
+          (&xs[s0][0][0])[h] = xn[q];
+          csf[h] = cn[q] * (&xs[s2][0][0])[h];
+        }
+      }
+      cm = c1;
+      c1 = cp;
+      cp = cnext;
+      un = unext;
       const int tmp = s0;
       s0 = s1;
       s1 = s2;
       s2 = tmp;
+      __syncthreads();
     }
+  }
+  __shared__ double red[2][VTX * VTY / 64];
+  for (int m = 32; m >= 1; m >>= 1) {
+    duy += __shfl_xor(duy, m, 64);
+    dyy += __shfl_xor(dyy, m, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = duy;
+    red[1][threadIdx.x >> 6] = dyy;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    double r = red[threadIdx.x][0];
+    for (int q = 1; q < VTX * VTY / 64; ++q) r += red[threadIdx.x][q];
+    part[(long long)threadIdx.x * gridDim.x + blockIdx.x] = r;
+  }
+}
+
+// The V-solve's start from V = 0 inside: r = rh = p = src - A V with V = Q on the face interiors
+// (src may be null), and part[b], work-group b's part of <r, r>.  Only the layer next to the
+// boundary has stencils to sum; the rest is a sweep over the vectors.  128^3: 79 us for the
+// general stencil over zeros and 30 for the sweeps after it, 29 here.
+template <int DIM>
+__global__ void __launch_bounds__(TPB)
+    k_vstart(Geom g, Weights w, long long n, const double* __restrict__ Q, const double* __restrict__ c,
+             const double* __restrict__ src, double* __restrict__ r, double* __restrict__ rh,
+             double* __restrict__ p, double* __restrict__ part) {
+  __shared__ double red[TPB / 64];
+  double rr = 0;
+  for (long long e = blockIdx.x * (long long)TPB + threadIdx.x; e < n; e += (long long)gridDim.x * TPB) {
+    const long long row = e / g.px;
+    const int i = (int)(e - row * g.px) + 1;
+    const int k = DIM == 3 ? (int)(row / g.ni[1]) + 1 : 0;
+    const int j = (int)(row - (DIM == 3 ? (long long)(k - 1) * g.ni[1] : 0)) + 1;
+    double v = 0;
+    if (i <= g.ni[0]) {
+      double lv = 0, mv = 0;
+      const int pos[3] = {i, j, k};
+#pragma unroll
+      for (int f = 0; f < 2 * DIM; ++f) {
+        const int ax = f >> 1, sd = f & 1 ? 1 : -1;
+        if (pos[ax] != (sd > 0 ? g.ni[ax] : 1)) continue;
+#pragma unroll
+        for (int o = 0; o < 2 * DIM - 1; ++o) {  // the node in the face, and its neighbours there
+          int d[3] = {0, 0, 0};
+          d[ax] = sd;
+          if (o) {
+            const int b = (o - 1) >> 1, tr = b < ax ? b : b + 1;
+            d[tr] = (o - 1) & 1 ? 1 : -1;
+            if (pos[tr] + d[tr] < 1 || pos[tr] + d[tr] > g.ni[tr]) continue;  // edges and corners are zero
+          }
+          const double vq = Q[qidx<DIM>(g, i + d[0], j + d[1], k + d[2])];
+          lv += lw<DIM>(w, d[0], d[1], d[2]) * vq;
+          if (!o) mv += w.m1 * c[nod(g, i + d[0], j + d[1], k + d[2])] * vq;
+        }
+      }
+      v = (src ? src[e] : 0.0) + lv - mv;
+    }
+    r[e] = v;
+    rh[e] = v;
+    p[e] = v;
+    rr += v * v;
+  }
+  for (int m = 32; m >= 1; m >>= 1) rr += __shfl_xor(rr, m, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = rr;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int q = 1; q < TPB / 64; ++q) rr += red[q];
+    part[blockIdx.x] = rr;
   }
 }
 
@@ -1343,20 +1421,43 @@ int setup_face_alpha(const Geom& g, const double* alpha, double* af64, float* af
   return ST_OK;
 }
 
-int vapply(const Geom& g, const Weights& w, const double* X, const double* Q, const double* c, const double* src,
-           double* y, hipStream_t st) {
+namespace {
+// Tiles of k_vapply_tile: chunks of 32 planes, shorter until two work-groups of 512 threads meet
+// on every compute unit.
+long long vapply_tiles(const Geom& g, int* kchunk) {
+  const long long cols = (long long)((g.ni[0] + VTX - 1) / VTX) * ((g.ni[1] + VTY - 1) / VTY);
+  *kchunk = (int)std::max<long long>(4, std::min<long long>(32, cols * g.ni[2] / 512));
+  return cols * ((g.ni[2] + *kchunk - 1) / *kchunk);
+}
+}  // namespace
+
+int vapply_dot_blocks(const Geom& g) {
+  int kchunk;
+  return g.dim == 3 && g.nb == 1 ? (int)std::min<long long>(vapply_tiles(g, &kchunk), 1 << 30) : 0;
+}
+
+int vapply_dot(const Geom& g, const Weights& w, const double* X, const double* c, double* y, const double* u,
+               double* part, hipStream_t st) {
+  if (g.nb != 1 || g.dim != 3) return ST_UNSUPPORTED;
+  // (the row padding of y is never written: the callers' output arrays keep it zero)
+  int kchunk;
+  const long long tiles = vapply_tiles(g, &kchunk);
+  hipLaunchKernelGGL(k_vapply_tile, dim3((unsigned)tiles), dim3(VTX * VTY), 0, st, g, w, X, c, y, kchunk, u, part);
+  AHOC_HIP_TRY(hipGetLastError());
+  return ST_OK;
+}
+
+int vapply(const Geom& g, const Weights& w, const double* X, const double* c, double* y, hipStream_t st) {
+  if (g.nb != 1 || g.dim != 2) return ST_UNSUPPORTED;
+  hipLaunchKernelGGL(k_vapply, dim3(interior_rows(g)), dim3(TPB), 0, st, g, w, X, c, y);
+  AHOC_HIP_TRY(hipGetLastError());
+  return ST_OK;
+}
+
+int vstart(const Geom& g, const Weights& w, long long n, const double* Q, const double* c, const double* src, double* r,
+           double* rh, double* p, double* part, int nb, hipStream_t st) {
   if (g.nb != 1) return ST_UNSUPPORTED;
-  if (g.dim == 3 && !Q && !src) {
-    // (the row padding of y is never written: the callers' output arrays keep it zero); chunks
-    // of 32 planes, shorter until two work-groups of 512 threads meet on every compute unit
-    const long long cols = (long long)((g.ni[0] + VTX - 1) / VTX) * ((g.ni[1] + VTY - 1) / VTY);
-    const int kchunk = (int)std::max<long long>(4, std::min<long long>(32, cols * g.ni[2] / 512));
-    const long long tiles = cols * ((g.ni[2] + kchunk - 1) / kchunk);
-    hipLaunchKernelGGL(k_vapply_tile, dim3((unsigned)tiles), dim3(VTX * VTY), 0, st, g, w, X, c, y, kchunk);
-    AHOC_HIP_TRY(hipGetLastError());
-    return ST_OK;
-  }
-  LAUNCH_DIM(k_vapply, dim3(interior_rows(g)), g, w, X, Q, c, src, y);
+  LAUNCH_DIM(k_vstart, dim3(nb), g, w, n, Q, c, src, r, rh, p, part);
   return ST_OK;
 }
 
