@@ -470,21 +470,21 @@ template <typename T> int prec_init(ahoc_handle* h, Prec<T>& P, int tile_opt, hi
     // (s, layer sine, face weight low, high) per position of the slowest axis, from the
     // tables above
     TRY(upload(h, &P.ptab, pt, st));
-    if (face_jobs_pay(g)) {
-      const long long sx = g.dim == 3 ? 2LL * g.ni[1] * g.ni[2] : 2LL * g.nb * g.ni[1];
-      const long long sy[2] = {g.dim == 3 ? 2LL * g.px * g.ni[2] : 2LL * g.nb * g.px,
-                               g.dim == 3 ? 2LL * g.ni[0] * g.ni[2] : 2LL * g.nb * g.px};
-      const long long sz = g.dim == 3 ? 2LL * g.px * g.ni[1] : 0;
-      for (int k = 0; k < 2; ++k) {
-        const long long n = sx + sy[k] + sz;
-        TRY(alloc_t(h, &P.ft[k][0], n));
-        P.ft[k][1] = P.ft[k][0] + sx;
-        P.ft[k][2] = P.ft[k][1] + sy[k];
-        AHOC_HIP_TRY(hipMemsetAsync(P.ft[k][0], 0, sizeof(T) * n, st));  // zero row padding
-      }
-    }
     const long long inner = g.dim == 3 ? (long long)g.px * g.ni[1] : g.px;
     P.mspec = dst_pipe_mpass_ok<T>(g.n[t], inner, g.px, mspec_gen<T>(g, P));
+  }
+  if (P.spectral && face_jobs_pay(g)) {  // (the sixth-order chain has only the first set)
+    const long long sx = g.dim == 3 ? 2LL * g.ni[1] * g.ni[2] : 2LL * g.nb * g.ni[1];
+    const long long sy[2] = {g.dim == 3 ? 2LL * g.px * g.ni[2] : 2LL * g.nb * g.px,
+                             g.dim == 3 ? 2LL * g.ni[0] * g.ni[2] : 2LL * g.nb * g.px};
+    const long long sz = g.dim == 3 ? 2LL * g.px * g.ni[1] : 0;
+    for (int k = 0; k < (h->tri ? 1 : 2); ++k) {
+      const long long n = sx + sy[k] + sz;
+      TRY(alloc_t(h, &P.ft[k][0], n));
+      P.ft[k][1] = P.ft[k][0] + sx;
+      P.ft[k][2] = P.ft[k][1] + sy[k];
+      AHOC_HIP_TRY(hipMemsetAsync(P.ft[k][0], 0, sizeof(T) * n, st));  // zero row padding
+    }
   }
   TRY(alloc_int(h, &P.bufA, st));
   TRY(alloc_int(h, &P.bufB, st));
@@ -852,7 +852,8 @@ int vsolve_spec(ahoc_handle* h, Prec<T>& P, const T* Q, hipStream_t st, bool ski
     tend(h, AHOC_K_LIFT, e, (double)TQ(g) * 2.0 * sizeof(T), st);
   }
   const double pass_bytes = 2.0 * (double)g.nint * g.nb * sizeof(T);
-  T* buf = P.bufA;
+  const bool planes = P.planes && dst_get_variant() == 0 && !skip_x && !addv;
+  T* buf = planes ? P.scr : P.bufA;
   DstGen<T> gen;
   gen.wa = P.wl[0];
   gen.nwa = g.ni[0];
@@ -882,6 +883,12 @@ int vsolve_spec(ahoc_handle* h, Prec<T>& P, const T* Q, hipStream_t st, bool ski
     TRY(dst_gen_pass<T>(P.tb[1], buf, g.nb, g.px, P.scV, gen, st));
   }
   tend(h, AHOC_K_DST_GEN, eg, (double)g.nint * g.nb * sizeof(T), st);
+  if (planes) {
+    hipEvent_t ev = tbegin(h, st);
+    TRY((dst_plane_pass<T, T, T>(P.tb[0], P.tb[1], buf, g.px, P.bufA, g.px, g.ni[2], st)));
+    tend(h, AHOC_K_DST_ROWS, ev, pass_bytes, st);
+    return ST_OK;
+  }
   auto run = [&](int kind, const DstTables<T>& tb, long long outer, long long inner, int tile) -> int {
     hipEvent_t ev = tbegin(h, st);
     const int rc = dst_pass<T>(tb, buf, buf, outer, inner, g.px, nullptr, tile, st);
