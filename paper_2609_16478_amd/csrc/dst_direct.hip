@@ -161,6 +161,20 @@ template <typename T> struct SineArgs {
 template <typename T, bool ROWS, int TP> constexpr int sine_half(int mc) {
   return ROWS ? 16 * TP * (mc + SineOps<T>::PAD) : mc * (TP == 1 ? 16 : 16 * TP + 16);
 }
+// lambda = A + B s_this of column `col`
+template <typename T> __device__ __forceinline__ void sine_lambda(const DstScale<T>& fs, long long col, bool in, T* A, T* B) {
+  const long long ib = col / fs.na;
+  const long long ia = col - ib * fs.na;
+  *A = 1;
+  *B = 0;
+  if (in && ia < fs.nva) {
+    const T sa = fs.s_a[ia];
+    const T sb = fs.s_b ? fs.s_b[ib] : T(0);
+    *A = sa + sb + fs.c_ab * sa * sb + fs.a0 + fs.ka * sa + fs.kb * sb;
+    *B = T(1) + fs.c_ta * sa + fs.c_tb * sb + fs.kt;
+  }
+}
+
 // The outputs of TO pairs per KS wavefronts, from pair `first` on, of tile `tile` of 16 TP
 // pencils.  KS wavefronts take every KS-th step of the sum over m and add their sums up at the
 // end (in wavefront order): where a pass has so few pencils that most of the chip is idle, its
@@ -336,15 +350,8 @@ __device__ __forceinline__ void sine_tile(const SineArgs<T>& a, const DstScale<T
     T A = 1, B = 0, sc = 1;
     if (!ROWS && scaled) {
       const long long col = c0 + 16 * b + li;
-      const long long ib = col / fs.na;
-      const long long ia = col - ib * fs.na;
       sc = fs.scale;
-      if (col < a.inner && ia < fs.nva) {
-        const T sa = fs.s_a[ia];
-        const T sb = fs.s_b ? fs.s_b[ib] : T(0);
-        A = sa + sb + fs.c_ab * sa * sb + fs.a0 + fs.ka * sa + fs.kb * sb;
-        B = T(1) + fs.c_ta * sa + fs.c_tb * sb + fs.kt;
-      }
+      sine_lambda<T>(fs, col, col < a.inner, &A, &B);
     }
 #pragma unroll
     for (int t = 0; t < TO; ++t) {
@@ -366,6 +373,104 @@ __device__ __forceinline__ void sine_tile(const SineArgs<T>& a, const DstScale<T
   }
 }
 
+// The same for N <= SINE_CHAIN_N, one pair of 16 odd and 16 even outputs of 16 pencils per
+// work-group: each of the four wavefronts has its quarter of the sum, C steps of four m, straight
+// from memory in registers, all in flight with the period table, and no tile to stage and wait
+// for.  The faces of 128^3, 6 passes in a launch: 6.6 -> 5.0 us in FP64, 6.2 -> 5.2 in FP32.  From
+// N of about 300 the rows' 32-byte pieces cost more than the staging: 500 x 300 points in FP64
+// 13.6 us against 11.5 along x, 9.2 against 9.1 along y.
+constexpr int SINE_CHAIN_N = 256;
+template <typename T, bool ROWS, int C>
+__device__ __forceinline__ void sine_chain(const SineArgs<T>& a, const DstScale<T>& fs, bool scaled, long long tile,
+                                           int pair) {
+  using S = SineOps<T>;
+  using v4 = typename S::v4;
+  extern __shared__ __align__(16) unsigned char smem[];
+  T* red = reinterpret_cast<T*>(smem);  // [wavefront][value][lane]
+  T* tab = red + 4 * 8 * 64;
+  const int N = a.N, L = N - 1, Hm = N / 2, two_n = 2 * N;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  long long base, c0 = 0;
+  int ncols;
+  if (ROWS) {
+    base = tile * 16 * a.pitch;
+    ncols = (int)min(16LL, a.outer - tile * 16);
+  } else {
+    const long long o = tile / a.ntile_inner;
+    c0 = (tile - o * a.ntile_inner) * 16;
+    base = o * (long long)L * a.inner + c0;
+    ncols = (int)min(16LL, a.inner - c0);
+  }
+  constexpr int TU = C / 4;  // 2 N <= 256 TU
+  T tv[TU];
+#pragma unroll
+  for (int u = 0; u < TU; ++u) tv[u] = sine_entry<T>(a.sn, N, a.half, min((int)threadIdx.x + u * 256, two_n - 1));
+  const int quarter = (Hm + 15) / 16 * 4, m0 = w * quarter;  // this wavefront's m: m0 + 1 ..
+  // bytes within the tile's slab or rows (below 4 GiB: the rule of the dispatch)
+  const unsigned sm = (ROWS ? 1u : (unsigned)a.inner) * sizeof(T);
+  const unsigned sp = (unsigned)min(li, ncols - 1) * (ROWS ? (unsigned)a.pitch * (unsigned)sizeof(T) : (unsigned)sizeof(T));
+  const char* src = reinterpret_cast<const char*>(a.in + base);
+  auto at = [&](int row) { return *reinterpret_cast<const T*>(src + (row * sm + sp)); };
+  unsigned k = 32u * pair + 2u * li + 1u;
+  const unsigned ke = (int)k < N ? k : 0u, ko = (int)k + 1 < N ? k + 1u : 0u;
+  unsigned ie = ke * (unsigned)(m0 + 1 + lk) % two_n, io = ko * (unsigned)(m0 + 1 + lk) % two_n;
+  const unsigned de = 4u * ke % two_n, dd = 4u * ko % two_n;
+  v4 ae = v4{T(0), T(0), T(0), T(0)}, ao = ae;
+  for (int s0 = 0; s0 < quarter; s0 += 4 * C) {
+    T x[C], y[C];
+#pragma unroll
+    for (int s = 0; s < C; ++s) {
+      const int m = min(m0 + s0 + 4 * s + lk + 1, Hm);
+      x[s] = at(m - 1);
+      y[s] = at(N - m - 1);
+    }
+    if (s0 == 0) {
+#pragma unroll
+      for (int u = 0; u < TU; ++u) {
+        const int i = threadIdx.x + u * 256;
+        if (i < two_n) tab[sine_pad(i)] = tv[u];
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int s = 0; s < C; ++s) {
+      const int q = s0 + 4 * s, m = m0 + q + lk + 1;
+      const bool ok = q < quarter && m <= Hm;
+      const T vs = 2 * m == N ? T(0) : y[s];
+      const T e = ok ? x[s] + vs : T(0), o = ok ? x[s] - vs : T(0);
+      const T se = tab[sine_pad(ie)], so = tab[sine_pad(io)];
+      ie = min(ie + de, ie + de - two_n);
+      io = min(io + dd, io + dd - two_n);
+      ae = ROWS ? S::mfma(e, se, ae) : S::mfma(se, e, ae);
+      ao = ROWS ? S::mfma(o, so, ao) : S::mfma(so, o, ao);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    red[(w * 8 + r) * 64 + lane] = ae[r];
+    red[(w * 8 + 4 + r) * 64 + lane] = ao[r];
+  }
+  __syncthreads();
+  // wavefront w adds up and stores the results' element w
+  T ve = red[w * 64 + lane], vo = red[(4 + w) * 64 + lane];
+#pragma unroll
+  for (int q = 1; q < 4; ++q) {
+    ve += red[(q * 8 + w) * 64 + lane];
+    vo += red[(q * 8 + 4 + w) * 64 + lane];
+  }
+  const int p = ROWS ? S::row(lk, w) : li, kk = 32 * pair + 2 * (ROWS ? li : S::row(lk, w));  // positions kk, kk + 1
+  if (p >= ncols) return;
+  if (!ROWS && scaled) {
+    T A, B;
+    sine_lambda<T>(fs, c0 + li, true, &A, &B);
+    if (kk < L) ve *= fs.scale / (A + B * fs.s_this[kk]);
+    if (kk + 1 < L) vo *= fs.scale / (A + B * fs.s_this[kk + 1]);
+  }
+  T* op = a.out + base + (ROWS ? p * a.pitch + kk : (long long)kk * a.inner + p);
+  if (kk < L) op[0] = ve;
+  if (kk + 1 < L) op[ROWS ? 1 : a.inner] = vo;
+}
+
 // grid.x: tiles; grid.y: groups of blockDim.x / 64 / KS * TO output pairs (one group in place)
 template <typename T, bool ROWS, int TO, int TP, int KS>
 __global__ void __launch_bounds__(KS > 1 ? 256 : 1024) k_dst_sine(SineArgs<T> a, DstScale<T> fs, int scaled, int mc) {
@@ -373,9 +478,15 @@ __global__ void __launch_bounds__(KS > 1 ? 256 : 1024) k_dst_sine(SineArgs<T> a,
                                  gridDim.y == 1, mc);
 }
 
+// grid.x: tiles; grid.y: output pairs
+template <typename T, bool ROWS, int C>
+__global__ void __launch_bounds__(256) k_dst_sine_chain(SineArgs<T> a, DstScale<T> fs, int scaled) {
+  sine_chain<T, ROWS, C>(a, fs, scaled != 0, blockIdx.x, blockIdx.y);
+}
+
 // Several passes in one launch (the faces of a grid: a few thousand pencils in up to six
 // arrays, whose separate launches each cost more than their work).  Work-groups of four
-// wavefronts, 128 / KS outputs of 16 pencils each.
+// wavefronts, 128 / KS outputs of 16 pencils each (CHAIN: its steps in flight, else 0).
 constexpr int SINE_JOBS_MAX = 6;
 template <typename T> struct SineJobs {
   SineArgs<T> job[SINE_JOBS_MAX];
@@ -383,11 +494,13 @@ template <typename T> struct SineJobs {
   int groups[SINE_JOBS_MAX];  // output groups of a tile
   int mc;
 };
-template <typename T, bool ROWS, int KS> __global__ void __launch_bounds__(256) k_dst_sine_jobs(SineJobs<T> s) {
+template <typename T, bool ROWS, int KS, int CHAIN>
+__global__ void __launch_bounds__(256) k_dst_sine_jobs(SineJobs<T> s) {
   int j = 0;
   while ((int)blockIdx.x >= s.end[j]) ++j;
   const int b = (int)blockIdx.x - (j ? s.end[j - 1] : 0), g = s.groups[j];
-  sine_tile<T, ROWS, 1, 1, KS>(s.job[j], DstScale<T>(), false, b / g, b % g * (4 / KS), false, s.mc);
+  if constexpr (CHAIN) sine_chain<T, ROWS, CHAIN>(s.job[j], DstScale<T>(), false, b / g, b % g);
+  else sine_tile<T, ROWS, 1, 1, KS>(s.job[j], DstScale<T>(), false, b / g, b % g * (4 / KS), false, s.mc);
 }
 
 constexpr size_t DIRECT_LDS_MAX = 160 * 1024;
@@ -423,6 +536,12 @@ int sine_mc(int N, int P, bool chain) {
   return mc;
 }
 
+template <typename T> size_t sine_chain_lds(int N) { return sizeof(T) * (4 * 8 * 64 + (size_t)sine_pad(2 * N)); }
+// Offsets within 16 rows stay below 4 GiB
+template <typename T> bool sine_chain_ok(const SineArgs<T>& a, bool rows) {
+  return a.N <= SINE_CHAIN_N && (!rows || a.pitch < (1 << 24)) && (rows || a.inner < (1 << 18));
+}
+
 template <typename T, bool ROWS, int TO, int TP, int KS = 1>
 int sine_launch(const SineArgs<T>& a, const DstScale<T>* fs, long long tiles, int groups, int waves, hipStream_t st) {
   if (tiles > 0x7fffffffLL || groups > 65535) return ST_UNSUPPORTED;
@@ -432,6 +551,18 @@ int sine_launch(const SineArgs<T>& a, const DstScale<T>* fs, long long tiles, in
   TRY_ST(sine_lds(&k_dst_sine<T, ROWS, TO, TP, KS>, lds, once));
   hipLaunchKernelGGL((k_dst_sine<T, ROWS, TO, TP, KS>), dim3((unsigned)tiles, (unsigned)groups), dim3(64 * waves),
                      lds, st, a, fs ? *fs : DstScale<T>(), fs ? 1 : 0, mc);
+  AHOC_HIP_TRY(hipGetLastError());
+  return ST_OK;
+}
+
+template <typename T, bool ROWS>
+int sine_chain_launch(const SineArgs<T>& a, const DstScale<T>* fs, long long tiles, int pairs, hipStream_t st) {
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles, (unsigned)pairs), dim3(256), sine_chain_lds<T>(a.N), st, a,
+                       fs ? *fs : DstScale<T>(), fs ? 1 : 0);
+  };
+  if (a.N <= 128) launch(k_dst_sine_chain<T, ROWS, 4>);
+  else launch(k_dst_sine_chain<T, ROWS, 8>);
   AHOC_HIP_TRY(hipGetLastError());
   return ST_OK;
 }
@@ -450,8 +581,10 @@ int sine_pass(SineArgs<T>& a, const DstScale<T>* fs, bool disjoint, hipStream_t 
   };
   if (disjoint && pairs > 64) return sine_launch<T, ROWS, 2, 2>(a, fs, tiles(32), (pairs + 15) / 16, 8, st);
   if (disjoint && pairs > 1 && tiles(16) < 512) {
-    if (a.N <= 1024 && tiles(16) * ((pairs + 3) / 4) < SINE_CHAIN_WGS)
+    if (a.N <= 1024 && tiles(16) * ((pairs + 3) / 4) < SINE_CHAIN_WGS) {
+      if (sine_chain_ok(a, ROWS)) return sine_chain_launch<T, ROWS>(a, fs, tiles(16), pairs, st);
       return sine_launch<T, ROWS, 1, 1, 4>(a, fs, tiles(16), pairs, 4, st);
+    }
     if (pairs > 4) return sine_launch<T, ROWS, 1, 1>(a, fs, tiles(16), (pairs + 3) / 4, 4, st);
   }
   if (pairs > 64) return ST_UNSUPPORTED;  // in place: one work-group holds every output of a tile
@@ -469,8 +602,17 @@ template <typename T, bool ROWS, int KS> int sine_jobs_launch(SineJobs<T>& s, in
   s.mc = sine_mc(nmax, 16, KS > 1);
   const size_t lds = sine_lds_bytes<T, ROWS, 1>(nmax, s.mc);
   static std::once_flag once;
-  TRY_ST(sine_lds(&k_dst_sine_jobs<T, ROWS, KS>, lds, once));
-  hipLaunchKernelGGL((k_dst_sine_jobs<T, ROWS, KS>), dim3(blocks), dim3(256), lds, st, s);
+  TRY_ST(sine_lds(&k_dst_sine_jobs<T, ROWS, KS, 0>, lds, once));
+  hipLaunchKernelGGL((k_dst_sine_jobs<T, ROWS, KS, 0>), dim3(blocks), dim3(256), lds, st, s);
+  AHOC_HIP_TRY(hipGetLastError());
+  return ST_OK;
+}
+template <typename T, bool ROWS> int sine_jobs_chain(SineJobs<T>& s, int blocks, int nmax, hipStream_t st) {
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), sine_chain_lds<T>(nmax), st, s);
+  };
+  if (nmax <= 128) launch(k_dst_sine_jobs<T, ROWS, 4, 4>);
+  else launch(k_dst_sine_jobs<T, ROWS, 4, 8>);
   AHOC_HIP_TRY(hipGetLastError());
   return ST_OK;
 }
@@ -569,6 +711,8 @@ template <typename T> int dst_sine_jobs(const SineJob<T>* jobs, int count, hipSt
       nmax = std::max(nmax, a.N);
     }
     const bool chain = wg < SINE_CHAIN_WGS;
+    bool direct = chain;
+    for (int j = 0; j < n; ++j) direct = direct && sine_chain_ok(s.job[j], rows);
     long long blocks = 0;
     for (int j = 0; j < SINE_JOBS_MAX; ++j) {
       if (!chain) s.groups[j] = (s.groups[j] + 3) / 4;
@@ -577,7 +721,8 @@ template <typename T> int dst_sine_jobs(const SineJob<T>* jobs, int count, hipSt
       s.end[j] = (int)blocks;
     }
     if (blocks == 0) continue;
-    if (rows) TRY_ST(chain ? sine_jobs_launch<T, true, 4>(s, (int)blocks, nmax, st) : sine_jobs_launch<T, true, 1>(s, (int)blocks, nmax, st));
+    if (direct) TRY_ST((rows ? sine_jobs_chain<T, true>(s, (int)blocks, nmax, st) : sine_jobs_chain<T, false>(s, (int)blocks, nmax, st)));
+    else if (rows) TRY_ST(chain ? sine_jobs_launch<T, true, 4>(s, (int)blocks, nmax, st) : sine_jobs_launch<T, true, 1>(s, (int)blocks, nmax, st));
     else TRY_ST(chain ? sine_jobs_launch<T, false, 4>(s, (int)blocks, nmax, st) : sine_jobs_launch<T, false, 1>(s, (int)blocks, nmax, st));
   }
   return ST_OK;
