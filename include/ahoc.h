@@ -93,7 +93,7 @@ typedef struct {
   int n[3];      /* intervals per axis, 4 <= n[a] <= 8192 (unused axis ignored); the
                     one-sided normal formula of Sec. 2.2 reads U_1..U_3, so n[a] >= 4.
                     Lengths with radix-2/3 factors use the FFT passes, any other length
-                    a direct sine-sum pass (O(n) work per output)                 */
+                    sine products on the matrix cores (O(n) work per output)      */
   double lo[3];
   double hi[3];
   const double* alpha;
@@ -357,7 +357,9 @@ enum {
                               inverted along the slowest axis (writes the volume only)     */
   AHOC_K_FACE_REDUCE = 10, /* U-solve: face sums along the two fastest axes from the stored
                               scaled spectrum (reads the volume only)                      */
-  AHOC_K_PRECOND = 11,     /* one application of the boundary-symbol preconditioner       */
+  AHOC_K_PRECOND = 11,     /* one application of the boundary-symbol preconditioner (on
+                              square 2-D grids of up to 1024 intervals the operator's first
+                              launch applies it: timed as AHOC_K_LIFT)                  */
   AHOC_K_VSOLVE = 12,      /* variable beta: one BiCGSTAB V-solve with its transform solves
                               and stencil applications (bytes not modelled)               */
   AHOC_K_DST_XMUL = 13,    /* 3-D matvec: the V-solve's inverse and the U-solve's forward
