@@ -21,7 +21,9 @@
 //
 // A Dirichlet solve, separate passes against planes: 128^3 97 -> 64 us in FP64 and 74 -> 51 in
 // FP32, 99 x 89 x 74 points 61 -> 51 and 54 -> 38, 64^3 38 -> 23 and 36 -> 22, 32^3 34 -> 19
-// and 33 -> 19; with the slowest axis below 48^3 122 -> 20 and 120 -> 18.  A pass at 128^3 in
+// and 33 -> 19; with the slowest axis below 48^3 122 -> 20 and 120 -> 18.  FP32 errors against 64
+// bits (rms of a solve): 128^3 6.7e-7 -> 5.1e-7, 64^3 4.8e-7 -> 3.0e-7, 99 x 89 x 74 points 4.0e-7
+// -> 3.6e-7.  A pass at 128^3 in
 // FP64 takes 20 us: 7 of matrix-core time, 5 of the other vector instructions, 3 of LDS and the
 // trips to memory, in phases that the two work-groups of a CU run side by side.
 #include "common.h"
@@ -310,8 +312,10 @@ __global__ void __launch_bounds__(256)
 template <typename T>
 int dst_solve_axis(const DstTables<T>& tb, T* data, long long inner, long long pitch, const DstScale<T>& fs, int tile,
                    T* tmp, hipStream_t st) {
-  // a length-specialised FFT kernel stays ahead (128^3 in FP64: 18 us)
-  if (tb.N > DST_PLANE_MAX_N || dst_fast_supported(tb.N))
+  // The length-specialised FFT kernel is ahead from 128 on, its pass longer below: a solve, FFT
+  // against products here, 128^3 63.3 and 66.0 us in FP64, 50.7 and 52.9 in FP32; 96^3 53.3 and
+  // 50.4, 44.0 and 37.0; 64^3 22.2 and 21.4, 21.5 and 18.4; 32^3 18.0 and 16.6, 18.6 and 16.6.
+  if (tb.N > DST_PLANE_MAX_N || (tb.N > 96 && dst_fast_supported(tb.N)))
     return dst_pass<T>(tb, data, data, 1, inner, pitch, &fs, tile, st, nullptr, tmp);
   if (tb.N < 4 || !tb.sn || !data || inner < 1) return ST_INVALID;
   const long long blocks = (inner + 15) / 16;

@@ -1,6 +1,7 @@
 """3-D Dirichlet solves with both axes of a plane in one launch, at the edges of its tiles (16
 columns of x, 32 outputs of either parity of y, eight planes per turn of the XCDs) and on both
-sides of its rule (128 in, 129 out in either axis): against the oracle, and against the same
+sides of its rule (128 in, 129 out in either axis; the slowest axis as products to 96 and where
+no FFT kernel is specialised on its length): against the oracle, and against the same
 solve as separate passes (variant 5).  Bars of the other Poisson parity tests."""
 import numpy as np
 import pytest
@@ -22,7 +23,8 @@ def ah():
 
 @pytest.mark.parametrize("n", [(4, 4, 4), (5, 33, 9), (17, 16, 10), (33, 5, 34), (32, 65, 17), (64, 64, 8), (65, 31, 5),
                                (66, 34, 12), (96, 97, 20), (99, 100, 7), (127, 128, 6), (128, 127, 24), (128, 4, 130),
-                               (129, 20, 9), (20, 129, 9)])
+                               (129, 20, 9), (20, 129, 9), (33, 20, 32), (20, 9, 64), (12, 30, 96), (9, 8, 97),
+                               (8, 8, 128)])
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_plane_poisson(ah, n, prec):
     lo, hi = (0.0,) * 3, (1.0, 0.7, 1.2)
