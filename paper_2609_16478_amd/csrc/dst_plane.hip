@@ -22,7 +22,7 @@
 // A Dirichlet solve, separate passes against planes: 128^3 97 -> 64 us in FP64 and 74 -> 51 in
 // FP32, 99 x 89 x 74 points 61 -> 51 and 54 -> 38, 64^3 38 -> 23 and 36 -> 22, 32^3 34 -> 19
 // and 33 -> 19; with the slowest axis below 48^3 122 -> 20 and 120 -> 18.  FP32 errors against 64
-// bits (rms of a solve): 128^3 6.7e-7 -> 5.1e-7, 64^3 4.8e-7 -> 3.0e-7, 99 x 89 x 74 points 4.0e-7
+// bits (rms of a solve): 128^3 5.8e-7 -> 5.1e-7, 64^3 3.7e-7 -> 3.0e-7, 99 x 89 x 74 points 4.0e-7
 // -> 3.6e-7.  A pass at 128^3 in
 // FP64 takes 20 us: 7 of matrix-core time, 5 of the other vector instructions, 3 of LDS and the
 // trips to memory, in phases that the two work-groups of a CU run side by side.
