@@ -530,14 +530,17 @@ __global__ void __launch_bounds__(NT) k_arnoldi_one(double* __restrict__ V, long
   for (int q = 0; q < EPT; ++q) nn += w[q] * w[q];
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) nn += __shfl_xor(nn, m, 64);
-  if (lane == 0) red[0][wv] = nn;  // the totals of the second sweep are read: a barrier ago
-  for (int i = threadIdx.x; i < nvec; i += NT) hs[i] += h1[i];
+  // red and h1 are free: their last reads, the totals of the second sweep and the update of the
+  // first, lie before a barrier that every wavefront has passed.  hs is not: a slower wavefront
+  // may still be in its second update, so the column is summed in h1.
+  if (lane == 0) red[0][wv] = nn;
+  for (int i = threadIdx.x; i < nvec; i += NT) h1[i] += hs[i];
   __syncthreads();
   nn = red[0][0];
 #pragma unroll
   for (int k = 1; k < NW; ++k) nn += red[0][k];
   nn = sqrt(fmax(nn, 0.0));
-  const bool still = rotate_and_update(a, sg, hs, l, nn);
+  const bool still = rotate_and_update(a, sg, h1, l, nn);
   const double r = nn > 0 && still ? 1.0 / nn : 0.0;
 #pragma unroll
   for (int q = 0; q < EPT; ++q)

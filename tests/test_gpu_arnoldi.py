@@ -57,3 +57,27 @@ def test_long_segments_in_a_batch(ah):
         with ah.Solver(p, tol=1e-11) as s:
             ref = s.solve()[0]
         assert float((u - ref).abs().max()) <= 1e-9 * max(float(ref.abs().max()), 1e-30)
+
+
+ROUGH = "1 + 0.95*sin(12*pi*x)*cos(10*pi*y)"
+
+
+@pytest.mark.parametrize("restart", [60, 200])
+@pytest.mark.parametrize("n,steps", [((130, 128), 32), ((258, 256), 64), ((514, 512), 64)])
+def test_more_vectors_than_the_registers_hold(ah, n, steps, restart):
+    """Long cycles (rough data, no preconditioner) whose basis outgrows the 32 or 16 vectors that
+    one work-group keeps in registers, and the 64 rows of one turn of the back substitution.  The
+    second Gram-Schmidt sweep and the sum of the two columns must not meet: with a column
+    subtracted twice the estimate leaves the residual by orders of magnitude.  Both carry the
+    operator's error of 1e-13 ||S|| ||q|| / ||b||, at most the condition number, which is below N."""
+    p = W.manufactured(ROUGH, U2, n, (0.0, 0.0), tuple(m / max(n) for m in n))
+    rng = np.random.default_rng(1)
+    p.f = rng.standard_normal(p.f.shape)
+    p.gN = rng.standard_normal(p.f.shape)
+    with ah.Solver(p, tol=1e-10, restart=restart, precond=0) as s:
+        b = s.schur_rhs()
+        _, _, q, st = s.solve(want_q=True)
+        r = float((b - s.schur_apply(q)).norm() / b.norm())
+    assert st.converged and st.schur_relres <= 1e-10
+    assert st.gmres_iters > min(steps, restart), st.gmres_iters
+    assert abs(r - st.schur_relres) <= 1e-13 * max(n), (r, st)
