@@ -562,14 +562,18 @@ int poisson(ahoc_handle* h, Prec<T>& P, T* buf, const DstScale<T>& sc, hipStream
   const T* src = in ? in : buf;
   T* cur = buf;
   bool first = true;
+  auto rows_lift = [&](T* out, long long rows) {  // the first pass with lf: from the source to `out`, padding zeroed
+    TRY(dst_rows_lift_pass<T>(P.tb[0].N, P.tb[0].tw, P.tb[0].sn, src, out, rows, g.px, *lf, st));
+    return src == out ? (int)ST_OK : zero_cols<T>(out, rows, g.ni[0], g.px, g.px, st);
+  };
   auto run = [&](int kind, const DstTables<T>& tb, long long outer, long long inner,
                  const DstScale<T>* f, int tile) -> int {
     hipEvent_t e = tbegin(h, st);
     T* other = P.scr ? (cur == buf ? P.scr : buf) : nullptr;
     if (!tb.ppt && !f && other) std::swap(cur, other);
     // with lf, the first (row) pass adds the lift's face layers to its input while loading
-    const int rc = (first && lf) ? dst_rows_lift_pass<T>(tb.N, tb.tw, tb.sn, src, cur, outer, g.px, *lf, st)
-                                 : dst_pass<T>(tb, src, cur, outer, inner, g.px, f, tile, st, nullptr, other);
+    const int rc = (first && lf) ? rows_lift(cur, outer)
+                                 : dst_pass<T>(tb, src, cur, outer, inner, g.px, f, tile, st, nullptr, other, g.px);
     first = false;
     src = cur;
     tend(h, kind, e, pass_bytes, st);
@@ -583,7 +587,7 @@ int poisson(ahoc_handle* h, Prec<T>& P, T* buf, const DstScale<T>& sc, hipStream
   } else if (P.planes && dst_get_variant() == 0) {
     hipEvent_t e = tbegin(h, st);
     if (lf) {
-      TRY(dst_rows_lift_pass<T>(P.tb[0].N, P.tb[0].tw, P.tb[0].sn, src, P.scr, (long long)g.ni[1] * g.ni[2], g.px, *lf, st));
+      TRY(rows_lift(P.scr, (long long)g.ni[1] * g.ni[2]));
       TRY(dst_pass<T>(P.tb[1], P.scr, P.scr, g.ni[2], g.px, g.px, nullptr, P.tile[1], st, nullptr, nullptr));
     } else {
       TRY((dst_plane_pass<T, T, T>(P.tb[0], P.tb[1], src, g.px, P.scr, g.px, g.ni[2], st)));
@@ -631,7 +635,7 @@ template <typename T> int poisson_dense(ahoc_handle* h, Prec<T>& P, const double
     TRY(dst_solve_axis<T>(P.tb[2], P.bufA, (long long)g.px * g.ni[1], g.px, P.scP, P.tile[2], P.scr, st));
     return dst_plane_pass<T, T, double>(P.tb[0], P.tb[1], P.bufA, g.px, wout, g.ni[0], g.ni[2], st);
   }
-  TRY((pitch_copy<double, T>(rows, g.ni[0], gin, g.ni[0], P.bufA, g.px, st)));
+  TRY((pitch_copy<double, T>(rows, g.ni[0], gin, g.ni[0], P.bufA, g.px, st, g.px)));  // with zero padding
   TRY(poisson<T>(h, P, P.bufA, P.scP, st));
   return pitch_copy<T, double>(rows, g.ni[0], P.bufA, g.px, wout, g.ni[0], st);
 }

@@ -219,11 +219,16 @@ int face_reduce(const T* W, long long planes, int ny, int nx, int px, const T* w
 // of L elements starting `pitch` elements apart.  tmp: optional array of out's size, apart
 // from in and out, that a fused pass of a length without an FFT plan keeps its scaled
 // spectrum in (a pass that writes elsewhere than it reads can split a pencil's outputs over
-// work-groups).
+// work-groups).  cols: columns that a row pass with in != out writes to each row, those from L
+// on as zeros (0: L alone).  Whatever fills a padded array has to write its padding: the strided
+// FFT passes pair the last column with it, in one complex sequence, and leave rounding noise (or
+// NaN) there, so that what an earlier call left would show in the next one's results.
 template <typename T>
 int dst_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long long inner,
              long long pitch, const DstScale<T>* fused, int tile_seqs, hipStream_t st,
-             const DstFaces<T>* faces = nullptr, T* tmp = nullptr);
+             const DstFaces<T>* faces = nullptr, T* tmp = nullptr, int cols = 0);
+// out[r * pitch + c] = 0 for lo <= c < hi, r < rows
+template <typename T> int zero_cols(T* out, long long rows, int lo, int hi, long long pitch, hipStream_t st);
 
 // Length-specialised kernels (dst_fast.hip) for N in {32, 64, 96, ..., 4096}.
 bool dst_fast_supported(int N);
@@ -302,7 +307,7 @@ int dst_gemm_hp(int N);
 template <typename T> std::vector<T> dst_gemm_table(const SineBase& b);
 template <typename T>
 int dst_gemm_pass(const T* S, int N, const T* in, T* out, long long outer, long long inner, long long pitch,
-                  hipStream_t st);
+                  hipStream_t st, int cols = 0);
 // Times the candidate kernels for the plain pass of this shape (buf is overwritten) and
 // records the fastest in tb.method / tb.tile (dst_tune.hip); no-op outside automatic
 // selection.
@@ -333,11 +338,11 @@ template <typename T> int dst_plan_only(DstTables<T>& tb, int N);
 constexpr int DST_MAX_N = 8192;
 bool dst_supported(int N);
 int dst_ppt(int N);
-// O(N) per output pass for any length (same layouts, fused scaling and tmp as dst_pass;
+// O(N) per output pass for any length (same layouts, fused scaling, tmp and cols as dst_pass;
 // `sn2` holds sin(pi j / N), j = 0..2N-1).
 template <typename T>
 int dst_direct_pass(int N, const T* sn2, const T* in, T* out, long long outer, long long inner, long long pitch,
-                    const DstScale<T>* fused, hipStream_t st, T* tmp = nullptr);
+                    const DstScale<T>* fused, hipStream_t st, T* tmp = nullptr, int cols = 0);
 // Plain passes of any lengths in as few launches as their number allows, as sine products on
 // the matrix cores (dst_direct.hip): all of rows or all of strided pencils, each writing an
 // array apart from every job's input.  Refused (ST_UNSUPPORTED) before anything is launched

@@ -26,6 +26,7 @@
 #include <atomic>
 #include "common.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -568,10 +569,11 @@ static std::atomic<int> g_variant_{0};
 void dst_set_variant(int v) { g_variant_.store(v, std::memory_order_relaxed); }
 int dst_get_variant() { return g_variant_.load(std::memory_order_relaxed); }
 
+// dst_pass; *padded is set where the kernel writes the columns from L to cols itself
 template <typename T>
-int dst_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long long inner,
-             long long pitch, const DstScale<T>* fused, int tile_seqs, hipStream_t st,
-             const DstFaces<T>* faces, T* tmp) {
+static int run_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long long inner, long long pitch,
+                    const DstScale<T>* fused, int tile_seqs, hipStream_t st, const DstFaces<T>* faces, T* tmp, int cols,
+                    bool* padded) {
   const int N = tb.N;
   const int g_variant = dst_get_variant();
   if (inner == 1 && pitch < N - 1) return ST_INVALID;
@@ -579,8 +581,11 @@ int dst_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long 
   if (!fused && !(faces && faces->mode) && tile_seqs <= 0) {
     const int k = inner == 1 ? 0 : 1;
     if (tb.S && (g_variant == 4 || (g_variant == 0 && tb.method[k] == DST_M_GEMM))) {
-      const int rc = dst_gemm_pass<T>(tb.S, N, in, out, outer, inner, pitch, st);
-      if (rc != ST_UNSUPPORTED) return rc;
+      const int rc = dst_gemm_pass<T>(tb.S, N, in, out, outer, inner, pitch, st, cols);
+      if (rc != ST_UNSUPPORTED) {
+        *padded = true;
+        return rc;
+      }
     }
     if (g_variant == 0 && tb.method[k] == DST_M_TILE) tile_seqs = tb.tile[k];
   }
@@ -592,7 +597,8 @@ int dst_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long 
   const int ppt = tb.ppt;
   if (!ppt) {  // no FFT plan for this length: the sine sums
     if (!tb.sn) return ST_INVALID;
-    return dst_direct_pass<T>(N, tb.sn, in, out, outer, inner, pitch, fused, st, tmp);
+    *padded = true;
+    return dst_direct_pass<T>(N, tb.sn, in, out, outer, inner, pitch, fused, st, tmp, cols);
   }
   if (!tb.tw) return ST_INVALID;
   const int tps = N / ppt;
@@ -637,6 +643,36 @@ int dst_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long 
   }
 }
 
+template <typename T>
+__global__ void k_zero_cols(T* __restrict__ out, long long rows, int lo, int w, long long pitch) {
+  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < rows * w;
+       e += (long long)gridDim.x * blockDim.x) {
+    const long long r = e / w;
+    out[r * pitch + lo + (e - r * w)] = T(0);
+  }
+}
+template <typename T> int zero_cols(T* out, long long rows, int lo, int hi, long long pitch, hipStream_t st) {
+  if (rows <= 0 || hi <= lo) return ST_OK;
+  const long long blocks = std::min<long long>((rows * (hi - lo) + 255) / 256, 65536);
+  hipLaunchKernelGGL(k_zero_cols<T>, dim3((unsigned)blocks), dim3(256), 0, st, out, rows, lo, hi - lo, pitch);
+  AHOC_HIP_TRY(hipGetLastError());
+  return ST_OK;
+}
+template int zero_cols<float>(float*, long long, int, int, long long, hipStream_t);
+template int zero_cols<double>(double*, long long, int, int, long long, hipStream_t);
+
+template <typename T>
+int dst_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long long inner,
+             long long pitch, const DstScale<T>* fused, int tile_seqs, hipStream_t st,
+             const DstFaces<T>* faces, T* tmp, int cols) {
+  if (inner != 1 || in == out) cols = 0;
+  if (cols > pitch) return ST_INVALID;
+  bool padded = false;
+  const int rc = run_pass<T>(tb, in, out, outer, inner, pitch, fused, tile_seqs, st, faces, tmp, cols, &padded);
+  if (rc != ST_OK || padded) return rc;
+  return zero_cols<T>(out, outer, tb.N - 1, cols, pitch, st);
+}
+
 template int dst_tables_init<float>(DstTables<float>&, int, hipStream_t, const DevAlloc*, const SineBase*, HostImages*);
 template int dst_tables_init<double>(DstTables<double>&, int, hipStream_t, const DevAlloc*, const SineBase*,
                                      HostImages*);
@@ -645,9 +681,10 @@ template int dst_plan_only<double>(DstTables<double>&, int);
 template void dst_tables_free<float>(DstTables<float>&);
 template void dst_tables_free<double>(DstTables<double>&);
 template int dst_pass<float>(const DstTables<float>&, const float*, float*, long long, long long,
-                             long long, const DstScale<float>*, int, hipStream_t, const DstFaces<float>*, float*);
+                             long long, const DstScale<float>*, int, hipStream_t, const DstFaces<float>*, float*,
+                             int);
 template int dst_pass<double>(const DstTables<double>&, const double*, double*, long long,
                               long long, long long, const DstScale<double>*, int, hipStream_t,
-                              const DstFaces<double>*, double*);
+                              const DstFaces<double>*, double*, int);
 
 }  // namespace ahoc

@@ -45,6 +45,7 @@ template <typename T> struct DirectArgs {
   int P;              // pencils per work-group
   long long outer, inner, pitch;
   long long ntile_inner;
+  int cols;
   bool fused;
   DstScale<T> fs;
 };
@@ -145,6 +146,11 @@ template <typename T> __global__ void __launch_bounds__(256) k_dst_direct(Direct
     if (rows) a.out[(base + p) * a.pitch + k] = v;
     else a.out[base + (long long)k * a.inner + p] = v;
   }
+  if (rows)
+    for (int e = threadIdx.x; e < ncols * (a.cols - L); e += blockDim.x) {
+      const int p = e / (a.cols - L);
+      a.out[(base + p) * a.pitch + L + (e - p * (a.cols - L))] = T(0);
+    }
 }
 
 template <typename T> struct SineArgs {
@@ -153,6 +159,7 @@ template <typename T> struct SineArgs {
   const T* sn;        // sin(pi j / N): j = 0..2N-1, or (half, even N) j = 0..N/2
   int N;
   int half;
+  int cols;           // columns stored per row: L, or more (zeros) up to the row's pitch
   long long outer, inner, pitch;
   long long ntile_inner;
 };
@@ -366,8 +373,8 @@ __device__ __forceinline__ void sine_tile(const SineArgs<T>& a, const DstScale<T
           if (k + 1 < L) vo *= sc / (A + B * fs.s_this[k + 1]);
         }
         T* op = ROWS ? a.out + (base + p) * a.pitch + k : a.out + base + (long long)k * a.inner + p;
-        if (k < L) op[0] = ve;
-        if (k + 1 < L) op[ROWS ? 1 : a.inner] = vo;
+        if (k < (ROWS ? a.cols : L)) op[0] = k < L ? ve : T(0);
+        if (k + 1 < (ROWS ? a.cols : L)) op[ROWS ? 1 : a.inner] = k + 1 < L ? vo : T(0);
       }
     }
   }
@@ -467,8 +474,8 @@ __device__ __forceinline__ void sine_chain(const SineArgs<T>& a, const DstScale<
     if (kk + 1 < L) vo *= fs.scale / (A + B * fs.s_this[kk + 1]);
   }
   T* op = a.out + base + (ROWS ? p * a.pitch + kk : (long long)kk * a.inner + p);
-  if (kk < L) op[0] = ve;
-  if (kk + 1 < L) op[ROWS ? 1 : a.inner] = vo;
+  if (kk < (ROWS ? a.cols : L)) op[0] = kk < L ? ve : T(0);
+  if (kk + 1 < (ROWS ? a.cols : L)) op[ROWS ? 1 : a.inner] = kk + 1 < L ? vo : T(0);
 }
 
 // grid.x: tiles; grid.y: groups of blockDim.x / 64 / KS * TO output pairs (one group in place)
@@ -621,13 +628,16 @@ template <typename T, bool ROWS> int sine_jobs_chain(SineJobs<T>& s, int blocks,
 
 template <typename T>
 int dst_direct_pass(int N, const T* sn2, const T* in, T* out, long long outer, long long inner, long long pitch,
-                    const DstScale<T>* fused, hipStream_t st, T* tmp) {
+                    const DstScale<T>* fused, hipStream_t st, T* tmp, int cols) {
   if (N < 2 || N > DST_MAX_N || !sn2 || !in || !out || outer < 0 || inner < 1) return ST_INVALID;
   const int L = N - 1;
   if (inner == 1 && (pitch < L || fused)) return ST_INVALID;
+  if (cols < L) cols = L;
+  // (the output pairs reach the next multiple of 32)
+  if (inner == 1 && cols > L && (cols > pitch || cols > (N / 2 + 15) / 16 * 32)) return ST_INVALID;
   if (outer == 0) return ST_OK;
   {
-    const long long extent = inner == 1 ? (outer - 1) * pitch + L : outer * (long long)L * inner;
+    const long long extent = inner == 1 ? (outer - 1) * pitch + cols : outer * (long long)L * inner;
     auto apart = [&](const T* x, const T* y) { return x + extent <= y || y + extent <= x; };
     auto run = [&](const T* src, T* dst, const DstScale<T>* f) {
       SineArgs<T> s;
@@ -636,6 +646,7 @@ int dst_direct_pass(int N, const T* sn2, const T* in, T* out, long long outer, l
       s.sn = sn2;
       s.N = N;
       s.half = 0;
+      s.cols = cols;
       s.outer = outer;
       s.inner = inner;
       s.pitch = pitch;
@@ -659,6 +670,7 @@ int dst_direct_pass(int N, const T* sn2, const T* in, T* out, long long outer, l
   a.outer = outer;
   a.inner = inner;
   a.pitch = pitch;
+  a.cols = cols;
   a.fused = fused != nullptr;
   if (fused) a.fs = *fused;
   long long blocks;
@@ -699,6 +711,7 @@ template <typename T> int dst_sine_jobs(const SineJob<T>* jobs, int count, hipSt
       a.sn = q.tb->sn;
       a.N = q.tb->N;
       a.half = q.tb->ppt != 0;
+      a.cols = a.N - 1;
       if (a.N > DST_SINE_JOBS_MAX_N) return ST_UNSUPPORTED;
       a.outer = q.outer;
       a.inner = q.inner;
@@ -731,8 +744,8 @@ template int dst_sine_jobs<float>(const SineJob<float>*, int, hipStream_t);
 template int dst_sine_jobs<double>(const SineJob<double>*, int, hipStream_t);
 
 template int dst_direct_pass<float>(int, const float*, const float*, float*, long long, long long, long long,
-                                    const DstScale<float>*, hipStream_t, float*);
+                                    const DstScale<float>*, hipStream_t, float*, int);
 template int dst_direct_pass<double>(int, const double*, const double*, double*, long long, long long, long long,
-                                     const DstScale<double>*, hipStream_t, double*);
+                                     const DstScale<double>*, hipStream_t, double*, int);
 
 }  // namespace ahoc

@@ -59,7 +59,7 @@ template <int TP> constexpr int cols_ldc() { return TP == 16 ? 16 : TP + 16; }
 template <typename T, int HP, int TP>
 __global__ void __launch_bounds__(HP / 8 * 64) k_dst_gemm_rows(const T* __restrict__ in, T* __restrict__ out,
                                                                const T* __restrict__ S, long long nrows,
-                                                               long long pitch, int N, long long ntiles) {
+                                                               long long pitch, int cols, int N, long long ntiles) {
   using M = Mfma<T>;
   constexpr int NT = HP / 8 * 64;
   constexpr int LDX = HP + M::XPAD;
@@ -110,7 +110,7 @@ __global__ void __launch_bounds__(HP / 8 * 64) k_dst_gemm_rows(const T* __restri
     __syncthreads();
     for (int e = threadIdx.x; e < TP * 2 * HP; e += NT) {
       const int r = e / (2 * HP), c = e - r * (2 * HP);
-      if (c < L && r0 + r < nrows) out[(r0 + r) * pitch + c] = zs[r * YS + c];
+      if (c < cols && r0 + r < nrows) out[(r0 + r) * pitch + c] = c < L ? zs[r * YS + c] : T(0);
     }
     __syncthreads();  // the next tile overwrites the staging rows
   }
@@ -176,13 +176,13 @@ __global__ void __launch_bounds__(HP / 8 * 64) k_dst_gemm_cols(const T* __restri
 
 template <typename T, int HP, int TP>
 void gemm_launch_tp(const T* S, int N, const T* in, T* out, long long outer, long long inner, long long pitch,
-                    hipStream_t st) {
+                    int cols, hipStream_t st) {
   constexpr int NT = HP / 8 * 64;
   if (inner == 1) {
     const long long ntiles = (outer + TP - 1) / TP;
     const unsigned grid = (unsigned)std::min<long long>(ntiles, MAX_GRID);
-    hipLaunchKernelGGL((k_dst_gemm_rows<T, HP, TP>), dim3(grid), dim3(NT), 0, st, in, out, S, outer, pitch, N,
-                       ntiles);
+    hipLaunchKernelGGL((k_dst_gemm_rows<T, HP, TP>), dim3(grid), dim3(NT), 0, st, in, out, S, outer, pitch, cols,
+                       N, ntiles);
   } else {
     const long long nti = (inner + TP - 1) / TP;
     const long long ntiles = outer * nti;
@@ -195,12 +195,12 @@ void gemm_launch_tp(const T* S, int N, const T* in, T* out, long long outer, lon
 // Tiles of 64 pencils; 16-pencil tiles (four times the work-groups, a quarter of the MFMA
 // chain per wavefront) when a pass has fewer 64-pencil tiles than two per compute unit.
 template <typename T, int HP>
-int gemm_launch(const T* S, int N, const T* in, T* out, long long outer, long long inner, long long pitch,
+int gemm_launch(const T* S, int N, const T* in, T* out, long long outer, long long inner, long long pitch, int cols,
                 hipStream_t st) {
   const long long n64 = inner == 1 ? (outer + 63) / 64 : outer * ((inner + 63) / 64);
   if (n64 <= 0) return ST_OK;
-  if (n64 < 512) gemm_launch_tp<T, HP, 16>(S, N, in, out, outer, inner, pitch, st);
-  else gemm_launch_tp<T, HP, 64>(S, N, in, out, outer, inner, pitch, st);
+  if (n64 < 512) gemm_launch_tp<T, HP, 16>(S, N, in, out, outer, inner, pitch, cols, st);
+  else gemm_launch_tp<T, HP, 64>(S, N, in, out, outer, inner, pitch, cols, st);
   AHOC_HIP_TRY(hipGetLastError());
   return ST_OK;
 }
@@ -225,14 +225,15 @@ template <typename T> std::vector<T> dst_gemm_table(const SineBase& b) {
 
 template <typename T>
 int dst_gemm_pass(const T* S, int N, const T* in, T* out, long long outer, long long inner, long long pitch,
-                  hipStream_t st) {
+                  hipStream_t st, int cols) {
   if (!S || !dst_gemm_supported(N)) return ST_UNSUPPORTED;
-  if (outer < 0 || inner < 1 || (inner == 1 && pitch < N - 1)) return ST_INVALID;
+  if (cols < N - 1) cols = N - 1;
+  if (outer < 0 || inner < 1 || (inner == 1 && (pitch < cols || cols > 2 * dst_gemm_hp(N)))) return ST_INVALID;
   switch (dst_gemm_hp(N)) {
-    case 16: return gemm_launch<T, 16>(S, N, in, out, outer, inner, pitch, st);
-    case 32: return gemm_launch<T, 32>(S, N, in, out, outer, inner, pitch, st);
-    case 48: return gemm_launch<T, 48>(S, N, in, out, outer, inner, pitch, st);
-    case 64: return gemm_launch<T, 64>(S, N, in, out, outer, inner, pitch, st);
+    case 16: return gemm_launch<T, 16>(S, N, in, out, outer, inner, pitch, cols, st);
+    case 32: return gemm_launch<T, 32>(S, N, in, out, outer, inner, pitch, cols, st);
+    case 48: return gemm_launch<T, 48>(S, N, in, out, outer, inner, pitch, cols, st);
+    case 64: return gemm_launch<T, 64>(S, N, in, out, outer, inner, pitch, cols, st);
     default: return ST_UNSUPPORTED;
   }
 }
@@ -240,8 +241,8 @@ int dst_gemm_pass(const T* S, int N, const T* in, T* out, long long outer, long 
 template std::vector<float> dst_gemm_table<float>(const SineBase&);
 template std::vector<double> dst_gemm_table<double>(const SineBase&);
 template int dst_gemm_pass<float>(const float*, int, const float*, float*, long long, long long, long long,
-                                  hipStream_t);
+                                  hipStream_t, int);
 template int dst_gemm_pass<double>(const double*, int, const double*, double*, long long, long long, long long,
-                                   hipStream_t);
+                                   hipStream_t, int);
 
 }  // namespace ahoc

@@ -1242,16 +1242,17 @@ __global__ void k_absmax(long long n, const Tx* __restrict__ x, double* __restri
   if (threadIdx.x == 0) bmax[blockIdx.x] = red[0];
 }
 
-// rows x cols block copy between arrays with different row pitches (with conversion)
+// rows x cols block copy between arrays with different row pitches (with conversion); columns
+// from cols to wide are written as zeros
 template <typename Ti, typename To>
-__global__ void k_pitch_copy(long long rows, int cols, const Ti* __restrict__ in, long long ip,
+__global__ void k_pitch_copy(long long rows, int cols, int wide, const Ti* __restrict__ in, long long ip,
                              To* __restrict__ out, long long op) {
-  const long long n = rows * cols;
+  const long long n = rows * wide;
   for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n;
        e += (long long)gridDim.x * blockDim.x) {
-    const long long r = e / cols;
-    const int c = (int)(e - r * cols);
-    out[r * op + c] = (To)in[r * ip + c];
+    const long long r = e / wide;
+    const int c = (int)(e - r * wide);
+    out[r * op + c] = c < cols ? (To)in[r * ip + c] : To(0);
   }
 }
 
@@ -1519,8 +1520,10 @@ int out_v(const Geom& g, const T* Vi, const double* Q, const double* vedge, doub
 }
 
 template <typename Ti, typename To>
-int pitch_copy(long long rows, int cols, const Ti* in, long long ip, To* out, long long op, hipStream_t st) {
-  hipLaunchKernelGGL((k_pitch_copy<Ti, To>), dim3(nblocks(rows * cols)), dim3(TPB), 0, st, rows, cols, in, ip, out, op);
+int pitch_copy(long long rows, int cols, const Ti* in, long long ip, To* out, long long op, hipStream_t st, int wide) {
+  if (wide < cols) wide = cols;
+  hipLaunchKernelGGL((k_pitch_copy<Ti, To>), dim3(nblocks(rows * wide)), dim3(TPB), 0, st, rows, cols, wide, in, ip, out,
+                     op);
   AHOC_HIP_TRY(hipGetLastError());
   return ST_OK;
 }
@@ -1582,9 +1585,9 @@ int fill(long long n, double v, double* x, hipStream_t st) {
 
 INST_T(float)
 INST_T(double)
-template int pitch_copy<double, float>(long long, int, const double*, long long, float*, long long, hipStream_t);
-template int pitch_copy<float, double>(long long, int, const float*, long long, double*, long long, hipStream_t);
-template int pitch_copy<double, double>(long long, int, const double*, long long, double*, long long, hipStream_t);
+template int pitch_copy<double, float>(long long, int, const double*, long long, float*, long long, hipStream_t, int);
+template int pitch_copy<float, double>(long long, int, const float*, long long, double*, long long, hipStream_t, int);
+template int pitch_copy<double, double>(long long, int, const double*, long long, double*, long long, hipStream_t, int);
 template int convert<double, float>(long long, const double*, float*, hipStream_t);
 template int convert<float, double>(long long, const float*, double*, hipStream_t);
 template int convert<double, double>(long long, const double*, double*, hipStream_t);
