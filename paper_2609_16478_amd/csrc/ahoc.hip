@@ -790,9 +790,11 @@ template <typename T> T* const* face_arrays(Prec<T>& P, int set, T* (&f)[3]) {
   f[2] = set ? P.Uz : P.Fz;
   return f;
 }
+// The test switch may move at any time: a caller asks face_jobs once and hands the answer on, so
+// that the steps around the transforms look where those left their result.
 template <typename T> bool face_jobs(const Prec<T>& P) { return P.ft[0][0] && face_jobs_on(); }
 template <typename T>
-int face_dst2(ahoc_handle* h, Prec<T>& P, int sets, hipStream_t st, bool from_ft = false) {
+int face_dst2(ahoc_handle* h, Prec<T>& P, int sets, hipStream_t st, bool jobs, bool from_ft = false) {
   const Geom& g = h->g;
   const DstTables<T>* tb = P.tb;
   SineJob<T> r[6], c[6];
@@ -805,7 +807,7 @@ int face_dst2(ahoc_handle* h, Prec<T>& P, int sets, hipStream_t st, bool from_ft
     if (g.dim == 3) {
       // rows, then strided; y faces of the second set are [2][n_x'][n_z'] (z rows)
       const long long yr = k ? 2LL * g.ni[0] : 2LL * g.ni[2], yp = k ? g.ni[2] : g.px;
-      if (face_jobs(P)) {
+      if (jobs) {
         r[n] = {&tb[0], f[2], t[2], 2LL * g.ni[1], 1, g.px};
         c[n++] = {&tb[1], t[2], f[2], 2, g.px, g.px};
         r[n] = {&tb[2], f[0], t[0], 2LL * g.ni[1], 1, g.ni[2]};
@@ -820,7 +822,7 @@ int face_dst2(ahoc_handle* h, Prec<T>& P, int sets, hipStream_t st, bool from_ft
         TRY(dst_pass<T>(tb[k ? 2 : 0], f[1], f[1], yr, 1, yp, nullptr, 0, st));
         TRY(dst_pass<T>(tb[k ? 0 : 2], f[1], f[1], 2, yp, yp, nullptr, 0, st));
       }
-    } else if (face_jobs(P)) {
+    } else if (jobs) {
       r[n++] = {&tb[0], from_ft ? t[1] : f[1], from_ft ? f[1] : t[1], 2LL * g.nb, 1, g.px};
       r[n++] = {&tb[1], from_ft ? t[0] : f[0], from_ft ? f[0] : t[0], 2LL * g.nb, 1, g.ni[1]};
     } else {
@@ -831,13 +833,12 @@ int face_dst2(ahoc_handle* h, Prec<T>& P, int sets, hipStream_t st, bool from_ft
   TRY(dst_sine_jobs<T>(r, n, st));
   return g.dim == 3 ? dst_sine_jobs<T>(c, n, st) : ST_OK;
 }
-// Whether the layers of a 2-D lift go to P.ft, from where face_dst2 takes them to F and U.
-template <typename T> bool lift_to_ft(const ahoc_handle* h, const Prec<T>& P) { return h->g.dim == 2 && face_jobs(P); }
 // Boundary residual from the face sums in F, through their transforms.
 template <typename T>
 int gather_sums(ahoc_handle* h, Prec<T>& P, const T* Q, const T* srcq, double* R, hipStream_t st) {
-  TRY(face_dst2<T>(h, P, 1, st));
-  if (lift_to_ft(h, P)) return gather_faces<T>(h->g, P.ft[0][0], P.ft[0][1], nullptr, Q, P.af, srcq, R, st);
+  const bool jobs = face_jobs(P);
+  TRY(face_dst2<T>(h, P, 1, st, jobs));
+  if (jobs && h->g.dim == 2) return gather_faces<T>(h->g, P.ft[0][0], P.ft[0][1], nullptr, Q, P.af, srcq, R, st);
   return gather_faces<T>(h->g, P.Fx, P.Fy, P.Fz, Q, P.af, srcq, R, st);
 }
 
@@ -850,9 +851,10 @@ int vsolve_spec(ahoc_handle* h, Prec<T>& P, const T* Q, hipStream_t st, bool ski
   const Geom& g = h->g;
   if (!lifted) {  // (else the face layers are in Fx, Fy, Fz already)
     hipEvent_t e = tbegin(h, st);
-    const bool ft = lift_to_ft(h, P);
+    // (the layers of a 2-D lift go to P.ft, from where the sine products take them to F)
+    const bool jobs = face_jobs(P), ft = jobs && g.dim == 2;
     TRY(face_lift<T>(g, h->wv, Q, ft ? P.ft[0][0] : P.Fx, ft ? P.ft[0][1] : P.Fy, P.Fz, st));
-    TRY(face_dst2<T>(h, P, 1, st, ft));
+    TRY(face_dst2<T>(h, P, 1, st, jobs, ft));
     tend(h, AHOC_K_LIFT, e, (double)TQ(g) * 2.0 * sizeof(T), st);
   }
   const double pass_bytes = 2.0 * (double)g.nint * g.nb * sizeof(T);
@@ -974,7 +976,7 @@ int matvec_mspec(ahoc_handle* h, Prec<T>& P, const T* Q, double* y, hipStream_t 
   const Geom& g = h->g;
   const bool d3 = g.dim == 3;
   const bool tiled = d3 && P.mq;
-  const bool ft = lift_to_ft(h, P);
+  const bool jobs = face_jobs(P), ft = jobs && !d3;
   // both face-layer sets and their spectra: 3-D in one tiled pass over Q, 2-D in one pass of
   // its own
   hipEvent_t el = tbegin(h, st);
@@ -1013,7 +1015,7 @@ int matvec_mspec(ahoc_handle* h, Prec<T>& P, const T* Q, double* y, hipStream_t 
     TRY(face_lift<T>(g, h->wv, Q, P.Fx, P.Fy, P.Fz, st));
     TRY(face_lift_m<T>(g, h->w, Q, P.ia, P.Ux, P.Uy, P.Uz, st));
   }
-  if (!lines) TRY(face_dst2<T>(h, P, 3, st, ft));
+  if (!lines) TRY(face_dst2<T>(h, P, 3, st, jobs, ft));
   tend(h, AHOC_K_LIFT, el, (double)TQ(g) * 7.0 * sizeof(T), st);
   TRY(vsolve_spec<T>(h, P, zq, st, true, true));
   T* buf = P.bufA;
@@ -1246,12 +1248,12 @@ template <typename T> bool lines_ok(const ahoc_handle* h, const Prec<T>& P) {
   return g.dim == 2 && g.n[0] == g.n[1] && P.mspec && !h->tri && face_jobs_on() && lines2d_supported(g.n[0]);
 }
 
-// y = S_h q  (homogeneous Lemma-1 form); with pre, y = S_h P^-1 q where lines_ok
+// y = S_h q  (homogeneous Lemma-1 form); with pre, y = S_h P^-1 q (the caller has asked lines_ok)
 template <typename T>
 int matvec(ahoc_handle* h, Prec<T>& P, const double* q, double* y, hipStream_t st, bool pre = false) {
   int rc = 0;
   hipEvent_t e = tbegin(h, st);
-  if (lines_ok(h, P)) {
+  if (pre || lines_ok(h, P)) {
     TRY(matvec_mspec<T>(h, P, nullptr, y, st, true, q, pre));
     tend(h, AHOC_K_MATVEC, e, (double)sizeof(T) * (6.0 * h->g.nint + h->g.nnodal) * h->g.nb, st);
     return ST_OK;

@@ -171,17 +171,18 @@ int small_units(int n0, int n1) {
   return std::max(units(n0, n1 - 1), units(n1, n0 - 1));
 }
 
-}  // namespace
-
-template <typename T> bool poisson_small_ok(int n0, int n1) {
-  return dst_get_variant() == 0 &&
-         2.0 * (dst_sine_flops(n0, n1 - 1, 1) + dst_sine_flops(n1, 1, n0 - 1)) <= POISSON_SMALL_FLOPS &&
+template <typename T> bool small_fits(int n0, int n1) {
+  return 2.0 * (dst_sine_flops(n0, n1 - 1, 1) + dst_sine_flops(n1, 1, n0 - 1)) <= POISSON_SMALL_FLOPS &&
          small_lds<T>(n0, n1) <= 160 * 1024 && small_units(n0, n1) <= 16 * POISSON_UNITS;
 }
 
+}  // namespace
+
+template <typename T> bool poisson_small_ok(int n0, int n1) { return dst_get_variant() == 0 && small_fits<T>(n0, n1); }
+
 template <typename T> int poisson_small(const PoissonSmall<T>& a, hipStream_t st) {
   const int n0 = a.n[0], n1 = a.n[1];
-  if (n0 < 2 || n1 < 2 || !poisson_small_ok<T>(n0, n1)) return ST_UNSUPPORTED;
+  if (n0 < 2 || n1 < 2 || !small_fits<T>(n0, n1)) return ST_UNSUPPORTED;
   const size_t lds = small_lds<T>(n0, n1);
   if (lds > 64 * 1024) {
     static std::once_flag once;
