@@ -473,23 +473,9 @@ template <typename T> int prec_init(ahoc_handle* h, Prec<T>& P, int tile_opt, hi
     const long long inner = g.dim == 3 ? (long long)g.px * g.ni[1] : g.px;
     P.mspec = dst_pipe_mpass_ok<T>(g.n[t], inner, g.px, mspec_gen<T>(g, P));
   }
-  if (P.spectral && face_jobs_pay(g)) {  // (the sixth-order chain has only the first set)
-    const long long sx = g.dim == 3 ? 2LL * g.ni[1] * g.ni[2] : 2LL * g.nb * g.ni[1];
-    const long long sy[2] = {g.dim == 3 ? 2LL * g.px * g.ni[2] : 2LL * g.nb * g.px,
-                             g.dim == 3 ? 2LL * g.ni[0] * g.ni[2] : 2LL * g.nb * g.px};
-    const long long sz = g.dim == 3 ? 2LL * g.px * g.ni[1] : 0;
-    for (int k = 0; k < (h->tri ? 1 : 2); ++k) {
-      const long long n = sx + sy[k] + sz;
-      TRY(alloc_t(h, &P.ft[k][0], n));
-      P.ft[k][1] = P.ft[k][0] + sx;
-      P.ft[k][2] = P.ft[k][1] + sy[k];
-      AHOC_HIP_TRY(hipMemsetAsync(P.ft[k][0], 0, sizeof(T) * n, st));  // zero row padding
-    }
-  }
   TRY(alloc_int(h, &P.bufA, st));
   TRY(alloc_int(h, &P.bufB, st));
   P.planes = planes_pay<T>(g);
-  if (!has_plans(g) || P.planes) TRY(alloc_int(h, &P.scr, st));
   // setup-time choice between the FFT and the matrix-core pass for the plain passes of the
   // operator, timed on their own shapes: the x (row) passes; in 3-D also the strided y passes
   if (g.dim == 2) {
@@ -541,6 +527,57 @@ template <typename T> int prec_init(ahoc_handle* h, Prec<T>& P, int tile_opt, hi
   P.scM.mcb = g.dim == 3 ? (T)(h->w.m1 * g.h[1] * g.h[1]) : (T)0;
   P.scM.mct = (T)(h->w.m1 * g.h[t] * g.h[t]);
   P.ready = true;
+  return ST_OK;
+}
+
+// Whether a pass of the Dirichlet solves along an axis without an FFT plan gains from a second
+// interior array.
+bool scr_pays(const Geom& g) {
+  bool pays = false;
+  for (int a = 0; a < g.dim; ++a) {
+    if (dst_ppt(g.n[a])) continue;
+    const bool slow = a == g.dim - 1;
+    const long long outer = a == 0 ? (long long)g.nb * g.ni[1] * g.ni[2] : slow ? g.nb : g.ni[2];
+    const long long inner = a == 0 ? 1 : slow && a == 2 ? (long long)g.px * g.ni[1] : g.px;
+    pays = pays || dst_direct_splits(g.n[a], outer, inner);
+  }
+  return pays;
+}
+
+// The arrays that only make passes faster, after every other one of the handle: where there is no
+// memory left for one, its passes work in place, so that a setup fits as it would without them.
+template <typename T> int optional_arrays(ahoc_handle* h, Prec<T>& P, hipStream_t st) {
+  const Geom& g = h->g;
+  if (!P.ready) return ST_OK;
+  auto take = [&](T** p, long long n) -> int {
+    const int rc = alloc_t(h, p, n);
+    if (rc == ST_NOMEM) *p = nullptr;
+    if (rc != ST_OK) return rc;
+    AHOC_HIP_TRY(hipMemsetAsync(*p, 0, sizeof(T) * (size_t)n, st));  // zero row padding
+    return ST_OK;
+  };
+  int rc = ST_OK;
+  if (P.spectral && face_jobs_pay(g)) {  // (the sixth-order chain has only the first set)
+    const long long sx = g.dim == 3 ? 2LL * g.ni[1] * g.ni[2] : 2LL * g.nb * g.ni[1];
+    const long long sy[2] = {g.dim == 3 ? 2LL * g.px * g.ni[2] : 2LL * g.nb * g.px,
+                             g.dim == 3 ? 2LL * g.ni[0] * g.ni[2] : 2LL * g.nb * g.px};
+    const long long sz = g.dim == 3 ? 2LL * g.px * g.ni[1] : 0;
+    const int sets = h->tri ? 1 : 2;
+    T* f = nullptr;
+    rc = take(&f, sets * (sx + sz) + sy[0] + (sets > 1 ? sy[1] : 0));
+    if (rc != ST_OK && rc != ST_NOMEM) return rc;
+    for (int k = 0; f && k < sets; ++k) {
+      P.ft[k][0] = f;
+      P.ft[k][1] = f + sx;
+      P.ft[k][2] = P.ft[k][1] + sy[k];
+      f = P.ft[k][2] + sz;
+    }
+  }
+  if (P.planes || scr_pays(g)) {
+    rc = take(&P.scr, TA(g));
+    if (rc != ST_OK && rc != ST_NOMEM) return rc;
+    P.planes = P.planes && P.scr;
+  }
   return ST_OK;
 }
 
@@ -1829,8 +1866,6 @@ int setup_impl(const ahoc_problem* pbs, int count, hipStream_t st, ahoc_handle* 
   TRY(alloc_t(h, &h->dq, TQ(g)));
   TRY(alloc_t(h, &h->rvec, TQ(g)));
   TRY(alloc_t(h, &h->zvec, TQ(g)));
-  h->pjobs = face_jobs_pay(g);
-  if (h->pjobs || !has_plans(g)) TRY(alloc_t(h, &h->zt, TQ(g)));
   if (h->opt.use_graph) {
     TRY(alloc_t(h, &h->gin, TQ(g)));
     TRY(alloc_t(h, &h->gout, TQ(g)));
@@ -1844,7 +1879,17 @@ int setup_impl(const ahoc_problem* pbs, int count, hipStream_t st, ahoc_handle* 
   h->pinned_b = h->pinned + npin;
   h->pinned_i = reinterpret_cast<int*>(h->pinned_b + nb);
   h->pinned_s = h->pinned_i + npin;
-  if (h->opt.precond) TRY(precond_init(h, st));
+  if (h->opt.precond) {
+    TRY(precond_init(h, st));
+    if (face_jobs_pay(g) || !has_plans(g)) {
+      const int rc = alloc_t(h, &h->zt, TQ(g));
+      if (rc != ST_OK && rc != ST_NOMEM) return rc;
+      if (rc == ST_NOMEM) h->zt = nullptr;
+    }
+    h->pjobs = h->zt && face_jobs_pay(g);
+  }
+  TRY(optional_arrays<double>(h, h->p64, st));
+  TRY(optional_arrays<float>(h, h->p32, st));
   AHOC_HIP_TRY(hipStreamSynchronize(st));
   h->images.clear();
   h->base.clear();

@@ -343,6 +343,8 @@ int dst_ppt(int N);
 template <typename T>
 int dst_direct_pass(int N, const T* sn2, const T* in, T* out, long long outer, long long inner, long long pitch,
                     const DstScale<T>* fused, hipStream_t st, T* tmp = nullptr, int cols = 0);
+// Whether such a pass is faster from one array to another than in place (the same kernel otherwise).
+bool dst_direct_splits(int N, long long outer, long long inner);
 // Plain passes of any lengths in as few launches as their number allows, as sine products on
 // the matrix cores (dst_direct.hip): all of rows or all of strided pencils, each writing an
 // array apart from every job's input.  Refused (ST_UNSUPPORTED) before anything is launched

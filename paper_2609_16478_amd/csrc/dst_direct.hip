@@ -574,11 +574,18 @@ int sine_chain_launch(const SineArgs<T>& a, const DstScale<T>* fs, long long til
   return ST_OK;
 }
 
+// Whether a pass of `tiles` 16-pencil tiles that writes elsewhere than it reads splits its outputs
+// over work-groups of four wavefronts (each re-reads the tile): while whole pencils would give
+// fewer than two work-groups per CU, and their sums over the four wavefronts too while even those
+// would leave compute units idle (SINE_CHAIN_WGS); and where a tile's outputs exceed one
+// work-group's registers.
+bool sine_splits(int N, long long tiles) {
+  const int pairs = (N / 2 + 15) / 16;
+  return pairs > 64 || (pairs > 1 && tiles < 512 && (pairs > 4 || tiles * ((pairs + 3) / 4) < SINE_CHAIN_WGS));
+}
+
 // Tiles of 32 pencils share each gathered sine between two MFMAs, 16-pencil tiles double the
-// work-groups: 32 from two work-groups per CU upward.  A pass that writes elsewhere than it
-// reads splits its outputs over work-groups of four wavefronts (each re-reads the tile) while
-// whole pencils would give fewer than that, and their sums over the four wavefronts while even
-// those would leave compute units idle.
+// work-groups: 32 from two work-groups per CU upward.
 template <typename T, bool ROWS>
 int sine_pass(SineArgs<T>& a, const DstScale<T>* fs, bool disjoint, hipStream_t st) {
   const int pairs = (a.N / 2 + 15) / 16;
@@ -587,12 +594,12 @@ int sine_pass(SineArgs<T>& a, const DstScale<T>* fs, bool disjoint, hipStream_t 
     return ROWS ? (a.outer + P - 1) / P : a.outer * a.ntile_inner;
   };
   if (disjoint && pairs > 64) return sine_launch<T, ROWS, 2, 2>(a, fs, tiles(32), (pairs + 15) / 16, 8, st);
-  if (disjoint && pairs > 1 && tiles(16) < 512) {
+  if (disjoint && sine_splits(a.N, tiles(16))) {
     if (a.N <= 1024 && tiles(16) * ((pairs + 3) / 4) < SINE_CHAIN_WGS) {
       if (sine_chain_ok(a, ROWS)) return sine_chain_launch<T, ROWS>(a, fs, tiles(16), pairs, st);
       return sine_launch<T, ROWS, 1, 1, 4>(a, fs, tiles(16), pairs, 4, st);
     }
-    if (pairs > 4) return sine_launch<T, ROWS, 1, 1>(a, fs, tiles(16), (pairs + 3) / 4, 4, st);
+    return sine_launch<T, ROWS, 1, 1>(a, fs, tiles(16), (pairs + 3) / 4, 4, st);
   }
   if (pairs > 64) return ST_UNSUPPORTED;  // in place: one work-group holds every output of a tile
   const bool wide = tiles(32) >= 512;
@@ -687,6 +694,10 @@ int dst_direct_pass(int N, const T* sn2, const T* in, T* out, long long outer, l
   hipLaunchKernelGGL(k_dst_direct<T>, dim3((unsigned)blocks), dim3(256), lds, st, a);
   AHOC_HIP_TRY(hipGetLastError());
   return ST_OK;
+}
+
+bool dst_direct_splits(int N, long long outer, long long inner) {
+  return sine_splits(N, inner == 1 ? (outer + 15) / 16 : outer * ((inner + 15) / 16));
 }
 
 // Flops of a pass as sine products, its pencils rounded up to the tile.
