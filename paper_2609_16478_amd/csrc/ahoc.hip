@@ -665,12 +665,23 @@ template <typename T> int poisson_dense(ahoc_handle* h, Prec<T>& P, const double
     }
     a.c_ta = P.scP.c_ta;
     a.scale = P.scP.scale;
-    return poisson_small<T>(a, st);
+    hipEvent_t e = tbegin(h, st);
+    TRY(poisson_small<T>(a, st));
+    tend(h, AHOC_K_DST_FUSED, e, 2.0 * g.nint * sizeof(double), st);
+    return ST_OK;
   }
   if (P.planes && dst_get_variant() == 0) {  // the caller's rows are read and written by the plane passes
+    const double plane_bytes = (double)g.nint * (sizeof(double) + sizeof(T));
+    hipEvent_t e = tbegin(h, st);
     TRY((dst_plane_pass<T, double, T>(P.tb[0], P.tb[1], gin, g.ni[0], P.bufA, g.px, g.ni[2], st)));
+    tend(h, AHOC_K_DST_ROWS, e, plane_bytes, st);
+    e = tbegin(h, st);
     TRY(dst_solve_axis<T>(P.tb[2], P.bufA, (long long)g.px * g.ni[1], g.px, P.scP, P.tile[2], P.scr, st));
-    return dst_plane_pass<T, T, double>(P.tb[0], P.tb[1], P.bufA, g.px, wout, g.ni[0], g.ni[2], st);
+    tend(h, AHOC_K_DST_FUSED, e, 2.0 * g.nint * sizeof(T), st);
+    e = tbegin(h, st);
+    TRY((dst_plane_pass<T, T, double>(P.tb[0], P.tb[1], P.bufA, g.px, wout, g.ni[0], g.ni[2], st)));
+    tend(h, AHOC_K_DST_ROWS, e, plane_bytes, st);
+    return ST_OK;
   }
   TRY((pitch_copy<double, T>(rows, g.ni[0], gin, g.ni[0], P.bufA, g.px, st, g.px)));  // with zero padding
   TRY(poisson<T>(h, P, P.bufA, P.scP, st));
