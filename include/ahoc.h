@@ -342,8 +342,8 @@ ahoc_status ahoc_set_dst_tile(int pass, int precision, int pairs);
 /* Kernel classes for ahoc_kernel_times. */
 enum {
   AHOC_K_DST_ROWS = 0,     /* DST-I pass along x (contiguous pencils); in the Dirichlet solves of
-                              3-D grids with n_x, n_y <= 128, x and y of each plane in one
-                              pass                                                       */
+                              3-D grids with n_x, n_y <= 128 (but for many thin planes), x
+                              and y of each plane in one pass                            */
   AHOC_K_DST_STRIDED = 1,  /* DST-I pass along y in 3-D (strided pencils)               */
   AHOC_K_DST_FUSED = 2,    /* fused forward DST and eigen scaling along the slowest axis, then
                               the inverse DST (Poisson solves) or the face sums (U-solve);

@@ -375,7 +375,7 @@ bool has_plans(const Geom& g) {
 
 // Whether the Dirichlet solves of a 3-D grid take x and y of each plane in one launch.
 template <typename T> bool planes_pay(const Geom& g) {
-  return g.dim == 3 && dst_get_variant() == 0 && dst_plane_ok(g.n[0], g.n[1]);
+  return g.dim == 3 && dst_get_variant() == 0 && dst_plane_pays(g.n[0], g.n[1], g.ni[2]);
 }
 
 // Whether the transforms of a grid's faces run as sine products, all faces in one launch per

@@ -362,6 +362,7 @@ constexpr int DST_SINE_JOBS_MAX_N = 1024;
 // the output pitch (of at most the next multiple of 32) are written as zeros.
 constexpr int DST_PLANE_MAX_N = 128;
 bool dst_plane_ok(int n0, int n1);
+bool dst_plane_pays(int n0, int n1, int planes);  // against a pass per axis
 template <typename T, typename TI, typename TO>
 int dst_plane_pass(const DstTables<T>& tx, const DstTables<T>& ty, const TI* in, long long in_pitch, TO* out,
                    long long out_pitch, int planes, hipStream_t st);

@@ -334,6 +334,19 @@ template int dst_solve_axis<double>(const DstTables<double>&, double*, long long
 
 bool dst_plane_ok(int n0, int n1) { return n0 >= 4 && n1 >= 4 && n0 <= DST_PLANE_MAX_N && n1 <= DST_PLANE_MAX_N; }
 
+// A plane takes the time of 32 outputs of either parity of y for each 32 columns of x, whatever its
+// size in y, where the time of separate passes goes with its values once they outlast their
+// launches.  A solve, separate passes against planes, FP64: 128 x 8 points in y of 256, 512, 2048
+// planes 42 and 40, 51 and 63, 124 and 189 us; 128 x 16 of 512 and 2048 planes 59 and 56, 157 and
+// 203; 128 x 32 of 2048 planes 266 and 242; 64 x 8 and 64 x 16 of 2048 planes 88 and 100, 110 and
+// 105; 32 x 8 of 2048 planes 71 and 65; 8 x 8 of 4096 planes 96 and 101.  The two meet at y = 8 per
+// 32 columns of x in long grids (twice that where x fills less than half of them), below it where
+// fewer than some thousand groups of columns leave the launches as the time.
+bool dst_plane_pays(int n0, int n1, int planes) {
+  const long long pairs = (n0 / 2 + 15) / 16;
+  return dst_plane_ok(n0, n1) && n1 >= std::min((n0 < 16 ? 16 : 8) * pairs, planes * pairs / 128);
+}
+
 template <typename T, typename TI, typename TO>
 int dst_plane_pass(const DstTables<T>& tx, const DstTables<T>& ty, const TI* in, long long in_pitch, TO* out,
                    long long out_pitch, int planes, hipStream_t st) {

@@ -195,7 +195,7 @@ int poisson_noalloc(int dim, const int* n, const double* lo, const double* hi, c
     }
     return ST_OK;
   };
-  if (dim == 3 && dst_get_variant() == 0 && dst_plane_ok(N[0], N[1])) {
+  if (dim == 3 && dst_get_variant() == 0 && dst_plane_pays(N[0], N[1], ni[2])) {
     // the caller's rows are read and written by the passes over planes
     TRY_ST((dst_plane_pass<T, double, T>(tb[0], tb[1], g, ni[0], buf, px, ni[2], st)));
     TRY_ST(dst_solve_axis<T>(tb[2], buf, px * ni[1], px, sc, 0, scr, st));

@@ -32,3 +32,31 @@ def test_poisson_is_timed(n, want, prec):
     for k in want:
         ms, _, nbytes = kt[k]
         assert ms > 0 and nbytes >= 8 * g.numel()
+
+
+# thin planes: few of them in one pass each, many as separate passes, on both sides of the rule
+# (n_y >= 8 per 32 columns of x, or fewer than 128 n_y groups of columns)
+@pytest.mark.parametrize("n,planes", [((128, 8, 200), True), ((128, 8, 600), False), ((128, 16, 512), True),
+                                      ((128, 16, 2048), False), ((100, 31, 2100), False), ((100, 32, 2100), True),
+                                      ((64, 15, 1100), False), ((64, 16, 1100), True), ((30, 8, 1030), True),
+                                      ((30, 7, 1030), False)])
+def test_thin_planes(n, planes):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import numpy as np
+    import paper_2609_16478_amd as ah
+    from oracle import fast
+    hi = tuple(m / max(n) for m in n)
+    shape = tuple(m + 1 for m in reversed(n))
+    pb = W.Problem(n, (0.0,) * 3, hi, np.ones(shape), np.zeros(shape))
+    g = np.random.default_rng(n[1]).standard_normal([m - 1 for m in reversed(n)])
+    ref = fast.FastTier(pb).poisson(g)
+    gt = torch.from_numpy(g).cuda()
+    for prec in (ah.FP64, ah.MIXED):
+        with ah.Solver(pb, precision=prec) as s:
+            s.profile(True)
+            w = s.poisson(gt)
+            kt = s.kernel_times()
+        assert kt["dst_strided"][1] == (0 if planes else 2) and kt["dst_rows"][1] == 2, kt
+        if prec == ah.FP64:
+            assert float(np.abs(w.cpu().numpy() - ref).max()) <= 1e-12 * np.abs(ref).max()
