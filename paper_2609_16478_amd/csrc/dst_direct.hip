@@ -26,7 +26,8 @@
 // staging loops that waited for each load, 10.7 us with the sum split over four wavefronts and
 // one trip to memory.
 // k_dst_direct, one thread per output and the whole pencil in LDS, remains for in-place
-// passes of N > 2048, whose outputs k_dst_sine could not hold in registers.
+// passes of N > 2048, whose outputs k_dst_sine could not hold in registers, and for short strided
+// pencils (see short_pencils).
 #include "common.h"
 #include "mfma_sine.h"
 
@@ -631,6 +632,19 @@ template <typename T, bool ROWS> int sine_jobs_chain(SineJobs<T>& s, int blocks,
   return ST_OK;
 }
 
+// Strided pencils so short that 16 x 16 products are mostly padding (N < 32 fills one pair of
+// them): one thread per output has no more to do, and transforms, scales and transforms back in one
+// launch and one trip to memory where the products take two.  The pass along the slowest axis of a
+// solve, products against one thread per output, FP64: 300 x 200 columns of 4, 9, 13, 17 and 20
+// intervals, of the whole solve 64 and 47, 88 and 74, 102 and 89, 117 and 108, 126 and 123 us; 150 x
+// 50 of 7 and 13 40.5 and 38.5, 40.9 and 41.5.  Two plain passes along y: 300 x 200 columns of 4, 9
+// and 13 intervals 62 and 52, 86 and 79, 97 and 98; 160 x 50 of 7 40.0 and 40.8.  In FP32 the lines lie
+// at the same bytes a row of columns.
+template <typename T> bool short_pencils(int N, long long columns, bool fused) {
+  const bool wide = columns * (long long)sizeof(T) >= 200000;
+  return fused ? N < (wide ? 18 : 12) : N < (wide ? 12 : 6);
+}
+
 }  // namespace
 
 template <typename T>
@@ -643,7 +657,7 @@ int dst_direct_pass(int N, const T* sn2, const T* in, T* out, long long outer, l
   // (the output pairs reach the next multiple of 32)
   if (inner == 1 && cols > L && (cols > pitch || cols > (N / 2 + 15) / 16 * 32)) return ST_INVALID;
   if (outer == 0) return ST_OK;
-  {
+  if (inner == 1 || !short_pencils<T>(N, outer * inner, fused != nullptr)) {
     const long long extent = inner == 1 ? (outer - 1) * pitch + cols : outer * (long long)L * inner;
     auto apart = [&](const T* x, const T* y) { return x + extent <= y || y + extent <= x; };
     auto run = [&](const T* src, T* dst, const DstScale<T>* f) {
