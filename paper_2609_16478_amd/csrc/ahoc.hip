@@ -459,10 +459,9 @@ template <typename T> int prec_init(ahoc_handle* h, Prec<T>& P, int tile_opt, hi
       TRY(alloc_t(h, &P.Ux, 2LL * g.ni[1] * g.ni[2]));
       TRY(alloc_t(h, &P.Uy, 2LL * g.ni[0] * g.ni[2]));
       TRY(alloc_t(h, &P.Uz, 2LL * g.px * g.ni[1]));
-      if (g.nb == 1) {  // m1 / alpha_b in Q layout, for the tiled face-layer pass
-        TRY(alloc_t(h, &P.mq, TQ(g)));
-        TRY(nodal_to_q<T>(g, h->w.m1, P.ia, P.mq, st));
-      }
+      // m1 / alpha_b in Q layout, for the tiled face-layer pass
+      TRY(alloc_t(h, &P.mq, TQ(g)));
+      TRY(nodal_to_q<T>(g, h->w.m1, P.ia, P.mq, st));
     } else {  // per instance [2][n_y'] and [2][px]
       TRY(alloc_t(h, &P.Ux, 2LL * g.nb * g.ni[1]));
       TRY(alloc_t(h, &P.Uy, 2LL * g.nb * g.px));
@@ -1023,7 +1022,6 @@ int matvec_mspec(ahoc_handle* h, Prec<T>& P, const T* Q, double* y, hipStream_t 
                  const double* q = nullptr, bool pre = false) {
   const Geom& g = h->g;
   const bool d3 = g.dim == 3;
-  const bool tiled = d3 && P.mq;
   const bool jobs = face_jobs(P), ft = jobs && !d3;
   // both face-layer sets and their spectra: 3-D in one tiled pass over Q, 2-D in one pass of
   // its own
@@ -1054,14 +1052,11 @@ int matvec_mspec(ahoc_handle* h, Prec<T>& P, const T* Q, double* y, hipStream_t 
     TRY(front2d<T>(g.n[0], f, g.nb, st));
     if constexpr (sizeof(T) == 8) zq = pre ? h->zvec : q;
     else zq = P.qT;
-  } else if (tiled) {
+  } else if (d3) {
     TRY(face_lifts3<T>(g, h->wv, Q, P.mq, P.Fx, P.Fy, P.Fz, P.Ux, P.Uy, P.Uz, st));
-  } else if (!d3) {
+  } else {
     TRY(face_lifts2<T>(g, h->wv, Q, P.ia, ft ? P.ft[0][0] : P.Fx, ft ? P.ft[0][1] : P.Fy, ft ? P.ft[1][0] : P.Ux,
                        ft ? P.ft[1][1] : P.Uy, st));
-  } else {
-    TRY(face_lift<T>(g, h->wv, Q, P.Fx, P.Fy, P.Fz, st));
-    TRY(face_lift_m<T>(g, h->w, Q, P.ia, P.Ux, P.Uy, P.Uz, st));
   }
   if (!lines) TRY(face_dst2<T>(h, P, 3, st, jobs, ft));
   tend(h, AHOC_K_LIFT, el, (double)TQ(g) * 7.0 * sizeof(T), st);
