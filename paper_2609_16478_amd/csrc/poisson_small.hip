@@ -10,6 +10,7 @@
 // 64^2 19 and 24, 96^2 43 and 33.  POISSON_SMALL_FLOPS lies between 64^2 and 80^2.
 #include "common.h"
 #include "kernels.h"
+#include "mfma_sine.h"
 
 #include <algorithm>
 #include <mutex>
@@ -18,23 +19,6 @@ namespace ahoc {
 
 namespace {
 
-template <typename T> struct Mma;
-template <> struct Mma<float> {
-  typedef float v4 __attribute__((ext_vector_type(4)));
-  static __device__ __forceinline__ v4 op(float a, float b, v4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int lk, int r) { return 4 * lk + r; }
-};
-template <> struct Mma<double> {
-  typedef double v4 __attribute__((ext_vector_type(4)));
-  static __device__ __forceinline__ v4 op(double a, double b, v4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int lk, int r) { return lk + 4 * r; }
-};
-
-__host__ __device__ constexpr int tpad(int j) { return j + (j >> 5); }
 constexpr int POISSON_UNITS = 2;  // units of 16 pencils x (16 odd + 16 even) outputs per wavefront
 constexpr double POISSON_SMALL_FLOPS = 1.3e6;
 
@@ -49,8 +33,8 @@ template <typename T> __host__ __device__ constexpr int plane_ld(int ni) {
 // f(pencil, k, value) takes output k (from 0) of each pencil after every read of the plane.
 template <typename T, bool ROWS, typename F>
 __device__ __forceinline__ void plane_pass(const T* x, int ld, int N, int npencil, const T* tab, F&& f) {
-  using M = Mma<T>;
-  using v4 = typename M::v4;
+  using S = SineOps<T>;
+  using v4 = typename S::v4;
   const int L = N - 1, Hm = N / 2, two_n = 2 * N, pairs = (Hm + 15) / 16;
   const int units = (npencil + 15) / 16 * pairs, nw = blockDim.x >> 6, w = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
@@ -73,13 +57,13 @@ __device__ __forceinline__ void plane_pass(const T* x, int ld, int N, int npenci
       T b = ROWS ? x[p * ld + N - mc - 1] : x[(N - mc - 1) * ld + p];
       if (m > Hm) a = T(0);
       if (m > Hm || 2 * m == N) b = T(0);
-      const T be = a + b, bo = a - b, se = tab[tpad(ie)], so = tab[tpad(io)];
+      const T be = a + b, bo = a - b, se = tab[sine_pad(ie)], so = tab[sine_pad(io)];
       ie += de;
       io += dd;
       ie = min(ie, ie - (unsigned)two_n);
       io = min(io, io - (unsigned)two_n);
-      ae[u] = ROWS ? M::op(be, se, ae[u]) : M::op(se, be, ae[u]);
-      ao[u] = ROWS ? M::op(bo, so, ao[u]) : M::op(so, bo, ao[u]);
+      ae[u] = ROWS ? S::mfma(be, se, ae[u]) : S::mfma(se, be, ae[u]);
+      ao[u] = ROWS ? S::mfma(bo, so, ao[u]) : S::mfma(so, bo, ao[u]);
     }
   }
   __syncthreads();
@@ -90,7 +74,7 @@ __device__ __forceinline__ void plane_pass(const T* x, int ld, int N, int npenci
     const int p0 = id / pairs * 16, j0 = id % pairs * 16;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int p = p0 + (ROWS ? M::row(lk, r) : li), k = 2 * (j0 + (ROWS ? li : M::row(lk, r)));
+      const int p = p0 + (ROWS ? S::row(lk, r) : li), k = 2 * (j0 + (ROWS ? li : S::row(lk, r)));
       if (p >= npencil) continue;
       if (k < L) f(p, k, ae[u][r]);
       if (k + 1 < L) f(p, k + 1, ao[u][r]);
@@ -104,25 +88,15 @@ template <typename T> __global__ void __launch_bounds__(1024) k_poisson_small(Po
   const int ld = plane_ld<T>(l0);
   T* x = reinterpret_cast<T*>(smem);
   T* tab0 = x + (size_t)l1 * ld;
-  T* tab1 = tab0 + tpad(2 * n0);
-  T* s0 = tab1 + tpad(2 * n1);
+  T* tab1 = tab0 + sine_pad(2 * n0);
+  T* s0 = tab1 + sine_pad(2 * n1);
   T* s1 = s0 + l0;
   // period tables sin(pi j / N) and eigenvalues of both axes
   auto tables = [&](T* tab, T* s, int ax) {
     const int N = a.n[ax];
     const T* sn = a.sn[ax];
     for (int i = threadIdx.x; i < 2 * N; i += blockDim.x) {
-      T v;
-      if (!sn) {
-        v = (T)sinpi((double)i / N);
-      } else if (a.half[ax]) {
-        const int j = i >= N ? i - N : i;
-        v = sn[j > N / 2 ? N - j : j];
-        if (i >= N) v = -v;
-      } else {
-        v = sn[i];
-      }
-      tab[tpad(i)] = v;
+      tab[sine_pad(i)] = sn ? sine_entry<T>(sn, N, a.half[ax], i) : (T)sinpi((double)i / N);
     }
     for (int i = threadIdx.x; i < N - 1; i += blockDim.x) {
       if (a.s[ax]) {
@@ -164,7 +138,7 @@ template <typename T> __global__ void __launch_bounds__(1024) k_poisson_small(Po
 
 template <typename T> size_t small_lds(int n0, int n1) {
   return sizeof(T) *
-         ((size_t)(n1 - 1) * plane_ld<T>(n0 - 1) + tpad(2 * n0) + tpad(2 * n1) + (n0 - 1) + (n1 - 1));
+         ((size_t)(n1 - 1) * plane_ld<T>(n0 - 1) + sine_pad(2 * n0) + sine_pad(2 * n1) + (n0 - 1) + (n1 - 1));
 }
 int small_units(int n0, int n1) {
   auto units = [](int N, int pencils) { return (pencils + 15) / 16 * ((N / 2 + 15) / 16); };
