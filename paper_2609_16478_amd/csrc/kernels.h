@@ -156,7 +156,6 @@ int mdot(const double* V, long long ld, int nvec, const double* w, long long n, 
 int maxpy(double* w, const double* V, long long ld, int nvec, const double* coef, int cstride, double sign,
           long long n, int ns, hipStream_t st);
 int axpby(long long n, double a, const double* x, double b, double* y, hipStream_t st);
-// y += a x with the per-work-group partial sums of <u, y> (u null: 0) and <y, y>, in part[0..nbk)
 // BiCGSTAB's vector steps with their scalars kept on the device.  part holds the nb1 work-groups'
 // parts of the dot products before the step (one vector after the other), part2 receives nb2
 // parts of those after it; coef = {alpha, alpha is good, omega, omega is good}.
@@ -170,6 +169,7 @@ int bicg_half(long long n, double rho, const double* part, int nb1, const double
 int bicg_full(long long n, const double* part, int nb1, const double* y, const double* z, const double* t,
               const double* rh, double* x, double* r, double* coef, double* part2, int nb2, hipStream_t st);
 int bicg_to_host(const double* part, int nb, int nvec, const double* coef, double* out, hipStream_t st);
+// w = a x + b y + c w
 int lin3(long long n, double a, const double* x, double b, const double* y, double c, double* w, hipStream_t st);
 // Segment-wise batch utilities (grid.y = segment): x_s = 0 where keep[s] == 0; gather of
 // per-instance arrays (device table of device pointers, null = zeros); scatter to them.

@@ -555,7 +555,7 @@ __global__ void __launch_bounds__(NT) k_arnoldi_one(double* __restrict__ V, long
 // w -= sum_v h_v V_v over the slice, h the sums of part (or hin), kept in hout by slice 0; then
 // the partial dot products <V_v, w> of the new w (sweep 1) or its partial <w, w> (sweep 2) into
 // part2.  A slice is at most ARN_SLICE entries, held in LDS between the two.
-constexpr int ARN_SLICE = 4096;
+constexpr int ARN_SLICE = 2048;  // the most that arnoldi_slices gives
 __device__ __forceinline__ void sum_partials(const double* __restrict__ part, int nbk, int nvec, int sg,
                                              double* __restrict__ h) {
   constexpr int U = 4;  // vectors in flight per wavefront
@@ -777,7 +777,7 @@ int back_solve(int ns, const double* H, int m, const double* gv, const int* kk, 
 // while every work-group can still sum their partials itself, else 2048.
 int arnoldi_slices(long long n) {
   const long long b = (n + 511) / 512;
-  return (int)(b <= ARN_INLINE ? b : std::max<long long>(ARN_INLINE, (n + 2047) / 2048));
+  return (int)(b <= ARN_INLINE ? b : std::max<long long>(ARN_INLINE, (n + ARN_SLICE - 1) / ARN_SLICE));
 }
 
 int arnoldi_step(double* V, long long ld, long long n, const ArnoldiArgs& g, hipStream_t st) {
