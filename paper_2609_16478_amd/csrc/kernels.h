@@ -192,9 +192,12 @@ struct ArnoldiArgs {
   int *ist, *act0;
   double *hist, *eres, *h1, *h2, *nrm, *part;
 };
-// a segment up to here is one work-group's step: 28 us at 4092 unknowns, the sliced step's four
-// launches about 30 us; longer ones leave the one compute unit behind
-constexpr long long ARN_ONE_MAX = 4096;
+// A segment up to here is one work-group's step.  A whole operator application and step in FP64,
+// one work-group against slices, cycles of 12 and of 30 vectors: 380 unknowns 111 and 122, 102 and
+// 119 us; 1020 97 and 112, 88 and 107; 2044 112 and 127, 106 and 122.  Beyond, the registers hold 8
+// basis vectors and one compute unit reads the others from L2 four times: 3068 174 and 175, 183 and
+// 166; 4092 170 and 172, 187 and 167.
+constexpr long long ARN_ONE_MAX = 2048;
 constexpr int ARN_INLINE = 256;          // most partial sums that every work-group adds up itself
 int arnoldi_slices(long long n);
 int arnoldi_step(double* V, long long ld, long long n, const ArnoldiArgs& a, hipStream_t st);

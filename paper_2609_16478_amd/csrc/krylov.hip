@@ -786,11 +786,11 @@ int arnoldi_step(double* V, long long ld, long long n, const ArnoldiArgs& g, hip
   ArnoldiState a{g.H, g.cs, g.sn, g.gv, g.resid, g.bnorm, g.ist, g.hist, g.eres, g.tol, g.ns, g.m, g.j, g.max_iters,
                  g.inexact ? 1 : 0};
   if (n <= ARN_ONE_MAX) {
+    static_assert(ARN_ONE_MAX <= 512 * 4, "the last kernel's entries");
     const dim3 grid(g.ns);
     if (n <= 512) hipLaunchKernelGGL((k_arnoldi_one<512, 1, 32>), grid, dim3(512), 0, st, V, ld, n, a);
     else if (n <= 1024) hipLaunchKernelGGL((k_arnoldi_one<512, 2, 32>), grid, dim3(512), 0, st, V, ld, n, a);
-    else if (n <= 2048) hipLaunchKernelGGL((k_arnoldi_one<512, 4, 16>), grid, dim3(512), 0, st, V, ld, n, a);
-    else hipLaunchKernelGGL((k_arnoldi_one<512, 8, 8>), grid, dim3(512), 0, st, V, ld, n, a);
+    else hipLaunchKernelGGL((k_arnoldi_one<512, 4, 16>), grid, dim3(512), 0, st, V, ld, n, a);
     AHOC_HIP_TRY(hipGetLastError());
     return ST_OK;
   }
