@@ -59,3 +59,18 @@ def test_lines_in_a_batch(ah, prec, precond):
         with ah.Solver(p, tol=1e-12) as s:
             ref = s.solve()[0]
         assert float((u - ref).abs().max()) <= 1e-9 * float(ref.abs().max())
+
+
+@pytest.mark.parametrize("N", [32, 128, 512, 1024])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_both_forms_reach_the_tolerance(ah, N, prec):
+    """The premise of the comparison above: both solves are done to the tolerance, or to the
+    operator's rounding (a few 1e-13 times a condition number below N: 1e-10 at the most)."""
+    p = W.manufactured(A2, U2, (N, N), (0.0, 0.0), (1.0, 0.5), navier=(False, False, True, False))
+    with ah.Solver(p, precision=ah.FP64 if prec == "fp64" else ah.MIXED, tol=1e-12) as s:
+        for variant in (0, 3):
+            ah.set_dst_variant(variant)
+            _, _, q, st = s.solve(want_q=True)
+            ah.set_dst_variant(0)
+            print(N, prec, variant, st.converged, st.schur_relres)
+            assert st.converged or st.schur_relres <= 1e-10, st
