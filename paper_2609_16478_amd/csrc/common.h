@@ -220,9 +220,10 @@ int face_reduce(const T* W, long long planes, int ny, int nx, int px, const T* w
 // from in and out, that a fused pass of a length without an FFT plan keeps its scaled
 // spectrum in (a pass that writes elsewhere than it reads can split a pencil's outputs over
 // work-groups).  cols: columns that a row pass with in != out writes to each row, those from L
-// on as zeros (0: L alone).  Whatever fills a padded array has to write its padding: the strided
-// FFT passes pair the last column with it, in one complex sequence, and leave rounding noise (or
-// NaN) there, so that what an earlier call left would show in the next one's results.
+// on as zeros (0: L alone).  Whatever fills a padded array has to write the padding next to its
+// values: the strided FFT passes pair the last column with it where their number is odd, in one
+// complex sequence, and leave rounding noise (or NaN) there, so that what an earlier call left would
+// show in the next one's results.
 template <typename T>
 int dst_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long long inner,
              long long pitch, const DstScale<T>* fused, int tile_seqs, hipStream_t st,
