@@ -604,17 +604,13 @@ int poisson(ahoc_handle* h, Prec<T>& P, T* buf, const DstScale<T>& sc, hipStream
   const T* src = in ? in : buf;
   T* cur = buf;
   bool first = true;
-  auto rows_lift = [&](T* out, long long rows) {  // the first pass with lf: from the source to `out`
-    TRY(dst_rows_lift_pass<T>(P.tb[0].N, P.tb[0].tw, P.tb[0].sn, src, out, rows, g.px, *lf, st));
-    return src == out ? (int)ST_OK : zero_cols<T>(out, rows, g.ni[0], paired_cols(g), g.px, st);
-  };
   auto run = [&](int kind, const DstTables<T>& tb, long long outer, long long inner,
                  const DstScale<T>* f, int tile) -> int {
     hipEvent_t e = tbegin(h, st);
     T* other = P.scr ? (cur == buf ? P.scr : buf) : nullptr;
     if (!tb.ppt && !f && other) std::swap(cur, other);
     // with lf, the first (row) pass adds the lift's face layers to its input while loading
-    const int rc = (first && lf) ? rows_lift(cur, outer)
+    const int rc = (first && lf) ? dst_rows_lift_pass<T>(tb.N, tb.tw, tb.sn, src, cur, outer, g.px, *lf, st)
                                  : dst_pass<T>(tb, src, cur, outer, inner, g.px, f, tile, st, nullptr, other, paired_cols(g));
     first = false;
     src = cur;
@@ -629,7 +625,7 @@ int poisson(ahoc_handle* h, Prec<T>& P, T* buf, const DstScale<T>& sc, hipStream
   } else if (P.planes && dst_get_variant() == 0) {
     hipEvent_t e = tbegin(h, st);
     if (lf) {
-      TRY(rows_lift(P.scr, (long long)g.ni[1] * g.ni[2]));
+      TRY(dst_rows_lift_pass<T>(P.tb[0].N, P.tb[0].tw, P.tb[0].sn, src, P.scr, (long long)g.ni[1] * g.ni[2], g.px, *lf, st));
       TRY(dst_pass<T>(P.tb[1], P.scr, P.scr, g.ni[2], g.px, g.px, nullptr, P.tile[1], st, nullptr, nullptr));
     } else {
       TRY((dst_plane_pass<T, T, T>(P.tb[0], P.tb[1], src, g.px, P.scr, g.px, g.ni[2], st)));

@@ -228,9 +228,6 @@ template <typename T>
 int dst_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long long inner,
              long long pitch, const DstScale<T>* fused, int tile_seqs, hipStream_t st,
              const DstFaces<T>* faces = nullptr, T* tmp = nullptr, int cols = 0);
-// out[r * pitch + c] = 0 for lo <= c < hi, r < rows
-template <typename T> int zero_cols(T* out, long long rows, int lo, int hi, long long pitch, hipStream_t st);
-
 // Length-specialised kernels (dst_fast.hip) for N in {32, 64, 96, ..., 4096}.
 bool dst_fast_supported(int N);
 enum { DST_PASS_ROWS = 0, DST_PASS_STRIDED = 1, DST_PASS_FUSED = 2 };
@@ -257,7 +254,8 @@ template <typename T> struct RowLift {
   long long xplane = 0, yplane = 0, zplane = 0;  // offset of the high face's array (3-D)
   int dim = 3, ni1 = 0, ni2 = 1, px = 0;
 };
-// Row pass whose input is in + the lift's face layers (no lift pass); in may equal out.
+// Row pass whose input is in + the lift's face layers (no lift pass); in may equal out.  Column N - 1
+// of each row of out, the padding next to its values, is written as zero (pitch >= N).
 // dst_rows_lift_supported: whether the pass exists for this length and shape (checked
 // before anything is launched).
 template <typename T> bool dst_rows_lift_supported(int N, long long nrows, long long pitch);

@@ -651,15 +651,15 @@ __global__ void k_zero_cols(T* __restrict__ out, long long rows, int lo, int w, 
     out[r * pitch + lo + (e - r * w)] = T(0);
   }
 }
-template <typename T> int zero_cols(T* out, long long rows, int lo, int hi, long long pitch, hipStream_t st) {
+// out[r * pitch + c] = 0 for lo <= c < hi, r < rows
+template <typename T>
+static int zero_cols(T* out, long long rows, int lo, int hi, long long pitch, hipStream_t st) {
   if (rows <= 0 || hi <= lo) return ST_OK;
   const long long blocks = std::min<long long>((rows * (hi - lo) + 255) / 256, 65536);
   hipLaunchKernelGGL(k_zero_cols<T>, dim3((unsigned)blocks), dim3(256), 0, st, out, rows, lo, hi - lo, pitch);
   AHOC_HIP_TRY(hipGetLastError());
   return ST_OK;
 }
-template int zero_cols<float>(float*, long long, int, int, long long, hipStream_t);
-template int zero_cols<double>(double*, long long, int, int, long long, hipStream_t);
 
 template <typename T>
 int dst_pass(const DstTables<T>& tb, const T* in, T* out, long long outer, long long inner,

@@ -193,6 +193,10 @@ __global__ void __launch_bounds__(rows_nseq<N>()*(N / RPlan<N>::PPT)) k_dst_rows
       const unsigned e = (unsigned)((m - 1) * (int)sizeof(T));
       if (oka) str_<T, NT>(dst, oa + e, v.x);
       if (okb) str_<T, NT>(dst, ob + e, v.y);
+    } else if constexpr (LIFT) {  // m = N: the padding column that a strided pass pairs with the last
+      const unsigned e = (unsigned)((N - 1) * (int)sizeof(T));
+      if (oka) str_<T, NT>(dst, oa + e, T(0));
+      if (okb) str_<T, NT>(dst, ob + e, T(0));
     }
   }
 }
@@ -468,7 +472,7 @@ template <typename T, int N> bool rows_lift_ok(long long nrows, long long pitch)
 }  // namespace fast
 
 template <typename T> bool dst_rows_lift_supported(int N, long long nrows, long long pitch) {
-  if (pitch < N - 1) return false;
+  if (pitch < N) return false;
   switch (N) {
     case 32: return fast::rows_lift_ok<T, 32>(nrows, pitch);
     case 64: return fast::rows_lift_ok<T, 64>(nrows, pitch);
@@ -491,7 +495,7 @@ template bool dst_rows_lift_supported<double>(int, long long, long long);
 template <typename T>
 int dst_rows_lift_pass(int N, const cx<T>* tw, const T* sn, const T* in, T* out, long long nrows, long long pitch,
                        const RowLift<T>& lf, hipStream_t st) {
-  if (pitch < N - 1 || lf.ni1 <= 0 || (lf.dim != 2 && lf.dim != 3)) return ST_INVALID;
+  if (pitch < N || lf.ni1 <= 0 || (lf.dim != 2 && lf.dim != 3)) return ST_INVALID;
   switch (N) {
     case 32: return fast::rows_lift_launch<T, 32>(in, out, tw, sn, nrows, pitch, lf, st);
     case 64: return fast::rows_lift_launch<T, 64>(in, out, tw, sn, nrows, pitch, lf, st);
