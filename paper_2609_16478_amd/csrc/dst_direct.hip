@@ -20,8 +20,8 @@
 // conflicts hide behind the MFMAs (64 cycles each in FP64) once two pencil tiles share it.
 // Against one thread per output (the form this replaces): FP32 along y of 199 x 149 x 119
 // points 549 -> 19 us a call, an FP64 Poisson solve of 99 x 89 x 74 points 227 -> 61 us, a 2-D
-// 500 x 300 FP64 solve (25 GMRES iterations) 118.8 -> 7.4 ms; errors against 64-bit sums no
-// larger (FP32 2.2e-7 -> 1.6e-7).  Where a pass has few pencils (lines of 2-D faces) its time
+// 500 x 300 FP64 solve (25 GMRES iterations) 118.8 -> 7.4 ms (3.5 with the Krylov step and
+// the faces in few launches); errors against 64-bit sums no larger (FP32 2.2e-7 -> 1.6e-7).  Where a pass has few pencils (lines of 2-D faces) its time
 // is latency: four lines of N = 1024 in FP64 took 25 us with a 128-step sum per wavefront and
 // staging loops that waited for each load, 10.7 us with the sum split over four wavefronts and
 // one trip to memory.

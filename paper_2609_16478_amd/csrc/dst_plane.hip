@@ -19,13 +19,13 @@
 // before the second sum reads it.  The work-groups of a plane sit on one XCD: the plane's second
 // to fourth read hit its L2.
 //
-// A Dirichlet solve, separate passes against planes: 128^3 97 -> 64 us in FP64 and 74 -> 51 in
-// FP32, 99 x 89 x 74 points 61 -> 51 and 54 -> 38, 64^3 38 -> 23 and 36 -> 22, 32^3 34 -> 19
-// and 33 -> 19; with the slowest axis below 48^3 122 -> 20 and 120 -> 18.  FP32 errors against 64
-// bits (rms of a solve): 128^3 5.8e-7 -> 5.1e-7, 64^3 3.7e-7 -> 3.0e-7, 99 x 89 x 74 points 4.0e-7
-// -> 3.6e-7.  A pass at 128^3 in
-// FP64 takes 20 us: 7 of matrix-core time, 5 of the other vector instructions, 3 of LDS and the
-// trips to memory, in phases that the two work-groups of a CU run side by side.
+// A Dirichlet solve between dense arrays, a pass per axis against planes (and the slowest axis in
+// one launch to 96), FP64 and FP32: 128^3 98 -> 61 and 71 -> 50 us, 99 x 89 x 74 points 65 -> 52 and
+// 53 -> 39, 96^3 69 -> 49 and 57 -> 37, 64^3 32 -> 21 and 32 -> 19, 48^3 51 -> 20 and 48 -> 18, 32^3
+// 29 -> 18 and 29 -> 17.  FP32 errors against 64 bits (rms of a solve): 128^3 5.8e-7 -> 5.1e-7, 64^3
+// 3.7e-7 -> 3.0e-7, 99 x 89 x 74 points 4.0e-7 -> 3.6e-7.  A pass at 128^3 in FP64 takes 20 us: 7 of
+// matrix-core time, 5 of the other vector instructions, 3 of LDS and the trips to memory, in phases
+// that the two work-groups of a CU run side by side.
 #include "common.h"
 #include "mfma_sine.h"
 
