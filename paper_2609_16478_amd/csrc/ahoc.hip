@@ -480,7 +480,7 @@ template <typename T> int prec_init(ahoc_handle* h, Prec<T>& P, int tile_opt, hi
   }
   TRY(alloc_int(h, &P.bufA, st));
   TRY(alloc_int(h, &P.bufB, st));
-  P.planes = planes_pay<T>(g);
+  P.planes = tile_opt <= 0 && planes_pay<T>(g);  // an explicit tile is one of the passes per axis
   // setup-time choice between the FFT and the matrix-core pass for the plain passes of the
   // operator, timed on their own shapes: the x (row) passes; in 3-D also the strided y passes
   if (g.dim == 2) {
@@ -653,7 +653,7 @@ template <typename T> int poisson_dense(ahoc_handle* h, Prec<T>& P, const double
   // dense caller arrays (row length n_x - 1) <-> padded interior rows
   const Geom& g = h->g;
   const long long rows = (long long)g.ni[1] * g.ni[2];
-  if (g.dim == 2 && poisson_small_ok<T>(g.n[0], g.n[1])) {
+  if (g.dim == 2 && P.tile[0] == 0 && P.tile[1] == 0 && poisson_small_ok<T>(g.n[0], g.n[1])) {
     PoissonSmall<T> a{};
     a.g = gin;
     a.w = wout;
